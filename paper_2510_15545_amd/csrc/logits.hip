@@ -98,11 +98,15 @@ __device__ __forceinline__ float scaled(uint32_t bits16, float c) { return bf16_
 // the scaled exponent z of a logit: fma(logit, c, b31) with b31 = 31 - mu
 __device__ __forceinline__ float expo(uint32_t bits16, float c, float b31) { return fmaf(bf16_value(bits16), c, b31); }
 
+// Eight bf16 at an address aligned to 2 bytes only: rows of an odd stride start anywhere, and
+// gfx950's 16-byte global loads take any address, so every row takes the wide path.
+typedef unsigned int u4u __attribute__((ext_vector_type(4), aligned(2)));
+
 // 16 consecutive logits x0 .. x0 + 15 of a lane (the sampler's crossing chunk; zero bits past v).
-__device__ __forceinline__ void load16(const uint16_t *row, int x0, int v, bool vec, uint32_t (&w)[8]) {
-    if (vec && x0 + 16 <= v) {
-        const uint4 a = *reinterpret_cast<const uint4 *>(row + x0);
-        const uint4 b = *reinterpret_cast<const uint4 *>(row + x0 + 8);
+__device__ __forceinline__ void load16(const uint16_t *row, int x0, int v, uint32_t (&w)[8]) {
+    if (x0 + 16 <= v) {
+        const u4u a = *reinterpret_cast<const u4u *>(row + x0);
+        const u4u b = *reinterpret_cast<const u4u *>(row + x0 + 8);
         w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w;
         w[4] = b.x; w[5] = b.y; w[6] = b.z; w[7] = b.w;
     } else {
@@ -120,20 +124,15 @@ __device__ __forceinline__ void load16(const uint16_t *row, int x0, int v, bool 
 // consecutive logits a lane would make each span 2 KB); 0 past v.  NT: the non-temporal hint
 // (the row's last read).  A chunk's sums and maximum do not depend on the order.
 template <bool NT>
-__device__ __forceinline__ void load16s(const uint16_t *row, int c, int lane, int v, bool vec, uint32_t (&w)[8]) {
+__device__ __forceinline__ void load16s(const uint16_t *row, int c, int lane, int v, uint32_t (&w)[8]) {
     const int xb = c * kChunk;
-    if (vec && xb + kChunk <= v) {
+    if (xb + kChunk <= v) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const uint4 *src = reinterpret_cast<const uint4 *>(row + xb + u * 512 + lane * 8);
-            uint4 t;
-            if constexpr (NT) {
-                typedef unsigned int u4v __attribute__((ext_vector_type(4)));
-                const u4v q = __builtin_nontemporal_load(reinterpret_cast<const u4v *>(src));
-                t = make_uint4(q.x, q.y, q.z, q.w);
-            } else {
-                t = *src;
-            }
+            const u4u *src = reinterpret_cast<const u4u *>(row + xb + u * 512 + lane * 8);
+            u4u t;
+            if constexpr (NT) t = __builtin_nontemporal_load(src);
+            else t = *src;
             w[4 * u] = t.x;
             w[4 * u + 1] = t.y;
             w[4 * u + 2] = t.z;
@@ -162,7 +161,7 @@ __device__ __forceinline__ uint32_t elem(const uint32_t (&w)[8], int k) {
 
 struct LogitsParams {
     LogitsArgs a;
-    int32_t nc, vec;
+    int32_t nc;
 };
 
 // Per-row table of the Q31 weights.  For a fixed scale and offset the weight of a logit is a
@@ -256,16 +255,16 @@ __device__ __forceinline__ uint64_t chunk_total(uint64_t a) {
 // loads of its first two chunks, so that their latency passes while the table is built; waves
 // take chunks from the LDS counter *next (which the caller sets to kWaves before a barrier that
 // precedes the call; wave w starts at chunk w), one chunk in flight ahead of the one summed.
-__device__ __forceinline__ void chunk_sums(const uint16_t *row, int v, int nc, bool vec, float sc, float b31,
+__device__ __forceinline__ void chunk_sums(const uint16_t *row, int v, int nc, float sc, float b31,
                                            uint64_t *tab, uint64_t *sh_part, int *next) {
     const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     uint32_t w[8] = {}, nx[8] = {};
     int c = wave, cn = nc, cnn = nc;  // chunk summed, chunk in flight, the one after it
     if (c < nc) {
-        load16s<true>(row, c, lane, v, vec, w);
+        load16s<true>(row, c, lane, v, w);
         cn = vcore::next_chunk(next, c, kWaves);
         if (cn < nc) {
-            load16s<true>(row, cn, lane, v, vec, nx);
+            load16s<true>(row, cn, lane, v, nx);
             cnn = vcore::next_chunk(next, cn, kWaves);
         }
     }
@@ -298,7 +297,7 @@ __device__ __forceinline__ void chunk_sums(const uint16_t *row, int v, int nc, b
             for (int k = 0; k < 8; ++k) w[k] = nx[k];
             cn = cnn;
             if (cn < nc) {
-                load16s<true>(row, cn, lane, v, vec, nx);
+                load16s<true>(row, cn, lane, v, nx);
                 cnn = vcore::next_chunk(next, cn, kWaves);
             }
         }
@@ -308,7 +307,7 @@ __device__ __forceinline__ void chunk_sums(const uint16_t *row, int v, int nc, b
 // Inverse-CDF sample of a row from its chunk sums (one wave).  When t >= 0 the entry at t
 // counts adj instead of the before its chunk sum holds (the residual's entry); Z is the row's
 // total so adjusted.  The first largest x when Z = 0.
-__device__ inline int sample_row(const uint16_t *row, int v, int nc, bool vec, float sc, float b31,
+__device__ inline int sample_row(const uint16_t *row, int v, int nc, float sc, float b31,
                                  const uint64_t *tab, int t, uint64_t adj, uint64_t before, float u,
                                  const uint64_t *sh_part) {
     const int lane = threadIdx.x % kWave;
@@ -364,7 +363,7 @@ __device__ inline int sample_row(const uint16_t *row, int v, int nc, bool vec, f
     // the crossing chunk: lane holds elements cs*1024 + lane*16 + [0, 16)
     const int x0 = cs * kChunk + lane * 16;
     uint32_t w[8];
-    load16(row, x0, v, vec, w);
+    load16(row, x0, v, w);
     uint64_t qv[16];
     lane_weights(tab, w, x0, v, sc, b31, qv);
     uint64_t sum = 0;
@@ -408,7 +407,6 @@ __global__ void __launch_bounds__(kThreads) verify_logits_row(LogitsParams p) {
     const float it = a.inv_temp[b];
     const float cb = it * kLog2e;  // the stream's base-2 scale
     const int v = a.v_t, nc = p.nc;
-    const bool vec = p.vec != 0;
     TT_STAMP(0);
     if (!(M >= 0 && M <= a.max_m && it > 0.0f)) {
         if (tid == 0) {
@@ -487,7 +485,7 @@ __global__ void __launch_bounds__(kThreads) verify_logits_row(LogitsParams p) {
         const uint16_t *row = a.logits + rr * a.ld;
         const float L = sh_L;
         const float b31 = 31.0f - L * kLog2e;
-        chunk_sums(row, v, nc, vec, cb, b31, sh_tab, sh_part, &sh_ctr);
+        chunk_sums(row, v, nc, cb, b31, sh_tab, sh_part, &sh_ctr);
         if (wave < 12) TT_STAMP_WAVE(4 + wave);
         __syncthreads();
         TT_STAMP(2);
@@ -499,7 +497,7 @@ __global__ void __launch_bounds__(kThreads) verify_logits_row(LogitsParams p) {
             adj = q31(fminf(fmaxf(sh_P - sh_q, 0.0f), 1.0f));
             before = e31_at(expo((uint32_t)sh_x, cb, b31));  // the weight the chunk sums counted at t
         }
-        const int token = sample_row(row, v, nc, vec, cb, b31, sh_tab, t, adj, before, a.u_sample[b], sh_part);
+        const int token = sample_row(row, v, nc, cb, b31, sh_tab, t, adj, before, a.u_sample[b], sh_part);
         if (lane == 0) {
             a.n_accepted[b] = r;
             a.out_token[b] = token;
@@ -520,9 +518,9 @@ __global__ void __launch_bounds__(kThreads) verify_logits_row(LogitsParams p) {
         // pass 1: the row's largest x
         float m = -INFINITY;
         uint32_t w[8] = {}, nx[8] = {};
-        if (wave < nc) load16s<false>(row, wave, lane, v, vec, w);
+        if (wave < nc) load16s<false>(row, wave, lane, v, w);
         for (int c = wave; c < nc; c += kWaves) {
-            if (c + kWaves < nc) load16s<false>(row, c + kWaves, lane, v, vec, nx);
+            if (c + kWaves < nc) load16s<false>(row, c + kWaves, lane, v, nx);
             if ((c + 1) * kChunk <= v) {
 #pragma unroll
                 for (int k = 0; k < 16; ++k) m = fmaxf(m, scaled(elem(w, k), cb));
@@ -547,7 +545,7 @@ __global__ void __launch_bounds__(kThreads) verify_logits_row(LogitsParams p) {
         m = sh_m;
         // pass 2: chunk sums of e31
         const float b31 = 31.0f - m;
-        chunk_sums(row, v, nc, vec, cb, b31, sh_tab, sh_part, &sh_ctr);
+        chunk_sums(row, v, nc, cb, b31, sh_tab, sh_part, &sh_ctr);
         __syncthreads();
         // S, the acceptance test of position j, and the residual's entry at t_j
         if (wave == 0) {
@@ -581,7 +579,7 @@ __global__ void __launch_bounds__(kThreads) verify_logits_row(LogitsParams p) {
         __syncthreads();
         if (sh_next) continue;
         if (wave == 0) {
-            const int token = sample_row(row, v, nc, vec, cb, b31, sh_tab, sh_t, sh_adj, sh_before, a.u_sample[b], sh_part);
+            const int token = sample_row(row, v, nc, cb, b31, sh_tab, sh_t, sh_adj, sh_before, a.u_sample[b], sh_part);
             if (lane == 0) {
                 a.n_accepted[b] = j;
                 a.out_token[b] = token;
@@ -598,7 +596,6 @@ int launch_verify_logits(const LogitsArgs &a, hipStream_t stream) {
     LogitsParams p;
     p.a = a;
     p.nc = (a.v_t + kChunk - 1) / kChunk;
-    p.vec = ((reinterpret_cast<uintptr_t>(a.logits) & 15u) == 0 && (a.ld % 8) == 0) ? 1 : 0;
     // the chunk sums (up to 64 KiB at the longest rows) sit beside the 64 KiB weight table in LDS
     const size_t lds = 8 * (size_t)p.nc;
     if (hipFuncSetAttribute(reinterpret_cast<const void *>(&verify_logits_row),

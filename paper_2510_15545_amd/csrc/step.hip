@@ -38,7 +38,7 @@ struct SParams {
     StepArgs s;
     uint64_t *zsum;
     int32_t *rsel;
-    int32_t nc, vec4;
+    int32_t nc;
 };
 
 // STREAM = false: the kernel stops once gamma is known and leaves it in rsel for the split
@@ -168,9 +168,8 @@ __global__ void __launch_bounds__(kThreads) step_fused(SParams p) {
     const float rq = sh_rq;
     const int vt = ve.v_t;
     const float *row = ve.target_probs + (int64_t)(t0 + b + r) * ve.target_ld;
-    const bool vec = p.vec4 != 0;
     const float rp = sh_rp;
-    vcore::stream_chunks(row, vt, vec, 0, p.nc, kThreads / kWave, rtok, rq, rp,
+    vcore::stream_chunks(row, vt, 0, p.nc, kThreads / kWave, rtok, rq, rp,
                          [&](int c, uint64_t sum) { sh_part[c] = sum; }, &sh_next);
     TT_STAMP(4);
     __syncthreads();
@@ -178,7 +177,7 @@ __global__ void __launch_bounds__(kThreads) step_fused(SParams p) {
     if (wave != 0) return;
     uint64_t Z;
     const int token =
-        vcore::wave_sample(row, nullptr, vt, p.nc, vec, [&](int c) { return sh_part[c]; }, us, rtok, rq, &Z);
+        vcore::wave_sample(row, nullptr, vt, p.nc, [&](int c) { return sh_part[c]; }, us, rtok, rq, &Z);
     if (lane == 0) {
         ve.n_accepted[b] = r;
         ve.out_token[b] = token;
@@ -215,7 +214,6 @@ SParams make_sparams(const StepArgs &s, const VerifyLayout &L) {
     p.zsum = reinterpret_cast<uint64_t *>(ws + L.zsum);
     p.rsel = reinterpret_cast<int32_t *>(ws + L.rsel);
     p.nc = L.n_chunks;
-    p.vec4 = ((reinterpret_cast<uintptr_t>(s.ve.target_probs) & 15u) == 0 && (s.ve.target_ld % 4) == 0) ? 1 : 0;
     return p;
 }
 

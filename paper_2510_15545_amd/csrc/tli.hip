@@ -13,7 +13,7 @@
 // One 1024-thread workgroup per row, two passes over the row:
 //   1. coalesced reads of q and d2t (16-byte loads when the rows allow), Q62 sums in
 //      registers, a wave and then a workgroup reduction of the 128-bit sums;
-//   2. coalesced reads of t2d and writes of q' (16-byte stores when aligned), with q(x)
+//   2. coalesced reads of t2d and writes of q' (16-byte stores), with q(x)
 //      gathered from the row read in pass 1 (it is still in L2 or the Infinity Cache).
 // The row is read from HBM once; the maps are shared by every row and stay in cache.
 #include "verify_core.h"
@@ -68,7 +68,7 @@ __device__ inline float q62_to_f32(U128 n) {
 // S, the mass row q puts on the intersection: every intersected q(x) (clamped to [0, 1])
 // truncated to Q62 and the integers summed exactly, rounded once to fp32.  Called by every
 // thread of the workgroup (barriers inside); sh_part holds a partial sum per wave.
-__device__ float row_mass(const float *q, const int32_t *d2t, int v_d, bool vec_in, U128 *sh_part, float *sh_S) {
+__device__ float row_mass(const float *q, const int32_t *d2t, int v_d, U128 *sh_part, float *sh_S) {
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     U128 acc{0, 0};
     auto add = [&](float x, int32_t m) {  // branch-free: the loads stay batched
@@ -76,9 +76,7 @@ __device__ float row_mass(const float *q, const int32_t *d2t, int v_d, bool vec_
         acc = add128(acc, U128{q62(clamp01(x)) & keep, 0});
     };
     int x0 = 0;
-    if (vec_in) {
-        const float4 *q4 = reinterpret_cast<const float4 *>(q);
-        const int4 *m4 = reinterpret_cast<const int4 *>(d2t);
+    {
         const int n4 = v_d / 4;
         int k = tid;
         for (; k + (kUnroll - 1) * kThreads < n4; k += kUnroll * kThreads) {  // kUnroll loads of each in flight
@@ -86,8 +84,8 @@ __device__ float row_mass(const float *q, const int32_t *d2t, int v_d, bool vec_
             int4 m[kUnroll];
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
-                v[u] = q4[k + u * kThreads];
-                m[u] = m4[k + u * kThreads];
+                v[u] = vcore::load4(q + 4 * (k + u * kThreads));
+                m[u] = vcore::load4(d2t + 4 * (k + u * kThreads));
             }
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
@@ -98,8 +96,8 @@ __device__ float row_mass(const float *q, const int32_t *d2t, int v_d, bool vec_
             }
         }
         for (; k < n4; k += kThreads) {
-            const float4 v = q4[k];
-            const int4 m = m4[k];
+            const float4 v = vcore::load4(q + 4 * k);
+            const int4 m = vcore::load4(d2t + 4 * k);
             add(v.x, m.x);
             add(v.y, m.y);
             add(v.z, m.z);
@@ -124,7 +122,7 @@ __device__ float row_mass(const float *q, const int32_t *d2t, int v_d, bool vec_
 // outside [0, v_d): the entry is 0 either way); 0 when S is not positive.
 __device__ __forceinline__ float qprime(float g, float S) { return S > 0.0f ? clamp01(g) / S : 0.0f; }
 
-__global__ void __launch_bounds__(kThreads) tli_rows(TliArgs a, int vec_in, int vec_out) {
+__global__ void __launch_bounds__(kThreads) tli_rows(TliArgs a) {
     const int r = blockIdx.x;
     const int tid = threadIdx.x;
     const float *q = a.draft_probs + (int64_t)r * a.draft_ld;
@@ -133,7 +131,7 @@ __global__ void __launch_bounds__(kThreads) tli_rows(TliArgs a, int vec_in, int 
     __shared__ float sh_S;
 
     // 1. exact Q62 sum of the intersected mass
-    const float S = row_mass(q, a.d2t, a.v_d, vec_in != 0, sh_part, &sh_S);
+    const float S = row_mass(q, a.d2t, a.v_d, sh_part, &sh_S);
 
     // 2. q' over the target vocabulary
     // every lane loads (q[0] outside the intersection) so the gathers of a batch stay in flight together
@@ -142,28 +140,27 @@ __global__ void __launch_bounds__(kThreads) tli_rows(TliArgs a, int vec_in, int 
         return (x >= 0 && x < a.v_d && S > 0.0f) ? clamp01(g) / S : 0.0f;
     };
     int y0 = 0;
-    if (vec_out) {
-        const int4 *m4 = reinterpret_cast<const int4 *>(a.t2d);
-        float4 *o4 = reinterpret_cast<float4 *>(out);
+    auto store4 = [&](int k, vcore::f4u v) { *reinterpret_cast<vcore::f4u *>(out + 4 * k) = v; };
+    {
         const int n4 = a.v_t / 4;
         int k = tid;
         for (; k + (kUnroll - 1) * kThreads < n4; k += kUnroll * kThreads) {
             int4 m[kUnroll];
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) m[u] = m4[k + u * kThreads];
+            for (int u = 0; u < kUnroll; ++u) m[u] = vcore::load4(a.t2d + 4 * (k + u * kThreads));
             float4 g[kUnroll];
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u)
                 g[u] = make_float4(gather(m[u].x), gather(m[u].y), gather(m[u].z), gather(m[u].w));
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u)
-                o4[k + u * kThreads] = make_float4(value(m[u].x, g[u].x), value(m[u].y, g[u].y),
-                                                   value(m[u].z, g[u].z), value(m[u].w, g[u].w));
+                store4(k + u * kThreads, vcore::f4u{value(m[u].x, g[u].x), value(m[u].y, g[u].y),
+                                                    value(m[u].z, g[u].z), value(m[u].w, g[u].w)});
         }
         for (; k < n4; k += kThreads) {
-            const int4 m = m4[k];
+            const int4 m = vcore::load4(a.t2d + 4 * k);
             const float4 g = make_float4(gather(m.x), gather(m.y), gather(m.z), gather(m.w));
-            o4[k] = make_float4(value(m.x, g.x), value(m.y, g.y), value(m.z, g.z), value(m.w, g.w));
+            store4(k, vcore::f4u{value(m.x, g.x), value(m.y, g.y), value(m.z, g.z), value(m.w, g.w)});
         }
         y0 = 4 * n4;
     }
@@ -190,15 +187,15 @@ constexpr int kWaves = kThreads / kWave;
 
 struct TliVerifyParams {
     TliVerifyArgs a;
-    int32_t nc, vec_t, vec_d;
+    int32_t nc;
 };
 
 // The 16 draft ids t2d of a lane's elements x0 .. x0+15 (x0 = c*1024 + lane*16; -1 past v_t).
-__device__ __forceinline__ void load_x(const TliVerifyArgs &a, int x0, bool vec, int32_t (&xs)[16]) {
-    if (vec && x0 + 16 <= a.v_t) {
+__device__ __forceinline__ void load_x(const TliVerifyArgs &a, int x0, int32_t (&xs)[16]) {
+    if (x0 + 16 <= a.v_t) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int4 t = *reinterpret_cast<const int4 *>(a.t2d + x0 + 4 * q);
+            const int4 t = vcore::load4(a.t2d + x0 + 4 * q);
             xs[4 * q] = t.x;
             xs[4 * q + 1] = t.y;
             xs[4 * q + 2] = t.z;
@@ -211,10 +208,10 @@ __device__ __forceinline__ void load_x(const TliVerifyArgs &a, int x0, bool vec,
 }
 
 // Their target probabilities (0 past v_t) and ids (the sampler's crossing chunk, in position order).
-__device__ __forceinline__ void load_px(const TliVerifyArgs &a, const float *prow, int x0, bool vec, float (&pv)[16],
+__device__ __forceinline__ void load_px(const TliVerifyArgs &a, const float *prow, int x0, float (&pv)[16],
                                         int32_t (&xs)[16]) {
-    vcore::read16(prow, x0, a.v_t, vec, pv);
-    load_x(a, x0, vec, xs);
+    vcore::read16(prow, x0, a.v_t, pv);
+    load_x(a, x0, xs);
 }
 
 // The draft masses q(x) at the 16 ids (0 for an id outside [0, v_d), or without a draft row).
@@ -241,15 +238,14 @@ __device__ __forceinline__ uint64_t residual16(const float (&pv)[16], const floa
 // The row pass in vcore::load_chunk's element order (lane l holds elements 256 u + 4 l + j of a
 // chunk, so each 16-byte load instruction covers 1 KB of the row): the target probabilities
 // with the non-temporal hint, the 16 ids t2d in the same order (-1 past v_t).
-__device__ __forceinline__ void load_px_strided(const TliVerifyArgs &a, const float *prow, int c, bool vec,
-                                                float4 (&pv)[4], int32_t (&xs)[16]) {
+__device__ __forceinline__ void load_px_strided(const TliVerifyArgs &a, const float *prow, int c, float4 (&pv)[4], int32_t (&xs)[16]) {
     const int lane = threadIdx.x % kWave;
     const int xb = c * vcore::kChunk;
-    vcore::load_chunk(prow, xb, lane, a.v_t, vec, pv);
-    if (vec && xb + vcore::kChunk <= a.v_t) {
+    vcore::load_chunk(prow, xb, lane, a.v_t, pv);
+    if (xb + vcore::kChunk <= a.v_t) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int4 t = *reinterpret_cast<const int4 *>(a.t2d + xb + u * 256 + lane * 4);
+            const int4 t = vcore::load4(a.t2d + xb + u * 256 + lane * 4);
             xs[4 * u] = t.x;
             xs[4 * u + 1] = t.y;
             xs[4 * u + 2] = t.z;
@@ -359,7 +355,7 @@ __global__ void __launch_bounds__(kThreads) verify_tli_row(TliVerifyParams p) {
         }
         for (int j = 0; j < M; ++j) {  // S_j of each tested row, formed as tt_tli_proposal forms it
             const float *drow = a.draft_probs + (int64_t)(t0 + j) * a.draft_ld;
-            const float Sj = row_mass(drow, a.d2t, a.v_d, p.vec_d != 0, sh_red, &sh_S);
+            const float Sj = row_mass(drow, a.d2t, a.v_d, sh_red, &sh_S);
             if (tid == 0) {
                 const int tok = a.target_ids[t0 + j];
                 const float pt = a.target_probs[(int64_t)(t0 + b + j) * a.target_ld + tok];
@@ -378,7 +374,6 @@ __global__ void __launch_bounds__(kThreads) verify_tli_row(TliVerifyParams p) {
     }
     TT_STAMP(1);
     // residual (or bonus) row: Q62 chunk sums of max(0, p - q') into LDS
-    const bool vec = p.vec_t != 0;
     const float *prow = a.target_probs + (int64_t)(t0 + b + gamma) * a.target_ld;
     const float *drow = gamma < M ? a.draft_probs + (int64_t)(t0 + gamma) * a.draft_ld : nullptr;
     const int nc = p.nc;
@@ -390,10 +385,10 @@ __global__ void __launch_bounds__(kThreads) verify_tli_row(TliVerifyParams p) {
         int32_t xs[16];
         int c = wave, cn = nc;
         if (c < nc) {
-            load_px_strided(a, prow, c, vec, pv, xs);
+            load_px_strided(a, prow, c, pv, xs);
             gather16(a, drow, xs, gv);
             cn = vcore::next_chunk(&sh_ctr, c, kWaves);
-            if (cn < nc) load_px_strided(a, prow, cn, vec, pn, xs);
+            if (cn < nc) load_px_strided(a, prow, cn, pn, xs);
         }
         while (c < nc) {
             uint64_t acc = residual_sum_strided(pv, gv, S_r);
@@ -405,7 +400,7 @@ __global__ void __launch_bounds__(kThreads) verify_tli_row(TliVerifyParams p) {
                 for (int u = 0; u < 4; ++u) pv[u] = pn[u];
                 gather16(a, drow, xs, gv);
                 cn = vcore::next_chunk(&sh_ctr, c, kWaves);
-                if (cn < nc) load_px_strided(a, prow, cn, vec, pn, xs);
+                if (cn < nc) load_px_strided(a, prow, cn, pn, xs);
             }
         }
     }
@@ -425,7 +420,7 @@ __global__ void __launch_bounds__(kThreads) verify_tli_row(TliVerifyParams p) {
         const int x0 = cs * vcore::kChunk + lane * 16;
         float pv[16], gv[16];
         int32_t xs[16];
-        load_px(a, prow, x0, vec, pv, xs);
+        load_px(a, prow, x0, pv, xs);
         gather16(a, drow, xs, gv);
         uint64_t qv[16];
         const uint64_t sum = residual16(pv, gv, S_r, x0, a.v_t, qv);
@@ -453,15 +448,11 @@ __global__ void __launch_bounds__(kThreads) verify_tli_row(TliVerifyParams p) {
     TT_STAMP(3);
 }
 
-bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-
 }  // namespace
 
 int launch_tli_proposal(const TliArgs &a, hipStream_t stream) {
     if (a.n_rows == 0) return TT_OK;
-    const int vec_in = aligned16(a.draft_probs) && aligned16(a.d2t) && a.draft_ld % 4 == 0;
-    const int vec_out = aligned16(a.q_out) && aligned16(a.t2d) && a.q_ld % 4 == 0;
-    hipLaunchKernelGGL(tli_rows, dim3(a.n_rows), dim3(kThreads), 0, stream, a, vec_in, vec_out);
+    hipLaunchKernelGGL(tli_rows, dim3(a.n_rows), dim3(kThreads), 0, stream, a);
     return hipGetLastError() == hipSuccess ? TT_OK : TT_ELAUNCH;
 }
 
@@ -470,8 +461,6 @@ int launch_verify_tli(const TliVerifyArgs &a, hipStream_t stream) {
     TliVerifyParams p;
     p.a = a;
     p.nc = (a.v_t + vcore::kChunk - 1) / vcore::kChunk;
-    p.vec_t = aligned16(a.target_probs) && aligned16(a.t2d) && a.target_ld % 4 == 0;
-    p.vec_d = aligned16(a.draft_probs) && aligned16(a.d2t) && a.draft_ld % 4 == 0;
     hipLaunchKernelGGL(verify_tli_row, dim3(a.n_streams), dim3(kThreads), 8 * (size_t)p.nc, stream, p);
     return hipGetLastError() == hipSuccess ? TT_OK : TT_ELAUNCH;
 }

@@ -57,7 +57,7 @@ struct VParams {
     uint64_t *zsum;
     int32_t *rsel;
     uint64_t *partials;
-    int32_t nc, splits, cpw, work_items, vec4;
+    int32_t nc, splits, cpw, work_items;
 };
 
 // Acceptance scan by one wave: gamma (first rejection, else M) and the rejected
@@ -132,10 +132,10 @@ __device__ __forceinline__ Proposal proposal(const VerifyArgs &a, int t0, int M,
 // row's entry at the one-hot proposal's token (from the acceptance scan), next the LDS chunk
 // counter (or null).
 template <class Store>
-__device__ __forceinline__ void stream_row(const float *row, const Proposal &pr, int vt, bool vec, int c0, int c1,
+__device__ __forceinline__ void stream_row(const float *row, const Proposal &pr, int vt, int c0, int c1,
                                            int stride, float rp, Store store, int *next) {
-    if (pr.qrow != nullptr) stream_chunks_dense(row, pr.qrow, vt, vec, c0, c1, stride, store, next);
-    else stream_chunks(row, vt, vec, c0, c1, stride, pr.rtok, pr.rq, rp, store, next);
+    if (pr.qrow != nullptr) stream_chunks_dense(row, pr.qrow, vt, c0, c1, stride, store, next);
+    else stream_chunks(row, vt, c0, c1, stride, pr.rtok, pr.rq, rp, store, next);
 }
 
 // ------------------------------------------------------------------ row path
@@ -179,17 +179,16 @@ __global__ void __launch_bounds__(THREADS) verify_row(VParams p) {
     const int r = sh_gamma;
     const Rejection rj = sh_rj;
     const int vt = a.v_t;
-    const bool vec = p.vec4 != 0;
     const float *row = a.target_probs + (int64_t)(t0 + b + r) * a.target_ld;
     const Proposal pr{DENSE && r < M ? a.q_rows + (int64_t)(t0 + r) * a.q_ld : nullptr, rj.rtok, rj.rq};
-    stream_row(row, pr, vt, vec, 0, p.nc, kWaves, rj.rp, [&](int c, uint64_t s) { sh_part[c] = s; }, &sh_next);
+    stream_row(row, pr, vt, 0, p.nc, kWaves, rj.rp, [&](int c, uint64_t s) { sh_part[c] = s; }, &sh_next);
     TT_STAMP(3);
     __syncthreads();
     TT_STAMP(4);
     if (wave != 0) return;
     uint64_t Z;
     const int token =
-        wave_sample(row, pr.qrow, vt, p.nc, vec, [&](int c) { return sh_part[c]; }, us, pr.rtok, pr.rq, &Z);
+        wave_sample(row, pr.qrow, vt, p.nc, [&](int c) { return sh_part[c]; }, us, pr.rtok, pr.rq, &Z);
     if (tid == 0) {
         a.n_accepted[b] = r;
         a.out_token[b] = token;
@@ -256,7 +255,7 @@ __global__ void __launch_bounds__(kSplitThreads) verify_stream(VParams p) {
     const float *row = a.target_probs + (int64_t)(t0 + b + r) * a.target_ld;
     const Proposal pr = proposal<DENSE>(a, t0, M, r);
     uint64_t *out = p.partials + (int64_t)b * p.nc;
-    stream_row(row, pr, a.v_t, p.vec4 != 0, c0, c1, kSplitThreads / kWave, sh_rp,
+    stream_row(row, pr, a.v_t, c0, c1, kSplitThreads / kWave, sh_rp,
                [&](int c, uint64_t sum) { out[c] = sum; }, &sh_next);
 }
 
@@ -276,7 +275,7 @@ __global__ void __launch_bounds__(kWave) verify_sample(VParams p) {
     const Proposal pr = proposal<DENSE>(a, t0, M, r);
     uint64_t Z;
     const int token =
-        wave_sample(row, pr.qrow, a.v_t, p.nc, p.vec4 != 0, [&](int c) { return part[c]; }, us, pr.rtok, pr.rq, &Z);
+        wave_sample(row, pr.qrow, a.v_t, p.nc, [&](int c) { return part[c]; }, us, pr.rtok, pr.rq, &Z);
     if (tid == 0) {
         a.n_accepted[b] = r;
         a.out_token[b] = token;
@@ -285,30 +284,61 @@ __global__ void __launch_bounds__(kWave) verify_sample(VParams p) {
 }
 
 // Optional normalised residual row: res[x] = R(x) / fp32(Z * 2^-62), one-hot when Z = 0.
+// Bound by its reads (one or two rows) and its write.  A workgroup takes kResSpan entries, its
+// loads all in flight before the first quotient: with a few streams that is what fills the chip
+// (48 rows of 50,257: about 1,200 workgroups, where spans of 8,192 read 4 bytes a lane at a time
+// by 336 workgroups took 14 us).
+constexpr int kResUnroll = 2;
+constexpr int kResSpan = kSplitThreads * 4 * kResUnroll;
+
 template <bool DENSE>
 __global__ void __launch_bounds__(kSplitThreads) residual_write(VParams p, int rsplit) {
     const VerifyArgs &a = p.a;
     const int b = blockIdx.x / rsplit, sidx = blockIdx.x % rsplit;
-    if (a.n_accepted[b] < 0) return;
     const int r = p.rsel[b];
+    if (r < 0) return;  // sentinel stream
     const uint64_t Z = p.zsum[b];
-    const int tok = a.out_token[b];
     const int t0 = a.target_off[b];
     const int M = a.target_off[b + 1] - t0;
     const float *row = a.target_probs + (int64_t)(t0 + b + r) * a.target_ld;
     const Proposal pr = proposal<DENSE>(a, t0, M, r);
     float *res = a.residual + (int64_t)b * a.target_ld;
     const int vt = a.v_t;
-    const int per = (vt + rsplit - 1) / rsplit;
-    const int x0 = sidx * per;
-    const int x1 = (x0 + per) < vt ? (x0 + per) : vt;
+    const int x0 = sidx * kResSpan + 4 * (int)threadIdx.x;
     if (Z == 0) {
-        for (int x = x0 + (int)threadIdx.x; x < x1; x += kSplitThreads) res[x] = (x == tok) ? 1.0f : 0.0f;
+        const int tok = a.out_token[b];
+        for (int u = 0; u < kResUnroll; ++u)
+            for (int k = 0; k < 4; ++k) {
+                const int x = x0 + u * 4 * kSplitThreads + k;
+                if ((uint32_t)x < (uint32_t)vt) res[x] = (x == tok) ? 1.0f : 0.0f;
+            }
         return;
     }
     const float zf = (float)Z * 0x1p-62f;
-    for (int x = x0 + (int)threadIdx.x; x < x1; x += kSplitThreads)
-        res[x] = clamp01(row[x] - (pr.qrow != nullptr ? pr.qrow[x] : (x == pr.rtok ? pr.rq : 0.0f))) / zf;
+    if (vt - sidx * kResSpan >= kResSpan) {
+        float4 v[kResUnroll], d[kResUnroll];
+#pragma unroll
+        for (int u = 0; u < kResUnroll; ++u) {
+            const int x = x0 + u * 4 * kSplitThreads;
+            v[u] = load4(row + x);
+            if (DENSE && pr.qrow != nullptr) d[u] = load4(pr.qrow + x);
+            else d[u] = make_float4(x == pr.rtok ? pr.rq : 0.0f, x + 1 == pr.rtok ? pr.rq : 0.0f,
+                                    x + 2 == pr.rtok ? pr.rq : 0.0f, x + 3 == pr.rtok ? pr.rq : 0.0f);
+        }
+#pragma unroll
+        for (int u = 0; u < kResUnroll; ++u) {
+            const f4u o{clamp01(v[u].x - d[u].x) / zf, clamp01(v[u].y - d[u].y) / zf, clamp01(v[u].z - d[u].z) / zf,
+                        clamp01(v[u].w - d[u].w) / zf};
+            __builtin_nontemporal_store(o, reinterpret_cast<f4u *>(res + x0 + u * 4 * kSplitThreads));
+        }
+        return;
+    }
+    for (int u = 0; u < kResUnroll; ++u)
+        for (int k = 0; k < 4; ++k) {
+            const int x = x0 + u * 4 * kSplitThreads + k;
+            if ((uint32_t)x < (uint32_t)vt)
+                res[x] = clamp01(row[x] - (DENSE && pr.qrow != nullptr ? pr.qrow[x] : (x == pr.rtok ? pr.rq : 0.0f))) / zf;
+        }
 }
 
 inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
@@ -346,8 +376,6 @@ VParams make_params(const VerifyArgs &a) {
     p.rsel = reinterpret_cast<int32_t *>(ws + L.rsel);
     p.partials = reinterpret_cast<uint64_t *>(ws + L.partials);
     p.nc = L.n_chunks;
-    p.vec4 = ((reinterpret_cast<uintptr_t>(a.target_probs) & 15u) == 0 && (a.target_ld % 4) == 0) ? 1 : 0;
-    if (a.q_rows != nullptr && ((reinterpret_cast<uintptr_t>(a.q_rows) & 15u) != 0 || (a.q_ld % 4) != 0)) p.vec4 = 0;
     p.splits = 1;
     p.cpw = p.nc;
     p.work_items = a.n_streams;
@@ -355,8 +383,7 @@ VParams make_params(const VerifyArgs &a) {
 }
 
 int launch_residual(const VParams &p, hipStream_t stream) {
-    int rsplit = (p.a.v_t + 8191) / 8192;
-    if (rsplit < 1) rsplit = 1;
+    const int rsplit = (p.a.v_t + kResSpan - 1) / kResSpan;
     if (p.a.q_rows != nullptr)
         hipLaunchKernelGGL(residual_write<true>, dim3(p.a.n_streams * rsplit), dim3(kSplitThreads), 0, stream, p,
                            rsplit);

@@ -127,18 +127,34 @@ __device__ inline int wave_first_argmax(const float *row, int vt) {
     return bi == INT_MAX ? 0 : bi;
 }
 
+// Four floats (or ids) at an address aligned to 4 bytes only: rows start anywhere (an odd row
+// stride misaligns all but one of four), and gfx950's 16-byte global loads and stores take any
+// dword address, so every row takes the wide path (373 rows of 181,642 floats: a step in 59.9 us,
+// 99.3 us with guarded 4-byte loads; 70 bf16 rows of 158,491: 20.5 against 46.6 us).
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef int i4u __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ float4 load4(const float *src) {
+    const f4u t = *reinterpret_cast<const f4u *>(src);
+    return make_float4(t.x, t.y, t.z, t.w);
+}
+
+__device__ __forceinline__ int4 load4(const int32_t *src) {
+    const i4u t = *reinterpret_cast<const i4u *>(src);
+    return make_int4(t.x, t.y, t.z, t.w);
+}
+
 // The four 16-byte loads of one lane for chunk starting at xb (guarded at the row end).
-__device__ __forceinline__ void load_chunk(const float *row, int xb, int lane, int vt, bool vec, float4 (&v)[4]) {
-    if (vec && xb + kChunk <= vt) {
+__device__ __forceinline__ void load_chunk(const float *row, int xb, int lane, int vt, float4 (&v)[4]) {
+    if (xb + kChunk <= vt) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const float4 *src = reinterpret_cast<const float4 *>(row + xb + u * 256 + lane * 4);
+            const float *src = row + xb + u * 256 + lane * 4;
 #if TT_VERIFY_NT_LOADS
-            typedef float f4v __attribute__((ext_vector_type(4)));
-            const f4v t = __builtin_nontemporal_load(reinterpret_cast<const f4v *>(src));
+            const f4u t = __builtin_nontemporal_load(reinterpret_cast<const f4u *>(src));
             v[u] = make_float4(t.x, t.y, t.z, t.w);
 #else
-            v[u] = *src;
+            v[u] = load4(src);
 #endif
         }
     } else {
@@ -185,18 +201,18 @@ __device__ __forceinline__ int next_chunk(int *next, int c, int stride) {
 // Q62 sums of chunks [c0, c1): wave w starts at c0 + w and keeps one chunk in flight ahead of
 // the one it sums; lane 63 hands each sum to store(c, sum).
 template <class Store>
-__device__ __forceinline__ void stream_chunks(const float *row, int vt, bool vec, int c0, int c1, int stride,
+__device__ __forceinline__ void stream_chunks(const float *row, int vt, int c0, int c1, int stride,
                                               int rtok, float rq, float rp, Store store, int *next = nullptr) {
     const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     int c = c0 + wave;
     if (c >= c1) return;
     float4 v[4], nx[4];
-    load_chunk(row, c * kChunk, lane, vt, vec, v);
+    load_chunk(row, c * kChunk, lane, vt, v);
     int cn = next_chunk(next, c, stride);
     for (;;) {
         int cnn = c1;
         if (cn < c1) {
-            load_chunk(row, cn * kChunk, lane, vt, vec, nx);
+            load_chunk(row, cn * kChunk, lane, vt, nx);
             cnn = next_chunk(next, cn, stride);
         }
         sum_chunk(v, c, rtok, rq, rp, store);
@@ -209,11 +225,11 @@ __device__ __forceinline__ void stream_chunks(const float *row, int vt, bool vec
 }
 
 // 16 consecutive floats row[x0 .. x0 + 16) (zero past vt).
-__device__ __forceinline__ void read16(const float *row, int x0, int vt, bool vec, float (&pv)[16]) {
-    if (vec && x0 + 16 <= vt) {
+__device__ __forceinline__ void read16(const float *row, int x0, int vt, float (&pv)[16]) {
+    if (x0 + 16 <= vt) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const float4 t = *reinterpret_cast<const float4 *>(row + x0 + 4 * q);
+            const float4 t = load4(row + x0 + 4 * q);
             pv[4 * q] = t.x;
             pv[4 * q + 1] = t.y;
             pv[4 * q + 2] = t.z;
@@ -241,20 +257,20 @@ __device__ __forceinline__ void sum_chunk_dense(const float4 (&vp)[4], const flo
 // As stream_chunks for the dense residual: chunks [c0, c1) of both rows, one chunk of each
 // ahead in flight.
 template <class Store>
-__device__ __forceinline__ void stream_chunks_dense(const float *prow, const float *qrow, int vt, bool vec, int c0,
+__device__ __forceinline__ void stream_chunks_dense(const float *prow, const float *qrow, int vt, int c0,
                                                     int c1, int stride, Store store, int *next = nullptr) {
     const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     int c = c0 + wave;
     if (c >= c1) return;
     float4 vp[4], vq[4], np_[4], nq[4];
-    load_chunk(prow, c * kChunk, lane, vt, vec, vp);
-    load_chunk(qrow, c * kChunk, lane, vt, vec, vq);
+    load_chunk(prow, c * kChunk, lane, vt, vp);
+    load_chunk(qrow, c * kChunk, lane, vt, vq);
     int cn = next_chunk(next, c, stride);
     while (c < c1) {
         int cnn = c1;
         if (cn < c1) {
-            load_chunk(prow, cn * kChunk, lane, vt, vec, np_);
-            load_chunk(qrow, cn * kChunk, lane, vt, vec, nq);
+            load_chunk(prow, cn * kChunk, lane, vt, np_);
+            load_chunk(qrow, cn * kChunk, lane, vt, nq);
             cnn = next_chunk(next, cn, stride);
         }
         sum_chunk_dense(vp, vq, c, store);
@@ -337,7 +353,7 @@ __device__ __forceinline__ int find_crossing(int nc, Part part, float u, uint64_
 // crossing chunk's row values come as 16 consecutive floats per lane from chunk16(cs, x0, pv)
 // (wave_sample: read again from the row) and are scanned.
 template <class Part, class Chunk16>
-__device__ inline int wave_sample_with(const float *row, const float *qrow, int vt, int nc, bool vec, Part part,
+__device__ inline int wave_sample_with(const float *row, const float *qrow, int vt, int nc, Part part,
                                        Chunk16 chunk16, float u, int rtok, float rq, uint64_t *Zout) {
     const int lane = threadIdx.x % kWave;
     uint64_t Z, T, base;
@@ -351,7 +367,7 @@ __device__ inline int wave_sample_with(const float *row, const float *qrow, int 
     float pv[16], dv[16];
     chunk16(cs, x0, pv);
     if (qrow != nullptr) {
-        read16(qrow, x0, vt, vec, dv);
+        read16(qrow, x0, vt, dv);
     } else {
 #pragma unroll
         for (int k = 0; k < 16; ++k) dv[k] = x0 + k == rtok ? rq : 0.0f;
@@ -380,10 +396,10 @@ __device__ inline int wave_sample_with(const float *row, const float *qrow, int 
 }
 
 template <class Part>
-__device__ inline int wave_sample(const float *row, const float *qrow, int vt, int nc, bool vec, Part part, float u,
+__device__ inline int wave_sample(const float *row, const float *qrow, int vt, int nc, Part part, float u,
                                   int rtok, float rq, uint64_t *Zout) {
     return wave_sample_with(
-        row, qrow, vt, nc, vec, part, [&](int, int x0, float(&pv)[16]) { read16(row, x0, vt, vec, pv); }, u, rtok,
+        row, qrow, vt, nc, part, [&](int, int x0, float(&pv)[16]) { read16(row, x0, vt, pv); }, u, rtok,
         rq, Zout);
 }
 
