@@ -10,12 +10,15 @@
 // rounded once to the nearest fp32 (ties to even).  q'(y) is the IEEE fp32 quotient
 // q(x) / S; a row with S = 0 is written as zeros.
 //
-// One 1024-thread workgroup per row, two passes over the row:
-//   1. coalesced reads of q and d2t (16-byte loads when the rows allow), Q62 sums in
-//      registers, a wave and then a workgroup reduction of the 128-bit sums;
-//   2. coalesced reads of t2d and writes of q' (16-byte stores), with q(x)
-//      gathered from the row read in pass 1 (it is still in L2 or the Infinity Cache).
-// The row is read from HBM once; the maps are shared by every row and stay in cache.
+// Two kernels: tli_mass forms S (coalesced 16-byte reads of q and d2t, Q62 sums in registers, a
+// wave and then a workgroup reduction of the 128-bit sums), tli_fill writes q' by slices of
+// 2,048 target ids with q(x) gathered through t2d.  The gathers bound the call: each takes
+// a cache line of the row for 4 bytes, so the rows being gathered from have to stay in
+// the XCD's L2.  A row's slices run together on one XCD (3 to 4 rows of 512 KB in flight there);
+// with one workgroup per row 32 rows (16 MB) were, and nearly every gather went to the Infinity
+// Cache.  1,024 rows of 128,256 -> 151,936 ids with 60% shared: 1,215 us with one workgroup per
+// row, 530 so (tli_fill about 200 G gathers/s).  Rows of small vocabularies keep the one
+// kernel (tli_rows).  The maps are shared by every row and stay in cache.
 #include "verify_core.h"
 
 TT_STAMPS_TABLE(tli)
@@ -29,6 +32,18 @@ using vcore::q62;
 constexpr int kThreads = 1024;
 constexpr int kWave = 64;
 constexpr int kUnroll = 4;  // 16-byte loads of each array a thread keeps in flight
+constexpr int kSlice = 2048;  // target ids of a workgroup of tli_fill
+constexpr int kFillThreads = 256;
+constexpr int kXcds = 8;
+constexpr int kCus = 256;
+// Both vocabularies up to here: one workgroup per row does both passes (tli_rows).  Its rows in
+// flight (one per CU, 32 per XCD) then fit the XCD's 4 MB L2, and one launch beats two: 300 rows of
+// 8,000 -> 12,000 ids 13.3 us against 17.7, of 16,000 -> 20,000 21.7 against 23.9; past it, 300 rows
+// of 32,000 -> 50,257 with 70% shared take 49.6 us in two kernels against 65.8 in one.
+constexpr int kSmallVocab = 16384;
+constexpr int64_t kCacheBytes = int64_t(256) << 20;  // the Infinity Cache
+constexpr int64_t kMaxItems = int64_t(1) << 21;      // workgroups of one grid
+constexpr int kMaxSplits = 16;  // workgroups a row's mass is split over at most
 
 struct U128 {
     uint64_t lo, hi;
@@ -65,55 +80,56 @@ __device__ inline float q62_to_f32(U128 n) {
     return ldexpf((float)m, sh - 62);
 }
 
-// S, the mass row q puts on the intersection: every intersected q(x) (clamped to [0, 1])
-// truncated to Q62 and the integers summed exactly, rounded once to fp32.  Called by every
-// thread of the workgroup (barriers inside); sh_part holds a partial sum per wave.
-__device__ float row_mass(const float *q, const int32_t *d2t, int v_d, U128 *sh_part, float *sh_S) {
+// The Q62 sum of the intersected q(x) (clamped to [0, 1], truncated) over x0 <= x < x1, exact, by the
+// whole workgroup (barriers inside; sh_part holds a partial sum per wave); the total is valid in
+// thread 0.
+__device__ U128 mass_sum(const float *q, const int32_t *d2t, int x0, int x1, U128 *sh_part) {
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     U128 acc{0, 0};
     auto add = [&](float x, int32_t m) {  // branch-free: the loads stay batched
         const uint64_t keep = 0ull - (uint64_t)(m >= 0);
         acc = add128(acc, U128{q62(clamp01(x)) & keep, 0});
     };
-    int x0 = 0;
-    {
-        const int n4 = v_d / 4;
-        int k = tid;
-        for (; k + (kUnroll - 1) * kThreads < n4; k += kUnroll * kThreads) {  // kUnroll loads of each in flight
-            float4 v[kUnroll];
-            int4 m[kUnroll];
+    const int n4 = (x1 - x0) / 4;
+    int k = tid;
+    for (; k + (kUnroll - 1) * kThreads < n4; k += kUnroll * kThreads) {  // kUnroll loads of each in flight
+        float4 v[kUnroll];
+        int4 m[kUnroll];
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                v[u] = vcore::load4(q + 4 * (k + u * kThreads));
-                m[u] = vcore::load4(d2t + 4 * (k + u * kThreads));
-            }
+        for (int u = 0; u < kUnroll; ++u) {
+            v[u] = vcore::load4(q + x0 + 4 * (k + u * kThreads));
+            m[u] = vcore::load4(d2t + x0 + 4 * (k + u * kThreads));
+        }
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                add(v[u].x, m[u].x);
-                add(v[u].y, m[u].y);
-                add(v[u].z, m[u].z);
-                add(v[u].w, m[u].w);
-            }
+        for (int u = 0; u < kUnroll; ++u) {
+            add(v[u].x, m[u].x);
+            add(v[u].y, m[u].y);
+            add(v[u].z, m[u].z);
+            add(v[u].w, m[u].w);
         }
-        for (; k < n4; k += kThreads) {
-            const float4 v = vcore::load4(q + 4 * k);
-            const int4 m = vcore::load4(d2t + 4 * k);
-            add(v.x, m.x);
-            add(v.y, m.y);
-            add(v.z, m.z);
-            add(v.w, m.w);
-        }
-        x0 = 4 * n4;
     }
-    for (int x = x0 + tid; x < v_d; x += kThreads) add(q[x], d2t[x]);
+    for (; k < n4; k += kThreads) {
+        const float4 v = vcore::load4(q + x0 + 4 * k);
+        const int4 m = vcore::load4(d2t + x0 + 4 * k);
+        add(v.x, m.x);
+        add(v.y, m.y);
+        add(v.z, m.z);
+        add(v.w, m.w);
+    }
+    for (int x = x0 + 4 * n4 + tid; x < x1; x += kThreads) add(q[x], d2t[x]);
     for (int m = kWave / 2; m > 0; m >>= 1) acc = add128(acc, shfl_xor128(acc, m));
     if (lane == 0) sh_part[wave] = acc;
     __syncthreads();
-    if (tid == 0) {
-        U128 tot{0, 0};
+    U128 tot{0, 0};
+    if (tid == 0)
         for (int w = 0; w < kThreads / kWave; ++w) tot = add128(tot, sh_part[w]);
-        *sh_S = q62_to_f32(tot);
-    }
+    return tot;
+}
+
+// S, the mass row q puts on the intersection: the exact sum rounded once to fp32, in every thread.
+__device__ float row_mass(const float *q, const int32_t *d2t, int v_d, U128 *sh_part, float *sh_S) {
+    const U128 tot = mass_sum(q, d2t, 0, v_d, sh_part);
+    if (threadIdx.x == 0) *sh_S = q62_to_f32(tot);
     __syncthreads();
     return *sh_S;
 }
@@ -122,6 +138,7 @@ __device__ float row_mass(const float *q, const int32_t *d2t, int v_d, U128 *sh_
 // outside [0, v_d): the entry is 0 either way); 0 when S is not positive.
 __device__ __forceinline__ float qprime(float g, float S) { return S > 0.0f ? clamp01(g) / S : 0.0f; }
 
+// Small vocabularies: one 1024-thread workgroup per row, the mass and then the row.
 __global__ void __launch_bounds__(kThreads) tli_rows(TliArgs a) {
     const int r = blockIdx.x;
     const int tid = threadIdx.x;
@@ -165,6 +182,84 @@ __global__ void __launch_bounds__(kThreads) tli_rows(TliArgs a) {
         y0 = 4 * n4;
     }
     for (int y = y0 + tid; y < a.v_t; y += kThreads) {
+        const int32_t x = a.t2d[y];
+        out[y] = value(x, gather(x));
+    }
+}
+
+// tli_mass: the masses, for rows [row0, ...).  A row is split over `splits` workgroups (1 once the rows fill the chip);
+// they hand their sums to tli_fill in the output row itself, once per slice of tli_fill: S in the
+// slice's first entry (one split), or the splits' 128-bit sums in its first 4 * splits entries.
+__global__ void __launch_bounds__(kThreads) tli_mass(TliArgs a, int row0, int splits, int slices) {
+    const int r = row0 + blockIdx.x / splits, sp = blockIdx.x % splits;
+    const int tid = threadIdx.x;
+    const float *q = a.draft_probs + (int64_t)r * a.draft_ld;
+    uint32_t *out = reinterpret_cast<uint32_t *>(a.q_out + (int64_t)r * a.q_ld);
+    __shared__ U128 sh_part[kThreads / kWave];
+    __shared__ U128 sh_tot;
+    const int per = ((a.v_d + splits - 1) / splits + 3) & ~3;
+    const int x0 = sp * per < a.v_d ? sp * per : a.v_d;
+    const int x1 = a.v_d - x0 < per ? a.v_d : x0 + per;
+    const U128 tot = mass_sum(q, a.d2t, x0, x1, sh_part);
+    if (tid == 0) sh_tot = tot;
+    __syncthreads();
+    if (splits == 1) {
+        const uint32_t S = __float_as_uint(q62_to_f32(sh_tot));
+        for (int s = tid; s < slices; s += kThreads) out[(int64_t)s * kSlice] = S;
+    } else {
+        const uint64_t w = (tid & 2) ? sh_tot.hi : sh_tot.lo;
+        const uint32_t word = (tid & 1) ? (uint32_t)(w >> 32) : (uint32_t)w;
+        for (int s = tid / 4; s < slices; s += kThreads / 4) out[(int64_t)s * kSlice + 4 * sp + (tid & 3)] = word;
+    }
+}
+
+// tli_fill: q' of one slice of kSlice target ids of a row.
+__global__ void __launch_bounds__(kFillThreads) tli_fill(TliArgs a, int row0, int splits, int slices, int items) {
+    const int G = gridDim.x, g = blockIdx.x;
+    const int work = (g % kXcds) * (G / kXcds) + g / kXcds;
+    if (work >= items) return;
+    const int r = row0 + work / slices, sl = work % slices;
+    const int tid = threadIdx.x;
+    const float *q = a.draft_probs + (int64_t)r * a.draft_ld;
+    float *out = a.q_out + (int64_t)r * a.q_ld;
+    const int y0 = sl * kSlice;
+    const int y1 = sl == slices - 1 ? a.v_t : y0 + kSlice;  // the last slice takes the remainder
+
+    constexpr int kVec = kSlice / (4 * kFillThreads);
+    // every lane loads (q[0] outside the intersection) so the gathers of a batch stay in flight together
+    auto gather = [&](int32_t x) -> float { return q[(x >= 0 && x < a.v_d) ? x : 0]; };
+    int4 m[kVec];
+    float4 gv[kVec];
+    const bool full = y1 - y0 >= kSlice;
+    if (full) {
+#pragma unroll
+        for (int u = 0; u < kVec; ++u) m[u] = vcore::load4(a.t2d + y0 + 4 * (tid + u * kFillThreads));
+#pragma unroll
+        for (int u = 0; u < kVec; ++u) gv[u] = make_float4(gather(m[u].x), gather(m[u].y), gather(m[u].z), gather(m[u].w));
+    }
+    float S;
+    if (splits == 1) {
+        S = out[y0];
+    } else {
+        U128 tot{0, 0};
+        const uint32_t *w = reinterpret_cast<const uint32_t *>(out + y0);
+        for (int k = 0; k < splits; ++k)
+            tot = add128(tot, U128{((uint64_t)w[4 * k + 1] << 32) | w[4 * k], ((uint64_t)w[4 * k + 3] << 32) | w[4 * k + 2]});
+        S = q62_to_f32(tot);
+    }
+    __syncthreads();  // every thread has read the slice's masses: its entries may be written
+    auto value = [&](int32_t x, float g) -> float { return x >= 0 && x < a.v_d ? qprime(g, S) : 0.0f; };
+    int y = y0 + tid;
+    if (full) {
+#pragma unroll
+        for (int u = 0; u < kVec; ++u) {
+            const vcore::f4u o{value(m[u].x, gv[u].x), value(m[u].y, gv[u].y), value(m[u].z, gv[u].z),
+                               value(m[u].w, gv[u].w)};
+            __builtin_nontemporal_store(o, reinterpret_cast<vcore::f4u *>(out + y0 + 4 * (tid + u * kFillThreads)));
+        }
+        y += kSlice;
+    }
+    for (; y < y1; y += kFillThreads) {
         const int32_t x = a.t2d[y];
         out[y] = value(x, gather(x));
     }
@@ -452,7 +547,28 @@ __global__ void __launch_bounds__(kThreads) verify_tli_row(TliVerifyParams p) {
 
 int launch_tli_proposal(const TliArgs &a, hipStream_t stream) {
     if (a.n_rows == 0) return TT_OK;
-    hipLaunchKernelGGL(tli_rows, dim3(a.n_rows), dim3(kThreads), 0, stream, a);
+    if (a.v_d <= kSmallVocab && a.v_t <= kSmallVocab) {
+        hipLaunchKernelGGL(tli_rows, dim3(a.n_rows), dim3(kThreads), 0, stream, a);
+        return hipGetLastError() == hipSuccess ? TT_OK : TT_ELAUNCH;
+    }
+    const int slices = a.v_t >= kSlice ? a.v_t / kSlice : 1;
+    // rows whose draft bytes fit the Infinity Cache go through both kernels together, in multiples
+    // of the compute units (a mass workgroup takes one), few enough for one grid
+    int64_t chunk = kCacheBytes / (4 * (int64_t)a.v_d);
+    chunk = chunk < kCus ? kCus : chunk / kCus * kCus;
+    if (chunk > kMaxItems / slices) chunk = kMaxItems / slices;
+    if (chunk > a.n_rows || (4 * (int64_t)a.v_d * a.n_rows <= kCacheBytes && a.n_rows <= kMaxItems / slices)) chunk = a.n_rows;
+    int splits = (int)((kCus + chunk / 2) / chunk);
+    if (splits > kMaxSplits) splits = kMaxSplits;
+    while (splits > 1 && (splits * 4 > a.v_t || a.v_d / splits < 4096)) --splits;
+    if (splits < 1) splits = 1;
+    for (int64_t r0 = 0; r0 < a.n_rows; r0 += chunk) {
+        const int rows = (int)(a.n_rows - r0 < chunk ? a.n_rows - r0 : chunk);
+        hipLaunchKernelGGL(tli_mass, dim3(rows * splits), dim3(kThreads), 0, stream, a, (int)r0, splits, slices);
+        const int items = rows * slices;
+        hipLaunchKernelGGL(tli_fill, dim3((items + kXcds - 1) / kXcds * kXcds), dim3(kFillThreads), 0, stream, a, (int)r0,
+                           splits, slices, items);
+    }
     return hipGetLastError() == hipSuccess ? TT_OK : TT_ELAUNCH;
 }
 

@@ -134,6 +134,36 @@ def test_proposal_at_the_benchmark_vocabulary_sizes():
     assert np.allclose(got.sum(axis=1, dtype=np.float64), 1.0, atol=1e-5)
 
 
+@pytest.mark.parametrize("v_d,v_t,n", [(16385, 5, 3), (16385, 63, 3), (16385, 64, 3), (40000, 2047, 9), (40000, 2049, 70),
+                                       (33000, 4095, 130), (65537, 6145, 1), (100, 16385, 2), (16384, 16384, 3)])
+def test_proposal_rows_in_two_kernels(v_d, v_t, n):
+    """Around the rule's line, slices with and without a remainder, a row's mass in 1 to 16 parts."""
+    rng = np.random.default_rng(v_d + v_t + n)
+    d2t, t2d = random_maps(rng, v_d, v_t, 0.7)
+    q = (rng.random((n, v_d)) ** 4).astype(np.float32)
+    q /= q.sum(axis=1, keepdims=True)
+    q[0, -1], q[n - 1, 1] = 1.75, np.nan
+    want = oracle.tli_proposal(d2t, t2d, q)
+    got = run_tli(d2t, t2d, q, None, v_t + 3)
+    assert np.array_equal(got[:, :v_t].view(np.uint32), want.view(np.uint32))
+    assert np.all(got[:, v_t:] == 7.0)
+
+
+def test_proposal_rows_past_the_cache():
+    """More draft bytes than the Infinity Cache: the rows go through the kernels in parts, and a row does
+    not depend on its part."""
+    import torch
+
+    import paper_2510_15545_amd as tt
+
+    v_d, v_t, n = 262144, 20000, 261
+    d2t, t2d = (to_dev(x) for x in random_maps(np.random.default_rng(7), v_d, v_t, 0.8))
+    q = torch.rand((n, v_d), generator=torch.Generator(device="cuda").manual_seed(7), device="cuda") / v_d
+    whole = tt.tli_proposal(d2t, t2d, q)
+    for a, b in ((0, 2), (250, 259), (256, 261)):
+        assert torch.equal(whole[a:b], tt.tli_proposal(d2t, t2d, q[a:b]))
+
+
 def test_standard_sd_on_the_tli_proposal():
     """Alg. 3 then Alg. 4 on the GPU: q' from tt_tli_proposal, drafts drawn from q', then
     tt_verify_dense; accept counts and tokens equal the oracle's on the oracle's q'."""
