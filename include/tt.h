@@ -273,7 +273,19 @@ int tt_verify_dense(int32_t n_streams, int32_t v,
  * sums), one after another.
  * One kernel on `stream`, a workgroup per stream; no workspace.
  * TT_EINVAL on a bad size or a missing pointer, TT_EUNSUPPORTED for v_t > 2^23.
+ *
+ * tt_verify_logits_ws is the same call with a workspace of tt_verify_logits_workspace_size bytes
+ * (with_lse: whether lse will be given; 0 bytes where the one kernel is the better one; no
+ * initialisation; calls that overlap in time must not share it): the rows of a stream are then
+ * spread over the GPU, several kernels on `stream`, with the same results.  A null workspace is
+ * tt_verify_logits; TT_EWORKSPACE when it is too small.
  */
+int tt_verify_logits_workspace_size(int32_t n_streams, int32_t v_t, int32_t max_m, int32_t with_lse, size_t *bytes);
+int tt_verify_logits_ws(int32_t n_streams, int32_t v_t, const int32_t *target_ids, const int32_t *target_off,
+                        const float *q, const uint16_t *target_logits, int64_t target_ld,
+                        const float *inv_temperature, const float *lse, const float *u_accept,
+                        const float *u_sample, int32_t max_m, int32_t *n_accepted, int32_t *out_token,
+                        void *workspace, size_t workspace_bytes, void *stream);
 int tt_verify_logits(int32_t n_streams, int32_t v_t, const int32_t *target_ids, const int32_t *target_off,
                      const float *q, const uint16_t *target_logits, int64_t target_ld,
                      const float *inv_temperature, const float *lse, const float *u_accept,

@@ -78,6 +78,10 @@ def lib():
         L.tt_verify_dense.restype = ctypes.c_int
         L.tt_verify_logits.argtypes = [i32, i32, P, P, P, P, i64, P, P, P, P, i32, P, P, P]
         L.tt_verify_logits.restype = ctypes.c_int
+        L.tt_verify_logits_workspace_size.argtypes = [i32, i32, i32, i32, ctypes.POINTER(sz)]
+        L.tt_verify_logits_workspace_size.restype = ctypes.c_int
+        L.tt_verify_logits_ws.argtypes = [i32, i32, P, P, P, P, i64, P, P, P, P, i32, P, P, P, sz, P]
+        L.tt_verify_logits_ws.restype = ctypes.c_int
         L.tt_delta_histogram.argtypes = [i32, P, P, P, P, i32, P, P]
         L.tt_delta_histogram.restype = ctypes.c_int
         L.tt_delta_quantile.argtypes = [P, i32, i32, i32, P, P]
@@ -129,6 +133,16 @@ def _ptr(t, dtype, name, allow_none=False):
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
     return ctypes.c_void_p(t.data_ptr())
+
+
+def _scratch(nbytes: int, device, stream):
+    """Device memory for one call on `stream`, from that stream's pool: once the call has returned, the
+    allocator hands it only to work that the same stream runs later."""
+    torch = _torch()
+    if stream is None:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
 
 
 def _check(status: int, where: str):
@@ -335,11 +349,15 @@ def verify_logits(v_t: int, target_ids, target_off, q, target_logits, inv_temper
     ids = target_ids if target_ids.numel() else torch.zeros(1, dtype=i32, device=dev)
     qq = q if q.numel() else torch.zeros(1, dtype=f32, device=dev)
     ua = u_accept if u_accept.numel() else torch.zeros(1, dtype=f32, device=dev)
-    st = lib().tt_verify_logits(n, int(v_t), _ptr(ids, i32, "target_ids"), _ptr(target_off, i32, "target_off"),
+    nb = ctypes.c_size_t(0)
+    st = lib().tt_verify_logits_workspace_size(n, int(v_t), int(max_m), 0 if lse is None else 1, ctypes.byref(nb))
+    ws = _scratch(nb.value, dev, stream) if st == TT_OK and nb.value else None
+    st = lib().tt_verify_logits_ws(n, int(v_t), _ptr(ids, i32, "target_ids"), _ptr(target_off, i32, "target_off"),
                                 _ptr(qq, f32, "q"), ctypes.c_void_p(target_logits.data_ptr()),
                                 int(target_logits.stride(0)), _ptr(inv_temperature, f32, "inv_temperature"),
                                 _ptr(lse, f32, "lse", allow_none=True), _ptr(ua, f32, "u_accept"), _ptr(u_sample, f32, "u_sample"), int(max_m),
-                                _ptr(nacc, i32, "n_accepted"), _ptr(tok, i32, "out_token"), _stream_handle(stream))
+                                _ptr(nacc, i32, "n_accepted"), _ptr(tok, i32, "out_token"),
+                                None if ws is None else ctypes.c_void_p(ws.data_ptr()), nb.value, _stream_handle(stream))
     _check(st, "tt_verify_logits")
     return out
 

@@ -159,11 +159,6 @@ __device__ __forceinline__ uint32_t elem(const uint32_t (&w)[8], int k) {
     return (k & 1) ? (w[k >> 1] >> 16) : (w[k >> 1] & 0xFFFFu);
 }
 
-struct LogitsParams {
-    LogitsArgs a;
-    int32_t nc;
-};
-
 // Per-row table of the Q31 weights.  For a fixed scale and offset the weight of a logit is a
 // function of its 16 bits, so the row pass looks it up instead of evaluating the exponential:
 // the table holds e31_at(expo(bits)) for every pattern whose magnitude lies in [2^-20, 2^8)
@@ -208,12 +203,14 @@ __device__ __forceinline__ uint64_t tab_at(const uint64_t *tab, uint32_t byte_of
 }
 
 // The 16 weights of a lane's logits x0 .. x0+15 (0 past v) into e; a sentinel for a logit
-// outside the table's domain is replaced by the formula's weight.
+// outside the table's domain is replaced by the formula's weight.  Without a table (tab null)
+// all by the formula.
 __device__ __forceinline__ void lane_weights(const uint64_t *tab, const uint32_t (&w)[8], int x0, int v, float sc,
                                              float b31, uint64_t (&e)[16]) {
-    uint64_t any = 0;
+    uint64_t any = tab == nullptr ? kSentinel : 0;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
+        if (tab == nullptr) break;
         const uint32_t o = tab_offsets(w[k]);
         e[2 * k] = x0 + 2 * k < v ? tab_at(tab, o & 0xFFFFu) : 0u;
         e[2 * k + 1] = x0 + 2 * k + 1 < v ? tab_at(tab, o >> 16) : 0u;
@@ -387,18 +384,367 @@ __device__ inline int sample_row(const uint16_t *row, int v, int nc, float sc, f
     return __builtin_amdgcn_readlane(x0 + k_at, tl);
 }
 
-__global__ void __launch_bounds__(kThreads) verify_logits_row(LogitsParams p) {
+// The acceptance scan with normalisers, by one wave: the first rejected position (M after full
+// acceptance) and its L, t, q, P and logit (the bonus row's L), one gathered logit per position.
+struct LseScan {
+    int r, t, x;
+    float L, q, P;
+};
+
+__device__ __forceinline__ LseScan lse_scan(const LogitsArgs &a, int b, int t0, int M, float cb, int lane) {
+    const int v = a.v_t;
+    const float L_bonus = a.lse[t0 + b + M];
+    int gamma = M, t_r = -1, x_r = 0;
+    float L_r = L_bonus, q_r = 0.0f, P_r = 0.0f;
+    for (int base = 0; base < M && gamma == M; base += kWave) {
+        const int j = base + lane;
+        bool rej = false;
+        int tj = 0, xj = 0;
+        float Lj = 0.0f, qj = 0.0f, P = 0.0f;
+        if (j < M) {
+            const int64_t r = t0 + b + j;
+            tj = a.target_ids[t0 + j];
+            Lj = a.lse[r];
+            qj = a.q[t0 + j];
+            if (tj >= 0 && tj < v) {
+                xj = a.logits[r * a.ld + tj];
+                P = fminf(fmaxf(weight_at(expo(xj, cb, 31.0f - Lj * kLog2e)), 0.0f), 1.0f);
+                rej = !(qj <= 0.0f || a.u_accept[t0 + j] < P / qj);
+            }
+        }
+        const unsigned long long rm = __ballot(rej);
+        if (rm != 0ull) {
+            const int src = __ffsll(rm) - 1;
+            gamma = base + src;
+            t_r = __builtin_amdgcn_readlane(tj, src);
+            x_r = __builtin_amdgcn_readlane(xj, src);
+            L_r = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(Lj), src));
+            q_r = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(qj), src));
+            P_r = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(P), src));
+        }
+    }
+    return LseScan{gamma, t_r, x_r, L_r, q_r, P_r};
+}
+
+// the residual entry at the rejected proposal: it loses q of its mass, clamped
+__device__ __forceinline__ uint64_t lse_residual(const LseScan &rec) {
+    return q31(fminf(fmaxf(rec.P - rec.q, 0.0f), 1.0f));
+}
+
+// ------------------------------------------------------------------ screening (no normalisers)
+// Without normalisers a row's S needs the row's mu first (two passes) and row j + 1 matters only
+// once row j accepted, so one workgroup per stream spends (gamma + 1) row walks of about 20 us
+// in series while the streams that stopped leave their compute units idle: 256 streams of
+// 151,936 logits, mean gamma about 1.1, 180-230 us.  Instead the rows are screened first, many
+// at once: one pass over a row gives its exact largest logit and an fp32 sum of 2^(y - max);
+// wherever the acceptance test holds with a relative margin kMargin the position is
+// accepted for certain, and the exact walk starts at the first position that is not (about one
+// row per stream).  Rows go in rounds: round r screens a window of positions of the streams
+// that every earlier window accepted whole, each window three times as long as the one before, so a
+// few launches cover any number of positions and little is read that no test needs.  The same
+// batch takes 88 us (rounds of 18, 23 and 12 us, the walk 22); 64 streams 48 against 195, 32
+// streams of 32,000 25 against 59, 512 of 32,000 96 against 113.
+//
+// The margin: P = E / S and its estimate differ by the estimate's exponents (a fused multiply-add
+// and a subtraction, each within 2^-19 for weights that count: 2.7e-6 relative), the hardware
+// exponential (2^-22), the polynomial of the exact weights (3.3e-6), the roundings of mu and
+// of 31 - mu where the exact exponent is held at 31 (4.3e-5 for |mu| < 512), fp32 sums of depth
+// at most 16 + a lane's chunks (below 300 * 2^-24 = 1.8e-5 at 2^23 logits), and the truncation
+// of the exact weights, which only lowers S (a larger P): below 8e-5 in all.
+constexpr int kScreenThreads = 256;
+constexpr int kScreenWaves = kScreenThreads / kWave;
+constexpr float kMargin = 2e-4f;
+constexpr float kLowest = -3e38f;  // below every scaled logit that counts
+constexpr int kScreenRows = 64;    // positions screened at most; the exact walk goes on from there
+constexpr int kScreenStreams = 512;  // streams of a screened batch at most
+constexpr int kMaxRounds = 8;
+
+struct Window {
+    int a, b;  // positions [a, b)
+};
+
+struct ScreenParams {
+    LogitsArgs a;
+    int32_t nc, rows, splits, cps;  // rows: positions with partials; cps: chunks of a split
+    int32_t sum_splits, sum_cps;    // the exact sums' split (logits_sums)
+    int32_t n_rounds;
+    Window win[kMaxRounds];
+    int32_t *from;     // [n] position the exact walk starts at (after logits_advance; the last window's
+                       // start while undecided)
+    int32_t *alive;    // [kMaxRounds][1 + n] count and streams of each round from the second on
+    float2 *part;      // [n][rows][splits] largest y and sum of 2^(y - largest)
+    uint64_t *sums;    // [n][nc] chunk sums of the selected row
+    LseScan *rec;      // [n] the scan's result (normalisers)
+};
+
+struct Screened {
+    int j;      // position the exact walk starts at
+    int known;  // its mu is known
+    float mu;
+};
+
+// The largest y and the sum of 2^(y - largest) of row j of stream b, from its splits.
+__device__ __forceinline__ float2 screen_combine(const ScreenParams &p, int b, int j) {
+    const float2 *q = p.part + ((int64_t)b * p.rows + j) * p.splits;
+    float m = kLowest, s = 0.0f;
+    for (int k0 = 0; k0 < p.splits; k0 += 8) {  // eight loads in flight
+        float2 v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = q[k0 + k < p.splits ? k0 + k : k0];
+        float mn = m;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) mn = fmaxf(mn, v[k].x);
+        s *= __builtin_amdgcn_exp2f(m - mn);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s += k0 + k < p.splits ? v[k].y * __builtin_amdgcn_exp2f(v[k].x - mn) : 0.0f;
+        m = mn;
+    }
+    return make_float2(m, s);
+}
+
+// Whether position j of stream b is accepted for certain.
+__device__ __forceinline__ bool screen_accepts(const ScreenParams &p, int b, int j) {
+    const LogitsArgs &a = p.a;
+    const int t0 = a.target_off[b];
+    const int M = a.target_off[b + 1] - t0;
+    if (M > a.max_m || j >= M) return false;
+    const int t = a.target_ids[t0 + j];
+    const float q = a.q[t0 + j], u = a.u_accept[t0 + j];
+    if (t < 0 || t >= a.v_t) return false;
+    const uint32_t x = a.logits[(int64_t)(t0 + b + j) * a.ld + t];
+    const float2 ms = screen_combine(p, b, j);
+    if (q <= 0.0f) return true;
+    const float e = __builtin_amdgcn_exp2f(fmaf(bf16_value(x), a.inv_temp[b] * kLog2e, -ms.x));
+    // (the exact weight is 0 below 2^-31; NaN, overlarge q and overlarge logits are left to the
+    // exact test)
+    return e >= 0x1.01p-31f && fabsf(ms.x) < 512.0f && q < 1e30f && u * q < e / ms.y * (1.0f - kMargin);
+}
+
+// Where the exact walk of stream b starts, by one wave: the last round's window is tested here.
+__device__ __forceinline__ Screened screen_result(const ScreenParams &p, int b, int lane) {
+    const Window w = p.win[p.n_rounds - 1];
+    int j = p.n_rounds > 1 ? p.from[b] : w.a;
+    if (j == w.a) {  // every earlier window accepted (a stream that stopped before has j < w.a)
+        bool go = true;
+        while (go && j < w.b) {
+            const bool acc = j + lane < w.b && screen_accepts(p, b, j + lane);
+            const uint64_t no = ~__ballot(acc);
+            const int f = no != 0 ? __ffsll((unsigned long long)no) - 1 : kWave;
+            j += f;
+            go = f == kWave;
+        }
+    }
+    Screened r{j, 0, 0.0f};
+    if (j < p.rows) {
+        r.mu = screen_combine(p, b, j).x;
+        r.known = r.mu > kLowest && r.mu < INFINITY && p.a.inv_temp[b] < 1e30f ? 1 : 0;
+    }
+    return r;
+}
+
+// Between rounds: the streams whose window was accepted whole go on (the list of round `round`), the
+// others' positions are final.  One workgroup: done by every workgroup of the next round instead,
+// the tests' scattered loads took more than the rows (256 streams, second round: 40 us for 270 rows,
+// 17 us without them).
+__global__ void __launch_bounds__(kThreads) logits_advance(ScreenParams p, int round) {
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    __shared__ uint8_t sh_acc[kScreenStreams * kScreenRows / 2];  // [stream of the list][position]
+    const int n = p.a.n_streams;
+    const Window pw = p.win[round - 1];
+    const int prows = pw.b - pw.a;
+    const int32_t *list = p.alive + (int64_t)(round - 1) * (n + 1);
+    int32_t *out = p.alive + (int64_t)round * (n + 1);
+    const int n_prev = round > 1 ? list[0] : n;
+    auto stream = [&](int i) { return round > 1 ? list[1 + i] : i; };
+    for (int i = tid; i < n_prev * prows; i += kThreads)
+        sh_acc[i] = screen_accepts(p, stream(i / prows), pw.a + i % prows) ? 1 : 0;
+    __syncthreads();
+    if (wave != 0) return;
+    int count = 0;
+    for (int base = 0; base < n_prev; base += kWave) {
+        const int i = base + lane;
+        int f = 0, b = 0;
+        if (i < n_prev) {
+            b = stream(i);
+            while (f < prows && sh_acc[i * prows + f]) ++f;
+            p.from[b] = pw.a + f;
+        }
+        const bool stay = i < n_prev && f == prows;
+        const uint64_t m = __ballot(stay);
+        if (stay) out[1 + count + __popcll(m & ((1ull << lane) - 1ull))] = b;
+        count += __popcll(m);
+    }
+    if (lane == 0) out[0] = count;
+}
+
+// One round: the splits of the window's rows of the streams still undecided, a workgroup each.
+__global__ void __launch_bounds__(kScreenThreads) logits_screen(ScreenParams p, int round) {
+    const LogitsArgs &a = p.a;
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    __shared__ float2 sh_ms[kScreenWaves];
+    const Window w = p.win[round];
+    const int rows = w.b - w.a;
+    const int32_t *list = p.alive + (int64_t)round * (a.n_streams + 1);
+    const int n_alive = round > 0 ? list[0] : a.n_streams;
+    const int items = n_alive * rows * p.splits;
+    for (int item = blockIdx.x; item < items; item += gridDim.x) {
+        const int sp = item % p.splits, row_item = item / p.splits;
+        const int i = row_item / rows, j = w.a + row_item % rows;
+        const int b = round > 0 ? list[1 + i] : i;
+        const int t0 = a.target_off[b];
+        const int M = a.target_off[b + 1] - t0;
+        if (M > a.max_m || j > M) continue;  // (M < 0: j > M)
+        const float c = a.inv_temp[b] * kLog2e;
+        const uint16_t *row = a.logits + (int64_t)(t0 + b + j) * a.ld;
+        const int c1 = (sp + 1) * p.cps < p.nc ? (sp + 1) * p.cps : p.nc;
+        float m = kLowest, s = 0.0f;
+        int ck = sp * p.cps + wave;
+        uint32_t wd[8] = {}, nx[8] = {};
+        if (ck < c1) load16s<false>(row, ck, lane, a.v_t, wd);
+        for (; ck < c1; ck += kScreenWaves) {
+            if (ck + kScreenWaves < c1) load16s<false>(row, ck + kScreenWaves, lane, a.v_t, nx);
+            float x[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) x[k] = bf16_value(elem(wd, k));
+            if ((ck + 1) * kChunk > a.v_t) {  // the row's ragged end
+#pragma unroll
+                for (int k = 0; k < 16; ++k)
+                    if (elem_index_s(ck, lane, k) >= a.v_t) x[k] = -INFINITY;
+            }
+            float mx = x[0];
+#pragma unroll
+            for (int k = 1; k < 16; ++k) mx = fmaxf(mx, x[k]);
+            const float mn = fmaxf(m, mx * c);  // scaling by c > 0 keeps the order: the largest y
+            float t = 0.0f;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) t += __builtin_amdgcn_exp2f(fmaf(x[k], c, -mn));
+            s = s * __builtin_amdgcn_exp2f(m - mn) + t;
+            m = mn;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) wd[k] = nx[k];
+        }
+        float wm = m;
+        for (int off = kWave / 2; off > 0; off >>= 1) wm = fmaxf(wm, __shfl_xor(wm, off));
+        float ws = s * __builtin_amdgcn_exp2f(m - wm);
+        for (int off = kWave / 2; off > 0; off >>= 1) ws += __shfl_xor(ws, off);
+        if (lane == 0) sh_ms[wave] = make_float2(wm, ws);
+        __syncthreads();
+        if (tid == 0) {
+            float bm = sh_ms[0].x, bs = 0.0f;
+            for (int k = 1; k < kScreenWaves; ++k) bm = fmaxf(bm, sh_ms[k].x);
+            for (int k = 0; k < kScreenWaves; ++k) bs += sh_ms[k].y * __builtin_amdgcn_exp2f(sh_ms[k].x - bm);
+            p.part[((int64_t)b * p.rows + j) * p.splits + sp] = make_float2(bm, bs);
+        }
+        __syncthreads();
+    }
+}
+
+// ------------------------------------------------------------------ exact sums over many workgroups
+// Fewer streams than compute units: the chunk sums of every stream's selected row by sum_splits
+// workgroups each (with normalisers after the acceptance scan, else of the position the screen
+// stopped at), the sampling in a second kernel.  A workgroup takes a few chunks, so the
+// weights come from the formula: a table would cost more than it saves.
+template <bool LSE>
+__global__ void __launch_bounds__(kScreenThreads) logits_sums(ScreenParams p) {
+    const LogitsArgs &a = p.a;
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int b = blockIdx.x / p.sum_splits, sp = blockIdx.x % p.sum_splits;
+    __shared__ LseScan sh_rec;
+    const int t0 = a.target_off[b];
+    const int M = a.target_off[b + 1] - t0;
+    const float it = a.inv_temp[b];
+    const float cb = it * kLog2e;
+    if (!(M >= 0 && M <= a.max_m && it > 0.0f)) return;  // the sampling kernel writes the sentinels
+    if (wave == 0) {
+        LseScan rec;
+        if (LSE) {
+            rec = lse_scan(a, b, t0, M, cb, lane);
+            if (sp == 0 && lane == 0) p.rec[b] = rec;
+        } else {
+            const Screened scr = screen_result(p, b, lane);
+            rec.r = scr.known ? scr.j : -1;
+            rec.L = scr.mu;
+        }
+        if (lane == 0) sh_rec = rec;
+    }
+    __syncthreads();
+    const int r = sh_rec.r;
+    if (r < 0) return;  // left to the walk
+    const float b31 = 31.0f - (LSE ? sh_rec.L * kLog2e : sh_rec.L);
+    const uint16_t *row = a.logits + (int64_t)(t0 + b + r) * a.ld;
+    const int c1 = (sp + 1) * p.sum_cps < p.nc ? (sp + 1) * p.sum_cps : p.nc;
+    for (int c = sp * p.sum_cps + wave; c < c1; c += kScreenWaves) {
+        uint32_t w[8];
+        load16s<true>(row, c, lane, a.v_t, w);
+        uint64_t acc = 0;
+        if ((c + 1) * kChunk <= a.v_t) {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) acc += e31_at(expo(elem(w, k), cb, b31));
+        } else {
+#pragma unroll
+            for (int k = 0; k < 16; ++k)
+                if (elem_index_s(c, lane, k) < a.v_t) acc += e31_at(expo(elem(w, k), cb, b31));
+        }
+        acc = chunk_total(acc);
+        if (lane == kWave - 1) p.sums[(int64_t)b * p.nc + c] = acc;
+    }
+}
+
+// With normalisers: one wave per stream samples from logits_sums' chunk sums.
+__global__ void __launch_bounds__(kWave) logits_sample(ScreenParams p) {
+    const LogitsArgs &a = p.a;
+    const int b = blockIdx.x, lane = threadIdx.x;
+    const int t0 = a.target_off[b];
+    const int M = a.target_off[b + 1] - t0;
+    const float it = a.inv_temp[b];
+    const float cb = it * kLog2e;
+    bool ok = M >= 0 && M <= a.max_m && it > 0.0f;
+    for (int base = 0; ok && base < M; base += kWave) {
+        const int j = base + lane;
+        ok = !__any(j < M && (a.target_ids[t0 + j] < 0 || a.target_ids[t0 + j] >= a.v_t));
+    }
+    int r = -1, token = -1;
+    if (ok) {
+        const LseScan rec = p.rec[b];
+        const float b31 = 31.0f - rec.L * kLog2e;
+        const uint16_t *row = a.logits + (int64_t)(t0 + b + rec.r) * a.ld;
+        uint64_t adj = 0, before = 0;
+        if (rec.r < M) {
+            adj = lse_residual(rec);
+            before = e31_at(expo((uint32_t)rec.x, cb, b31));
+        }
+        r = rec.r;
+        token = sample_row(row, a.v_t, p.nc, cb, b31, nullptr, rec.t, adj, before, a.u_sample[b], p.sums + (int64_t)b * p.nc);
+    }
+    if (lane == 0) {
+        a.n_accepted[b] = r;
+        a.out_token[b] = token;
+    }
+}
+
+// ------------------------------------------------------------------ one workgroup per stream
+// kWalk: all rows here.  kFrom: without normalisers, the walk starts where the screen stopped.
+// kSums: as kFrom, and that position's chunk sums are in p.sums.
+enum { kWalk, kFrom, kSums };
+
+template <int MODE>
+__global__ void __launch_bounds__(kThreads) verify_logits_row(ScreenParams p) {
     const LogitsArgs &a = p.a;
     const int b = blockIdx.x;
     const int tid = threadIdx.x, lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     extern __shared__ uint64_t sh_part[];  // nc chunk sums of e31
     __shared__ float sh_red[kWaves];
-    __shared__ int sh_ok, sh_r;
-    __shared__ float sh_m, sh_L, sh_q, sh_P;
+    __shared__ int sh_ok;
+    __shared__ float sh_m;
+    __shared__ LseScan sh_rec;
+    __shared__ Screened sh_scr;
     __shared__ int sh_next;  // 1: accepted, go to the next row
     __shared__ uint64_t sh_before, sh_adj;
-    __shared__ int sh_t, sh_x;
+    __shared__ int sh_t;
     __shared__ int sh_ctr;  // the row pass's chunk counter
     __shared__ uint64_t sh_tab[kTabSlots];  // the row's weight table
 
@@ -424,51 +770,21 @@ __global__ void __launch_bounds__(kThreads) verify_logits_row(LogitsParams p) {
         }
         if (lane == 0) sh_ok = ok ? 1 : 0;
     }
-    if (a.lse != nullptr) {
+    if (MODE != kWalk && wave == 0) {
+        const Screened scr = screen_result(p, b, lane);
+        if (lane == 0) sh_scr = scr;
+    }
+    if (MODE == kWalk && a.lse != nullptr) {
         // normalisers given: the acceptance test from one gathered logit per position, then
         // one pass over the residual (or bonus) row
         // (the rejecting lane's L, t, q, P and logit, or the bonus row's L, go to LDS with
         // gamma, so the row pass and the residual entry need no further dependent load; an id
         // outside the vocabulary is not gathered, and the stream then ends as a sentinel)
         if (wave == 0) {
-            const float L_bonus = a.lse[t0 + b + M];
-            int gamma = M, t_r = -1, x_r = 0;
-            float L_r = L_bonus, q_r = 0.0f, P_r = 0.0f;
-            for (int base = 0; base < M && gamma == M; base += kWave) {
-                const int j = base + lane;
-                bool rej = false;
-                int tj = 0, xj = 0;
-                float Lj = 0.0f, qj = 0.0f, P = 0.0f;
-                if (j < M) {
-                    const int64_t r = t0 + b + j;
-                    tj = a.target_ids[t0 + j];
-                    Lj = a.lse[r];
-                    qj = a.q[t0 + j];
-                    if (tj >= 0 && tj < v) {
-                        xj = a.logits[r * a.ld + tj];
-                        P = fminf(fmaxf(weight_at(expo(xj, cb, 31.0f - Lj * kLog2e)), 0.0f), 1.0f);
-                        rej = !(qj <= 0.0f || a.u_accept[t0 + j] < P / qj);
-                    }
-                }
-                const unsigned long long rm = __ballot(rej);
-                if (rm != 0ull) {
-                    const int src = __ffsll(rm) - 1;
-                    gamma = base + src;
-                    t_r = __builtin_amdgcn_readlane(tj, src);
-                    x_r = __builtin_amdgcn_readlane(xj, src);
-                    L_r = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(Lj), src));
-                    q_r = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(qj), src));
-                    P_r = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(P), src));
-                }
-            }
+            const LseScan rec = lse_scan(a, b, t0, M, cb, lane);
             if (lane == 0) {
                 sh_ctr = kWaves;
-                sh_r = gamma;
-                sh_t = t_r;
-                sh_x = x_r;
-                sh_L = L_r;
-                sh_q = q_r;
-                sh_P = P_r;
+                sh_rec = rec;
             }
         }
         __syncthreads();
@@ -480,11 +796,10 @@ __global__ void __launch_bounds__(kThreads) verify_logits_row(LogitsParams p) {
             }
             return;
         }
-        const int r = sh_r;
-        const int64_t rr = t0 + b + r;
-        const uint16_t *row = a.logits + rr * a.ld;
-        const float L = sh_L;
-        const float b31 = 31.0f - L * kLog2e;
+        const LseScan rec = sh_rec;
+        const int r = rec.r;
+        const uint16_t *row = a.logits + (int64_t)(t0 + b + r) * a.ld;
+        const float b31 = 31.0f - rec.L * kLog2e;
         chunk_sums(row, v, nc, cb, b31, sh_tab, sh_part, &sh_ctr);
         if (wave < 12) TT_STAMP_WAVE(4 + wave);
         __syncthreads();
@@ -493,9 +808,9 @@ __global__ void __launch_bounds__(kThreads) verify_logits_row(LogitsParams p) {
         int t = -1;
         uint64_t adj = 0, before = 0;
         if (r < M) {  // the rejected proposal loses q_r of its mass: its entry is E(t) - q_r, clamped
-            t = sh_t;
-            adj = q31(fminf(fmaxf(sh_P - sh_q, 0.0f), 1.0f));
-            before = e31_at(expo((uint32_t)sh_x, cb, b31));  // the weight the chunk sums counted at t
+            t = rec.t;
+            adj = lse_residual(rec);
+            before = e31_at(expo((uint32_t)rec.x, cb, b31));  // the weight the chunk sums counted at t
         }
         const int token = sample_row(row, v, nc, cb, b31, sh_tab, t, adj, before, a.u_sample[b], sh_part);
         if (lane == 0) {
@@ -513,39 +828,56 @@ __global__ void __launch_bounds__(kThreads) verify_logits_row(LogitsParams p) {
         }
         return;
     }
-    for (int j = 0; j <= M; ++j) {
+    int j = 0;
+    bool known = false;  // this row's mu (kSums: and chunk sums) are there already
+    if (MODE != kWalk) {
+        j = sh_scr.j;
+        known = sh_scr.known != 0;
+    }
+    for (; j <= M; ++j, known = false) {
         const uint16_t *row = a.logits + (int64_t)(t0 + b + j) * a.ld;
-        // pass 1: the row's largest x
+        const uint64_t *tab = sh_tab;
+        // pass 1: the row's largest y
         float m = -INFINITY;
-        uint32_t w[8] = {}, nx[8] = {};
-        if (wave < nc) load16s<false>(row, wave, lane, v, w);
-        for (int c = wave; c < nc; c += kWaves) {
-            if (c + kWaves < nc) load16s<false>(row, c + kWaves, lane, v, nx);
-            if ((c + 1) * kChunk <= v) {
-#pragma unroll
-                for (int k = 0; k < 16; ++k) m = fmaxf(m, scaled(elem(w, k), cb));
-            } else {
-#pragma unroll
-                for (int k = 0; k < 16; ++k)
-                    if (elem_index_s(c, lane, k) < v) m = fmaxf(m, scaled(elem(w, k), cb));
+        if (known) {
+            m = sh_scr.mu;
+            if (tid == 0) sh_ctr = kWaves;
+            if (MODE == kSums) {
+                for (int c = tid; c < nc; c += kThreads) sh_part[c] = p.sums[(int64_t)b * nc + c];
+                tab = nullptr;
             }
-#pragma unroll
-            for (int k = 0; k < 8; ++k) w[k] = nx[k];
+            __syncthreads();
+        } else {
+            uint32_t w[8] = {}, nx[8] = {};
+            if (wave < nc) load16s<false>(row, wave, lane, v, w);
+            for (int c = wave; c < nc; c += kWaves) {
+                if (c + kWaves < nc) load16s<false>(row, c + kWaves, lane, v, nx);
+                if ((c + 1) * kChunk <= v) {
+    #pragma unroll
+                    for (int k = 0; k < 16; ++k) m = fmaxf(m, scaled(elem(w, k), cb));
+                } else {
+    #pragma unroll
+                    for (int k = 0; k < 16; ++k)
+                        if (elem_index_s(c, lane, k) < v) m = fmaxf(m, scaled(elem(w, k), cb));
+                }
+    #pragma unroll
+                for (int k = 0; k < 8; ++k) w[k] = nx[k];
+            }
+            for (int off = kWave / 2; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+            if (lane == 0) sh_red[wave] = m;
+            __syncthreads();
+            if (tid == 0) {
+                float mm = -INFINITY;
+                for (int k = 0; k < kWaves; ++k) mm = fmaxf(mm, sh_red[k]);
+                sh_m = mm;
+                sh_ctr = kWaves;
+            }
+            __syncthreads();
+            m = sh_m;
         }
-        for (int off = kWave / 2; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-        if (lane == 0) sh_red[wave] = m;
-        __syncthreads();
-        if (tid == 0) {
-            float mm = -INFINITY;
-            for (int k = 0; k < kWaves; ++k) mm = fmaxf(mm, sh_red[k]);
-            sh_m = mm;
-            sh_ctr = kWaves;
-        }
-        __syncthreads();
-        m = sh_m;
         // pass 2: chunk sums of e31
         const float b31 = 31.0f - m;
-        chunk_sums(row, v, nc, cb, b31, sh_tab, sh_part, &sh_ctr);
+        if (MODE != kSums || !known) chunk_sums(row, v, nc, cb, b31, sh_tab, sh_part, &sh_ctr);
         __syncthreads();
         // S, the acceptance test of position j, and the residual's entry at t_j
         if (wave == 0) {
@@ -579,7 +911,7 @@ __global__ void __launch_bounds__(kThreads) verify_logits_row(LogitsParams p) {
         __syncthreads();
         if (sh_next) continue;
         if (wave == 0) {
-            const int token = sample_row(row, v, nc, cb, b31, sh_tab, sh_t, sh_adj, sh_before, a.u_sample[b], sh_part);
+            const int token = sample_row(row, v, nc, cb, b31, tab, sh_t, sh_adj, sh_before, a.u_sample[b], sh_part);
             if (lane == 0) {
                 a.n_accepted[b] = j;
                 a.out_token[b] = token;
@@ -591,17 +923,117 @@ __global__ void __launch_bounds__(kThreads) verify_logits_row(LogitsParams p) {
 
 }  // namespace
 
-int launch_verify_logits(const LogitsArgs &a, hipStream_t stream) {
-    if (a.n_streams == 0) return TT_OK;
-    LogitsParams p;
-    p.a = a;
+namespace {
+
+constexpr int kCus = 256;
+constexpr int kSumGrid = 1024;     // workgroups of logits_sums to aim for
+constexpr int kScreenGrid = 2048;  // workgroups of a screening round
+// With normalisers, the row split over workgroups and sampled by a second kernel: for rows long enough
+// to pay for that launch and streams too few to fill the chip.  32 streams of 151,936: 10.9 us against
+// 17.9 in one kernel, 128: 18.1 against 19.9, 200: 22.9 against 20.9; 32 of 32,000: 8.8 against 10.1,
+// 32 of 12,000: no difference.
+constexpr int kLseSplitStreams = 128;
+constexpr int kLseSplitChunks = 16;
+
+// Which kernels a call takes (with a workspace).
+enum Route { kRowRoute, kLseSplit, kScreenRow, kScreenSplit };
+
+Route route(const LogitsArgs &a, int nc) {
+    if (a.lse != nullptr) return a.n_streams <= kLseSplitStreams && nc >= kLseSplitChunks ? kLseSplit : kRowRoute;
+    if (a.n_streams > kScreenStreams || a.max_m < 1) return kRowRoute;
+    return a.n_streams < kCus ? kScreenSplit : kScreenRow;
+}
+
+inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
+
+// The parameters and workspace layout of a call; returns the bytes.
+size_t layout(ScreenParams &p, Route rt, uint8_t *ws) {
+    const LogitsArgs &a = p.a;
+    const size_t n = a.n_streams > 0 ? (size_t)a.n_streams : 0;
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        uint8_t *at = ws + off;
+        off = align256(off + bytes);
+        return at;
+    };
     p.nc = (a.v_t + kChunk - 1) / kChunk;
+    p.n_rounds = 0;
+    if (rt == kRowRoute) return 0;
+    if (rt == kScreenRow || rt == kScreenSplit) {
+        const int last = a.max_m + 1 < kScreenRows ? a.max_m + 1 : kScreenRows;  // rows 0 .. M, the bonus row among them
+        // the first window: about a row per compute unit
+        int len = kCus / a.n_streams < 1 ? 1 : kCus / a.n_streams;
+        for (int at = 0; at < last;) {
+            // (half a window or less left over goes along; sh_acc holds half of the positions)
+            int b = at + len;
+            if (last - b <= len / 2 || p.n_rounds == kMaxRounds - 1) b = last;
+            p.win[p.n_rounds++] = Window{at, b};
+            at = b;
+            len *= 3;
+        }
+        p.rows = last;
+        int splits = kScreenGrid / (a.n_streams * (p.win[0].b - p.win[0].a));
+        splits = splits < 8 ? 8 : splits > 32 ? 32 : splits;
+        const int most = (p.nc + kScreenWaves - 1) / kScreenWaves;
+        if (splits > most) splits = most;
+        p.cps = (p.nc + splits - 1) / splits;
+        p.splits = (p.nc + p.cps - 1) / p.cps;
+        p.from = reinterpret_cast<int32_t *>(take(4 * n));
+        p.alive = reinterpret_cast<int32_t *>(take(4 * (n + 1) * kMaxRounds));
+        p.part = reinterpret_cast<float2 *>(take(8 * n * p.rows * p.splits));
+    }
+    if (rt == kLseSplit || rt == kScreenSplit) {
+        int splits = (kSumGrid + a.n_streams - 1) / (a.n_streams > 0 ? a.n_streams : 1);
+        const int most = (p.nc + kScreenWaves - 1) / kScreenWaves;
+        if (splits > most) splits = most;
+        p.sum_cps = (p.nc + splits - 1) / splits;
+        p.sum_splits = (p.nc + p.sum_cps - 1) / p.sum_cps;
+        p.sums = reinterpret_cast<uint64_t *>(take(8 * n * p.nc));
+        p.rec = reinterpret_cast<LseScan *>(take(sizeof(LseScan) * n));
+    }
+    return off;
+}
+
+template <int MODE>
+int launch_row(const ScreenParams &p, hipStream_t stream) {
     // the chunk sums (up to 64 KiB at the longest rows) sit beside the 64 KiB weight table in LDS
     const size_t lds = 8 * (size_t)p.nc;
-    if (hipFuncSetAttribute(reinterpret_cast<const void *>(&verify_logits_row),
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(&verify_logits_row<MODE>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return TT_ELAUNCH;
-    hipLaunchKernelGGL(verify_logits_row, dim3(a.n_streams), dim3(kThreads), lds, stream, p);
+    hipLaunchKernelGGL(verify_logits_row<MODE>, dim3(p.a.n_streams), dim3(kThreads), lds, stream, p);
+    return hipGetLastError() == hipSuccess ? TT_OK : TT_ELAUNCH;
+}
+
+}  // namespace
+
+size_t logits_workspace_bytes(const LogitsArgs &a) {
+    if (a.n_streams == 0) return 0;
+    ScreenParams p{};
+    p.a = a;
+    return layout(p, route(a, (a.v_t + kChunk - 1) / kChunk), nullptr);
+}
+
+int launch_verify_logits(const LogitsArgs &a, void *workspace, size_t workspace_bytes, hipStream_t stream) {
+    if (a.n_streams == 0) return TT_OK;
+    ScreenParams p{};
+    p.a = a;
+    Route rt = workspace == nullptr ? kRowRoute : route(a, (a.v_t + kChunk - 1) / kChunk);
+    if (layout(p, rt, static_cast<uint8_t *>(workspace)) > workspace_bytes) return TT_EWORKSPACE;
+    for (int r = 0; r < p.n_rounds; ++r) {
+        const int items = a.n_streams * (p.win[r].b - p.win[r].a) * p.splits;
+        if (r > 0) hipLaunchKernelGGL(logits_advance, dim3(1), dim3(kThreads), 0, stream, p, r);
+        hipLaunchKernelGGL(logits_screen, dim3(items < kScreenGrid ? items : kScreenGrid), dim3(kScreenThreads), 0, stream, p, r);
+    }
+    if (rt == kScreenRow) return launch_row<kFrom>(p, stream);
+    if (rt == kRowRoute) return launch_row<kWalk>(p, stream);
+    const dim3 grid(a.n_streams * p.sum_splits);
+    if (rt == kScreenSplit) {
+        hipLaunchKernelGGL(logits_sums<false>, grid, dim3(kScreenThreads), 0, stream, p);
+        return launch_row<kSums>(p, stream);
+    }
+    hipLaunchKernelGGL(logits_sums<true>, grid, dim3(kScreenThreads), 0, stream, p);
+    hipLaunchKernelGGL(logits_sample, dim3(a.n_streams), dim3(kWave), 0, stream, p);
     return hipGetLastError() == hipSuccess ? TT_OK : TT_ELAUNCH;
 }
 

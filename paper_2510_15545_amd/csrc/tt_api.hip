@@ -198,10 +198,31 @@ int tt_verify_tli(int32_t n_streams, int32_t v_d, int32_t v_t, const int32_t *d2
     return tt::launch_verify_tli(a, static_cast<hipStream_t>(stream));
 }
 
+int tt_verify_logits_workspace_size(int32_t n_streams, int32_t v_t, int32_t max_m, int32_t with_lse, size_t *bytes) {
+    if (bytes == nullptr || n_streams < 0 || v_t < 1 || max_m < 0 || max_m > kMaxVerifyLen) return TT_EINVAL;
+    if (v_t > kMaxLogitsRow) return TT_EUNSUPPORTED;
+    static const float given = 0.0f;
+    tt::LogitsArgs a{};
+    a.n_streams = n_streams;
+    a.v_t = v_t;
+    a.max_m = max_m;
+    a.lse = with_lse != 0 ? &given : nullptr;
+    *bytes = tt::logits_workspace_bytes(a);
+    return TT_OK;
+}
+
 int tt_verify_logits(int32_t n_streams, int32_t v_t, const int32_t *target_ids, const int32_t *target_off,
                      const float *q, const uint16_t *target_logits, int64_t target_ld, const float *inv_temperature,
                      const float *lse, const float *u_accept, const float *u_sample, int32_t max_m,
                      int32_t *n_accepted, int32_t *out_token, void *stream) {
+    return tt_verify_logits_ws(n_streams, v_t, target_ids, target_off, q, target_logits, target_ld, inv_temperature, lse,
+                               u_accept, u_sample, max_m, n_accepted, out_token, nullptr, 0, stream);
+}
+
+int tt_verify_logits_ws(int32_t n_streams, int32_t v_t, const int32_t *target_ids, const int32_t *target_off,
+                        const float *q, const uint16_t *target_logits, int64_t target_ld, const float *inv_temperature,
+                        const float *lse, const float *u_accept, const float *u_sample, int32_t max_m,
+                        int32_t *n_accepted, int32_t *out_token, void *workspace, size_t workspace_bytes, void *stream) {
     if (n_streams < 0 || v_t < 1 || target_ld < v_t || max_m < 0 || max_m > kMaxVerifyLen) return TT_EINVAL;
     if (v_t > kMaxLogitsRow) return TT_EUNSUPPORTED;
     if (n_streams == 0) return TT_OK;
@@ -223,7 +244,7 @@ int tt_verify_logits(int32_t n_streams, int32_t v_t, const int32_t *target_ids, 
     a.max_m = max_m;
     a.n_accepted = n_accepted;
     a.out_token = out_token;
-    return tt::launch_verify_logits(a, static_cast<hipStream_t>(stream));
+    return tt::launch_verify_logits(a, workspace, workspace_bytes, static_cast<hipStream_t>(stream));
 }
 
 int tt_delta_histogram(int32_t n_pairs, const int32_t *draft_off, const int32_t *target_off,

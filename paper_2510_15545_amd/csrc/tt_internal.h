@@ -112,7 +112,10 @@ struct LogitsArgs {
     int32_t max_m;
     int32_t *n_accepted, *out_token;
 };
-int launch_verify_logits(const LogitsArgs &a, hipStream_t stream);
+// Workspace of the kernels that use more than one workgroup per stream (0: none does).
+size_t logits_workspace_bytes(const LogitsArgs &a);
+// workspace null: one workgroup per stream.
+int launch_verify_logits(const LogitsArgs &a, void *workspace, size_t workspace_bytes, hipStream_t stream);
 
 // ---------------------------------------------------------------- TLI proposal rows (tli.hip)
 struct TliArgs {

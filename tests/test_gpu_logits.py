@@ -216,3 +216,37 @@ def test_logits_at_the_row_limit(with_lse):
     us = np.float32([0.25, 0.75])
     case = (ids, off, q, bits, it, ua, us, Ms)
     run_both(V, case, 1, lse=case_lse(V, case) if with_lse else None)
+
+
+@pytest.mark.parametrize("n,V,max_m", [(1, 1023, 1), (1, 17409, 70), (5, 2048, 16), (8, 33000, 40), (129, 1500, 6), (200, 700, 16),
+                                       (255, 1100, 3), (256, 1100, 30), (300, 515, 16), (512, 700, 24), (513, 700, 3)])
+def test_logits_screened_rows(n, V, max_m):
+    """Rows without NaN, so that the screen decides: one round and several, windows past a stream's rows, more
+    positions than are screened, both kernels after it, and the first batch too large for it; logits so large
+    that the screen leaves every test to the exact walk; -inf and lowest-value masks."""
+    ids, off, q, bits, it, ua, us, Ms = logits_case(n, V, seed=5, max_m=max_m)
+    bits[:, :V] = np.where((bits[:, :V] & 0x7FFF) > 0x7F80, 0x3F80, bits[:, :V])  # NaN -> 1.0
+    kept = np.repeat(np.arange(n), Ms) % 3 != 2
+    q[kept] = 0.0  # two streams of three accept wherever q says so (q = 0 keeps the proposal): long walks
+    q[kept & (np.arange(len(q)) % 2 == 0)] = 2.0 ** -40  # and where the weight is not 0
+    case = (ids, off, q, bits, it, ua, us, Ms)
+    run_both(V, case, max_m)
+    masked = bits.copy()
+    masked[::2, : V // 3] = 0xFF80  # -inf
+    masked[1::2, V // 2: V // 2 + 300] = 0xFF7F  # the lowest finite value
+    masked[-1, :V] = 0xFF80
+    run_both(V, (ids, off, q, masked, it, ua, us, Ms), max_m)
+    run_both(V, (ids, off, q, bits, it * np.float32(300), ua, us, Ms), max_m)
+
+
+@pytest.mark.parametrize("n,V", [(1, 15361), (3, 16384), (128, 15400), (129, 15400), (2, 40001)])
+def test_logits_lse_split_rows(n, V):
+    """With normalisers, around the line to the split kernels; ragged rows, sentinels among the streams."""
+    ids, off, q, bits, it, ua, us, Ms = logits_case(n, V, seed=6, max_m=5)
+    if n > 2:
+        it[1] = 0.0
+        if Ms[2]:
+            ids[off[2]] = V
+    case = (ids, off, q, bits, it, ua, us, Ms)
+    run_both(V, case, 5, lse=case_lse(V, case))
+    run_both(V, case, 4, lse=case_lse(V, case, -1.0))
