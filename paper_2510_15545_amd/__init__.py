@@ -24,6 +24,8 @@ from __future__ import annotations
 import ctypes
 import os
 
+import torch
+
 __all__ = ["Vocab", "align", "align_workspace", "transfer", "verify", "verify_noalloc", "verify_dense", "verify_workspace", "lib",
            "delta_histogram", "delta_quantile", "w_at_quantile", "token_index", "retokenize", "LIB_PATH",
            "vocab_intersection", "tli_proposal", "verify_tli", "verify_logits",
@@ -109,36 +111,30 @@ def lib():
     return _lib
 
 
-def _torch():
-    import torch
-
-    return torch
-
-
 def _stream_handle(stream):
-    torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:  # the current stream's handle without a Stream object around it
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _ptr(t, dtype, name, allow_none=False):
+    """The tensor's address as an int (the argument types declared in lib() make a pointer of it)."""
     if t is None:
         if allow_none:
             return None
         raise ValueError(f"{name} is required")
+    if t.is_cuda and t.dtype is dtype and t.is_contiguous():
+        return t.data_ptr()
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
     if t.dtype != dtype:
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    raise ValueError(f"{name} must be contiguous")
 
 
 def _scratch(nbytes: int, device, stream):
     """Device memory for one call on `stream`, from that stream's pool: once the call has returned, the
     allocator hands it only to work that the same stream runs later."""
-    torch = _torch()
     if stream is None:
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
     with torch.cuda.stream(stream):
@@ -154,18 +150,16 @@ class Vocab:
     """Token byte table on the device: token t is data[offsets[t]:offsets[t+1]]."""
 
     def __init__(self, data, offsets, max_token_bytes: int):
-        torch = _torch()
         self.data = data if data.numel() else torch.zeros(1, dtype=torch.uint8, device=offsets.device)
         self.offsets = offsets
         self.n_tokens = int(offsets.numel()) - 1
         self.max_token_bytes = int(max_token_bytes)
-        self._c = c_tt_vocab(_ptr(self.data, torch.uint8, "vocab bytes").value,
-                             _ptr(self.offsets, torch.int32, "vocab offsets").value,
+        self._c = c_tt_vocab(_ptr(self.data, torch.uint8, "vocab bytes"),
+                             _ptr(self.offsets, torch.int32, "vocab offsets"),
                              self.n_tokens, self.max_token_bytes)
 
     @classmethod
     def from_host(cls, data, offsets, max_token_bytes: int, device="cuda"):
-        torch = _torch()
         return cls(torch.as_tensor(data, dtype=torch.uint8).to(device),
                    torch.as_tensor(offsets, dtype=torch.int32).to(device), max_token_bytes)
 
@@ -177,7 +171,6 @@ def path_capacity(draft_off_last: int, target_off_last: int) -> int:
 
 def align_workspace(n_pairs: int, max_k: int, max_m: int, w: int, max_token_bytes: int, device="cuda"):
     """A workspace for tt_align with these bounds (None when none is needed)."""
-    torch = _torch()
     n = ctypes.c_size_t(0)
     _check(lib().tt_align_workspace_size(int(n_pairs), int(max_k), int(max_m), int(w), int(max_token_bytes),
                                          ctypes.byref(n)), "tt_align_workspace_size")
@@ -192,7 +185,6 @@ def align(vd: Vocab, vt: Vocab, draft_ids, draft_off, target_ids, target_off, w:
     offsets on the host if not given (one small device->host copy).
     workspace: from align_workspace(); allocated here when needed and not given.
     """
-    torch = _torch()
     i32 = torch.int32
     n = int(draft_off.numel()) - 1
     dev = draft_off.device
@@ -214,7 +206,7 @@ def align(vd: Vocab, vt: Vocab, draft_ids, draft_off, target_ids, target_off, w:
                         int(max_k), int(max_m), int(w),
                         _ptr(cost, i32, "cost"), _ptr(plen, i32, "path_len"),
                         _ptr(path, i32, "path"), _ptr(mp, i32, "map"),
-                        None if workspace is None else ctypes.c_void_p(workspace.data_ptr()),
+                        None if workspace is None else workspace.data_ptr(),
                         0 if workspace is None else int(workspace.numel()), _stream_handle(stream))
     _check(st, "tt_align")
     return out
@@ -222,7 +214,6 @@ def align(vd: Vocab, vt: Vocab, draft_ids, draft_off, target_ids, target_off, w:
 
 def transfer(v_d: int, draft_ids, draft_off, target_off, mp, draft_probs, out=None, stream=None):
     """tt_transfer.  Returns q (float32, one per target position)."""
-    torch = _torch()
     i32 = torch.int32
     n = int(draft_off.numel()) - 1
     if draft_probs.dim() != 2 or draft_probs.stride(1) != 1:
@@ -233,7 +224,7 @@ def transfer(v_d: int, draft_ids, draft_off, target_off, mp, draft_probs, out=No
         out = torch.empty(max(1, int(mp.numel())), dtype=torch.float32, device=mp.device)
     st = lib().tt_transfer(n, int(v_d), _ptr(draft_ids, i32, "draft_ids"), _ptr(draft_off, i32, "draft_off"),
                            _ptr(target_off, i32, "target_off"), _ptr(mp, i32, "map"),
-                           ctypes.c_void_p(draft_probs.data_ptr()),
+                           draft_probs.data_ptr(),
                            int(draft_probs.stride(0)), _ptr(out, torch.float32, "q"), _stream_handle(stream))
     _check(st, "tt_transfer")
     return out
@@ -241,7 +232,6 @@ def transfer(v_d: int, draft_ids, draft_off, target_off, mp, draft_probs, out=No
 
 def verify_workspace(n_streams: int, v_t: int, device="cuda"):
     """A workspace for tt_verify (reusable by calls that do not overlap in time)."""
-    torch = _torch()
     n = ctypes.c_size_t(0)
     _check(lib().tt_verify_workspace_size(int(n_streams), int(v_t), ctypes.byref(n)),
            "tt_verify_workspace_size")
@@ -251,7 +241,6 @@ def verify_workspace(n_streams: int, v_t: int, device="cuda"):
 def verify(v_t: int, target_ids, target_off, q, target_probs, u_accept, u_sample, max_m: int,
            workspace=None, residual: bool = False, out=None, stream=None):
     """tt_verify.  Returns (n_accepted, out_token, residual or None)."""
-    torch = _torch()
     i32, f32 = torch.int32, torch.float32
     n = int(target_off.numel()) - 1
     dev = target_off.device
@@ -269,11 +258,11 @@ def verify(v_t: int, target_ids, target_off, q, target_probs, u_accept, u_sample
     if target_probs.dtype != f32 or not target_probs.is_cuda:
         raise ValueError("target_probs must be a float32 device tensor")
     st = lib().tt_verify(n, int(v_t), _ptr(ti, i32, "target_ids"), _ptr(target_off, i32, "target_off"),
-                         _ptr(qq, f32, "q"), ctypes.c_void_p(target_probs.data_ptr()),
+                         _ptr(qq, f32, "q"), target_probs.data_ptr(),
                          int(target_probs.stride(0)), _ptr(ua, f32, "u_accept"),
                          _ptr(u_sample, f32, "u_sample"), int(max_m), _ptr(nacc, i32, "n_accepted"),
                          _ptr(tok, i32, "out_token"), _ptr(res, f32, "residual", allow_none=True),
-                         ctypes.c_void_p(workspace.data_ptr()), int(workspace.numel()), _stream_handle(stream))
+                         workspace.data_ptr(), int(workspace.numel()), _stream_handle(stream))
     _check(st, "tt_verify")
     return out
 
@@ -282,7 +271,6 @@ def verify_noalloc(v_t: int, target_ids, target_off, q, target_probs, u_accept, 
                    residual: bool = False, out=None, stream=None):
     """tt_verify_noalloc: tt_verify with the library's own scratch (no workspace).  Returns
     (n_accepted, out_token, residual or None); pass `out` to allocate nothing here either."""
-    torch = _torch()
     i32, f32 = torch.int32, torch.float32
     n = int(target_off.numel()) - 1
     dev = target_off.device
@@ -293,7 +281,7 @@ def verify_noalloc(v_t: int, target_ids, target_off, q, target_probs, u_accept, 
                torch.zeros((n, target_probs.stride(0)), dtype=f32, device=dev) if residual else None)
     nacc, tok, res = out
     st = lib().tt_verify_noalloc(n, int(v_t), _ptr(target_ids, i32, "target_ids"), _ptr(target_off, i32, "target_off"),
-                                 _ptr(q, f32, "q"), ctypes.c_void_p(target_probs.data_ptr()),
+                                 _ptr(q, f32, "q"), target_probs.data_ptr(),
                                  int(target_probs.stride(0)), _ptr(u_accept, f32, "u_accept"),
                                  _ptr(u_sample, f32, "u_sample"), int(max_m), _ptr(nacc, i32, "n_accepted"),
                                  _ptr(tok, i32, "out_token"), _ptr(res, f32, "residual", allow_none=True),
@@ -305,7 +293,6 @@ def verify_noalloc(v_t: int, target_ids, target_off, q, target_probs, u_accept, 
 def verify_dense(v: int, draft_ids, off, draft_probs, target_probs, u_accept, u_sample, max_m: int,
                  workspace=None, residual: bool = False, out=None, stream=None):
     """tt_verify_dense.  Returns (n_accepted, out_token, residual or None)."""
-    torch = _torch()
     i32, f32 = torch.int32, torch.float32
     n = int(off.numel()) - 1
     dev = off.device
@@ -321,12 +308,12 @@ def verify_dense(v: int, draft_ids, off, draft_probs, target_probs, u_accept, u_
     ids = draft_ids if draft_ids.numel() else torch.zeros(1, dtype=i32, device=dev)
     ua = u_accept if u_accept.numel() else torch.zeros(1, dtype=f32, device=dev)
     st = lib().tt_verify_dense(n, int(v), _ptr(ids, i32, "draft_ids"), _ptr(off, i32, "off"),
-                               ctypes.c_void_p(draft_probs.data_ptr()), int(draft_probs.stride(0)),
-                               ctypes.c_void_p(target_probs.data_ptr()), int(target_probs.stride(0)),
+                               draft_probs.data_ptr(), int(draft_probs.stride(0)),
+                               target_probs.data_ptr(), int(target_probs.stride(0)),
                                _ptr(ua, f32, "u_accept"), _ptr(u_sample, f32, "u_sample"), int(max_m),
                                _ptr(nacc, i32, "n_accepted"), _ptr(tok, i32, "out_token"),
                                _ptr(res, f32, "residual", allow_none=True),
-                               ctypes.c_void_p(workspace.data_ptr()), int(workspace.numel()), _stream_handle(stream))
+                               workspace.data_ptr(), int(workspace.numel()), _stream_handle(stream))
     _check(st, "tt_verify_dense")
     return out
 
@@ -336,7 +323,6 @@ def verify_logits(v_t: int, target_ids, target_off, q, target_logits, inv_temper
     """tt_verify_logits: target_logits is a 2-D row-major device tensor of bf16 (or its int16 / uint16
     bit patterns); inv_temperature float32 [n_streams]; lse optional float32 [rows], the rows'
     log-sum-exp of logit * inv_temperature.  Returns (n_accepted, out_token)."""
-    torch = _torch()
     i32, f32 = torch.int32, torch.float32
     n = int(target_off.numel()) - 1
     dev = target_off.device
@@ -353,11 +339,11 @@ def verify_logits(v_t: int, target_ids, target_off, q, target_logits, inv_temper
     st = lib().tt_verify_logits_workspace_size(n, int(v_t), int(max_m), 0 if lse is None else 1, ctypes.byref(nb))
     ws = _scratch(nb.value, dev, stream) if st == TT_OK and nb.value else None
     st = lib().tt_verify_logits_ws(n, int(v_t), _ptr(ids, i32, "target_ids"), _ptr(target_off, i32, "target_off"),
-                                _ptr(qq, f32, "q"), ctypes.c_void_p(target_logits.data_ptr()),
+                                _ptr(qq, f32, "q"), target_logits.data_ptr(),
                                 int(target_logits.stride(0)), _ptr(inv_temperature, f32, "inv_temperature"),
                                 _ptr(lse, f32, "lse", allow_none=True), _ptr(ua, f32, "u_accept"), _ptr(u_sample, f32, "u_sample"), int(max_m),
                                 _ptr(nacc, i32, "n_accepted"), _ptr(tok, i32, "out_token"),
-                                None if ws is None else ctypes.c_void_p(ws.data_ptr()), nb.value, _stream_handle(stream))
+                                None if ws is None else ws.data_ptr(), nb.value, _stream_handle(stream))
     _check(st, "tt_verify_logits")
     return out
 
@@ -365,7 +351,6 @@ def verify_logits(v_t: int, target_ids, target_off, q, target_logits, inv_temper
 def delta_histogram(draft_off, target_off, path_len, path, n_bins: int, out=None, stream=None):
     """tt_delta_histogram: int32 counts of |i - j| over every aligned pair's path cells (last bin
     collects |i - j| >= n_bins - 1)."""
-    torch = _torch()
     i32 = torch.int32
     n = int(draft_off.numel()) - 1
     hist = torch.empty(int(n_bins), dtype=i32, device=draft_off.device) if out is None else out
@@ -379,7 +364,6 @@ def delta_histogram(draft_off, target_off, path_len, path, n_bins: int, out=None
 def delta_quantile(hist, num: int = 9, den: int = 10, out=None, stream=None):
     """tt_delta_quantile: (int32 device tensor of one element) the smallest deviation d at which
     the cumulative counts of `hist` reach num/den of their total (App. K)."""
-    torch = _torch()
     i32 = torch.int32
     d = torch.empty(1, dtype=i32, device=hist.device) if out is None else out
     st = lib().tt_delta_quantile(_ptr(hist, i32, "hist"), int(hist.numel()), int(num), int(den), _ptr(d, i32, "d_out"),
@@ -395,11 +379,10 @@ def w_at_quantile(hist, num: int = 9, den: int = 10) -> int:
 
 def token_index(v: Vocab, stream=None):
     """tt_token_index_build: the longest-match index of a token table (a uint8 device tensor)."""
-    torch = _torch()
     n = ctypes.c_size_t(0)
     _check(lib().tt_token_index_size(v.n_tokens, ctypes.byref(n)), "tt_token_index_size")
     idx = torch.empty(n.value, dtype=torch.uint8, device=v.offsets.device)
-    _check(lib().tt_token_index_build(ctypes.byref(v._c), ctypes.c_void_p(idx.data_ptr()), n.value,
+    _check(lib().tt_token_index_build(ctypes.byref(v._c), idx.data_ptr(), n.value,
                                       _stream_handle(stream)), "tt_token_index_build")
     return idx
 
@@ -408,7 +391,6 @@ def retokenize(vd: Vocab, vt: Vocab, vt_index, draft_ids, draft_off, max_bytes: 
                out=None, workspace=None, stream=None):
     """tt_retokenize.  Returns (target_ids, target_off) device tensors; target_ids has room for
     n_streams * max_m ids (the first target_off[-1] are valid)."""
-    torch = _torch()
     i32 = torch.int32
     n = int(draft_off.numel()) - 1
     dev = draft_off.device
@@ -420,10 +402,10 @@ def retokenize(vd: Vocab, vt: Vocab, vt_index, draft_ids, draft_off, max_bytes: 
         out = (torch.empty(max(1, n * int(max_m)), dtype=i32, device=dev), torch.empty(n + 1, dtype=i32, device=dev))
     tids, toff = out
     ids = draft_ids if draft_ids.numel() else torch.zeros(1, dtype=i32, device=dev)
-    st = lib().tt_retokenize(ctypes.byref(vd._c), ctypes.byref(vt._c), ctypes.c_void_p(vt_index.data_ptr()),
+    st = lib().tt_retokenize(ctypes.byref(vd._c), ctypes.byref(vt._c), vt_index.data_ptr(),
                              int(vt_index.numel()), n, _ptr(ids, i32, "draft_ids"), _ptr(draft_off, i32, "draft_off"),
                              int(max_bytes), int(max_m), _ptr(tids, i32, "target_ids"),
-                             _ptr(toff, i32, "target_off"), ctypes.c_void_p(workspace.data_ptr()),
+                             _ptr(toff, i32, "target_off"), workspace.data_ptr(),
                              int(workspace.numel()), _stream_handle(stream))
     _check(st, "tt_retokenize")
     return out
@@ -432,14 +414,13 @@ def retokenize(vd: Vocab, vt: Vocab, vt_index, draft_ids, draft_off, max_bytes: 
 def vocab_intersection(vd: Vocab, vd_index, vt: Vocab, vt_index, out=None, stream=None):
     """tt_vocab_intersection (App. D Alg. 3's T ∩ D by byte strings).  Returns (d2t, t2d) int32
     device tensors of vd.n_tokens and vt.n_tokens entries (-1 outside the intersection)."""
-    torch = _torch()
     i32 = torch.int32
     dev = vd.offsets.device
     if out is None:
         out = (torch.empty(vd.n_tokens, dtype=i32, device=dev), torch.empty(vt.n_tokens, dtype=i32, device=dev))
     d2t, t2d = out
-    st = lib().tt_vocab_intersection(ctypes.byref(vd._c), ctypes.c_void_p(vd_index.data_ptr()), int(vd_index.numel()),
-                                     ctypes.byref(vt._c), ctypes.c_void_p(vt_index.data_ptr()), int(vt_index.numel()),
+    st = lib().tt_vocab_intersection(ctypes.byref(vd._c), vd_index.data_ptr(), int(vd_index.numel()),
+                                     ctypes.byref(vt._c), vt_index.data_ptr(), int(vt_index.numel()),
                                      _ptr(d2t, i32, "d2t"), _ptr(t2d, i32, "t2d"), _stream_handle(stream))
     _check(st, "tt_vocab_intersection")
     return out
@@ -448,7 +429,6 @@ def vocab_intersection(vd: Vocab, vd_index, vt: Vocab, vt_index, out=None, strea
 def tli_proposal(d2t, t2d, draft_probs, v_d: int | None = None, out=None, stream=None):
     """tt_tli_proposal: q' rows over the target vocabulary (App. D Alg. 3) from draft rows
     [n, >= V_d] float32.  Returns out [n, V_t] (or the given tensor, any row stride >= V_t)."""
-    torch = _torch()
     i32, f32 = torch.int32, torch.float32
     v_d = int(d2t.numel()) if v_d is None else int(v_d)
     v_t = int(t2d.numel())
@@ -460,8 +440,8 @@ def tli_proposal(d2t, t2d, draft_probs, v_d: int | None = None, out=None, stream
     if out.dim() != 2 or out.stride(1) != 1 or out.dtype != f32 or not out.is_cuda:
         raise ValueError("out must be a 2-D row-major float32 device tensor")
     st = lib().tt_tli_proposal(n, v_d, v_t, _ptr(d2t, i32, "d2t"), _ptr(t2d, i32, "t2d"),
-                               ctypes.c_void_p(draft_probs.data_ptr()), int(draft_probs.stride(0)),
-                               ctypes.c_void_p(out.data_ptr()), int(out.stride(0)), _stream_handle(stream))
+                               draft_probs.data_ptr(), int(draft_probs.stride(0)),
+                               out.data_ptr(), int(out.stride(0)), _stream_handle(stream))
     _check(st, "tt_tli_proposal")
     return out
 
@@ -472,7 +452,6 @@ def verify_tli(d2t, t2d, target_ids, target_off, draft_probs, target_probs, u_ac
     draft rows [sum M, >= V_d] float32 (row target_off[b] + j for position j) against target rows
     [rows, >= V_t]; draft_mass optional float32 [sum M], the drafter's S_j.  Returns
     (n_accepted, out_token)."""
-    torch = _torch()
     i32, f32 = torch.int32, torch.float32
     v_d = int(d2t.numel()) if v_d is None else int(v_d)
     v_t = int(t2d.numel())
@@ -487,9 +466,9 @@ def verify_tli(d2t, t2d, target_ids, target_off, draft_probs, target_probs, u_ac
     ids = target_ids if target_ids.numel() else torch.zeros(1, dtype=i32, device=dev)
     ua = u_accept if u_accept.numel() else torch.zeros(1, dtype=f32, device=dev)
     st = lib().tt_verify_tli(n, v_d, v_t, _ptr(d2t, i32, "d2t"), _ptr(t2d, i32, "t2d"), _ptr(ids, i32, "target_ids"),
-                             _ptr(target_off, i32, "target_off"), ctypes.c_void_p(draft_probs.data_ptr()),
+                             _ptr(target_off, i32, "target_off"), draft_probs.data_ptr(),
                              int(draft_probs.stride(0)), _ptr(draft_mass, f32, "draft_mass", allow_none=True),
-                             ctypes.c_void_p(target_probs.data_ptr()), int(target_probs.stride(0)),
+                             target_probs.data_ptr(), int(target_probs.stride(0)),
                              _ptr(ua, f32, "u_accept"), _ptr(u_sample, f32, "u_sample"), int(max_m),
                              _ptr(nacc, i32, "n_accepted"), _ptr(tok, i32, "out_token"), _stream_handle(stream))
     _check(st, "tt_verify_tli")
@@ -499,7 +478,6 @@ def verify_tli(d2t, t2d, target_ids, target_off, draft_probs, target_probs, u_ac
 def step_workspace(n_streams: int, v_t: int, max_k: int, max_m: int, w: int, max_token_bytes: int,
                    device="cuda"):
     """A workspace for tt_step (reusable by calls that do not overlap in time)."""
-    torch = _torch()
     n = ctypes.c_size_t(0)
     _check(lib().tt_step_workspace_size(int(n_streams), int(v_t), int(max_k), int(max_m), int(w),
                                         int(max_token_bytes), ctypes.byref(n)), "tt_step_workspace_size")
@@ -511,7 +489,6 @@ def step(vd: Vocab, vt: Vocab, v_d: int, v_t: int, draft_ids, draft_off, target_
          workspace=None, residual: bool = False, out=None, stream=None):
     """tt_step (align + transfer + verify).  Returns
     (cost, path_len, path, map, q, n_accepted, out_token, residual or None)."""
-    torch = _torch()
     i32, f32 = torch.int32, torch.float32
     n = int(draft_off.numel()) - 1
     dev = draft_off.device
@@ -537,12 +514,12 @@ def step(vd: Vocab, vt: Vocab, v_d: int, v_t: int, draft_ids, draft_off, target_
                        _ptr(di, i32, "draft_ids"), _ptr(draft_off, i32, "draft_off"),
                        _ptr(ti, i32, "target_ids"), _ptr(target_off, i32, "target_off"),
                        int(max_k), int(max_m), int(w),
-                       ctypes.c_void_p(draft_probs.data_ptr()), int(draft_probs.stride(0)),
-                       ctypes.c_void_p(target_probs.data_ptr()), int(target_probs.stride(0)),
+                       draft_probs.data_ptr(), int(draft_probs.stride(0)),
+                       target_probs.data_ptr(), int(target_probs.stride(0)),
                        _ptr(ua, f32, "u_accept"), _ptr(u_sample, f32, "u_sample"),
                        _ptr(cost, i32, "cost"), _ptr(plen, i32, "path_len"), _ptr(path, i32, "path"),
                        _ptr(mp, i32, "map"), _ptr(q, f32, "q"), _ptr(nacc, i32, "n_accepted"),
                        _ptr(tok, i32, "out_token"), _ptr(res, f32, "residual", allow_none=True),
-                       ctypes.c_void_p(workspace.data_ptr()), int(workspace.numel()), _stream_handle(stream))
+                       workspace.data_ptr(), int(workspace.numel()), _stream_handle(stream))
     _check(st, "tt_step")
     return out
