@@ -21,7 +21,10 @@
 //   * Token distance: per-byte match masks of a packed token come from SWAR byte
 //     comparison.  When every draft token of a wave's cells has at most two bytes (nearly
 //     always for natural-language tokens), a closed form over the target token's match
-//     masks for those bytes gives the distance; otherwise the bit-parallel edit-distance
+//     masks for those bytes gives the distance, within one word when the target tokens have
+//     at most four (1,024 pairs of 64-512 tokens: 193 us, 209 with masks gathered from two
+//     words); long draft tokens against target tokens of one or two bytes take the same form
+//     with the roles changed; otherwise the bit-parallel edit-distance
 //     recurrence (Myers 1999, in Hyyro's 2001 global-distance form) runs with the longer
 //     token as the pattern (one bit per byte, at most 64) and the shorter one as the text.
 //     Each thread loads the target tokens of its four cells together before computing.
@@ -39,8 +42,8 @@
 //
 // LDS layout (bytes, each region 16-byte aligned):
 //   tslot [max_m + 8][TB + 4] / tlen [max_m + 8]  target token bytes and lengths: 4 empty
-//                                      slots on each side, a pad dword per slot when the plan fits
-//                                      that way
+//                                      slots on each side, a dword more per slot (the token's
+//                                      record) when the plan fits that way
 //   dslot [max_k][TB] / dlen [max_k]   draft token bytes and lengths
 //   row0, row1 [64 + max_m + 136] int32 C of the row above the strip / of the strip's last
 //                                      row, by column with a 64-entry front pad
@@ -195,6 +198,31 @@ __device__ __forceinline__ uint32_t closed_distance(const uint32_t (&yw)[TB / 4]
     return (xm == 0 || yn == 0) ? (uint32_t)(xm + yn) : (xm == 1 ? d1 : d2);
 }
 
+// The record a target token keeps in its slot's pad dword: its length in bits 0-6 and bit 7 of every
+// one of its first four bytes.
+__device__ __forceinline__ uint32_t token_record(int len) {
+    return (uint32_t)len | (0x80808080u & low_mask(8 * len < 32 ? 8 * len : 32));
+}
+
+// closed_distance for a target token of one to four bytes (y, its record rec), about 30 VALU
+// instructions: the match masks stay where the SWAR test leaves them, bit 7 of every byte, so one
+// word holds them and nothing is gathered.  The draft token's constants: m1 = its first byte exists,
+// m2 = its second does (0x80808080 or 0), sh = 8 with two bytes, else 0.  With them the two-byte form
+// covers the others: with one byte E2 is empty and E1 counts at the last position too (yn - [E1 != 0]),
+// with none both are (yn); yn = 1 adds the byte that the form deletes, unless it matched.
+__device__ __forceinline__ uint32_t closed_word(uint32_t y, uint32_t rec, uint32_t bc1, uint32_t bc2, uint32_t m1,
+                                                uint32_t m2, uint32_t sh) {
+    const uint32_t yn = rec & 0x7Fu;
+    const uint32_t t1 = y ^ bc1, t2 = y ^ bc2;
+    const uint32_t e1 = ~(((t1 & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | t1) & (rec & m1);
+    const uint32_t e2 = ~(((t2 & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | t2) & (rec & m2);
+    const uint32_t low1 = e1 & (0u - e1);
+    const bool in_order = (e2 & ~((low1 << 1) - 1u)) != 0;
+    const bool one = ((e1 & ((rec & 0x80808080u) >> sh)) | (e2 & 0xFFFFFF00u)) != 0;
+    const uint32_t extra = yn == 1u && sh != 0u && (e1 | e2) == 0u ? 1u : 0u;
+    return yn - 2u + (in_order ? 0u : (one ? 1u : 2u)) + extra;
+}
+
 // The same distance by Myers' recurrence with D(0, j) = j over the text's bytes, read at the
 // end from the vertical deltas; the loop leaves once no lane of the wave has bytes left.
 template <int TB>
@@ -227,9 +255,9 @@ __device__ __forceinline__ uint32_t myers_distance(const uint32_t (&pw)[TB / 4],
 // load their target tokens together (columns clamped into [1, M], results masked) and take
 // the closed form with the draft token as the text unless some lane of the wave has a draft
 // token of more than two bytes.
-template <int TB>
+template <int TB, int TS>
 __device__ __forceinline__ void chunk_costs(const Band &g, const Strip &st, int T0, uint32_t *buf,
-                                            const uint32_t *tslot, int ts, const uint8_t *tlen, const uint32_t *dslot,
+                                            const uint32_t *tslot, const uint8_t *tlen, const uint32_t *dslot,
                                             const uint8_t *dlen, int h, int nh) {
     for (int item = h; item < st.R * kGroups; item += nh) {
         const int r = item / kGroups, gq = item % kGroups;
@@ -245,39 +273,70 @@ __device__ __forceinline__ void chunk_costs(const Band &g, const Strip &st, int 
                 const bool closed = !__any(xm > 2);  // uniform: the wave's draft tokens have at most two bytes
                 const uint32_t bc1 = __builtin_amdgcn_perm(0u, xw[0], 0u);
                 const uint32_t bc2 = __builtin_amdgcn_perm(0u, xw[0], 0x01010101u);
-                constexpr int kBatch = TB <= 8 ? 4 : 1;  // target slots loaded together (within 64 VGPRs)
-                uint32_t d[4];
+                const uint32_t *tp = tslot + (jb - 1 + kTPad) * TS;  // jb - 1 + kTPad >= 0: the item meets the band
+                packed = 0;
+                bool done = false;
+                if constexpr (TS > TB / 4) {
+                    uint32_t yw[4], rec[4];
+                    bool words = true, texts = true;  // every target token of one to four (two) bytes
 #pragma unroll
-                for (int u0 = 0; u0 < 4; u0 += kBatch) {
-                    uint32_t yw[kBatch][TB / 4];
-                    int yn[kBatch];
-#pragma unroll
-                    for (int v = 0; v < kBatch; ++v) {  // jb - 1 + kTPad >= 0: the item meets the band
-                        const int sl = jb + u0 + v - 1 + kTPad;
-                        read_slot<TB>(tslot + sl * ts, yw[v]);
-                        yn[v] = tlen[sl];
+                    for (int u = 0; u < 4; ++u) {
+                        yw[u] = tp[u * TS];
+                        rec[u] = tp[u * TS + TB / 4];
+                        const uint32_t n1 = (rec[u] & 0x7Fu) - 1u;
+                        words = words && n1 < 4u;
+                        texts = texts && n1 < 2u;
                     }
+                    if (closed && __all(words)) {
+                        done = true;
+                        const uint32_t m1 = xm >= 1 ? 0x80808080u : 0u, m2 = xm == 2 ? 0x80808080u : 0u;
+                        const uint32_t sh = xm == 2 ? 8u : 0u;
 #pragma unroll
-                    for (int v = 0; v < kBatch; ++v) {
-                        if (closed) {
-                            d[u0 + v] = closed_distance<TB>(yw[v], yn[v], low_mask(yn[v]), bc1, bc2, xm);
-                        } else {
-                            const bool swap = yn[v] > xm;
-                            uint32_t pw[TB / 4], tw[TB / 4];
+                        for (int u = 0; u < 4; ++u) packed |= closed_word(yw[u], rec[u], bc1, bc2, m1, m2, sh) << (8 * u);
+                    } else if (TB > 8 && !closed && __all(texts && xm >= 1)) {
+                        // long draft tokens against target tokens of one or two bytes: the same form with
+                        // the target token as the text
+                        done = true;
+                        const uint32_t lim = low_mask(xm);
 #pragma unroll
-                            for (int q = 0; q < TB / 4; ++q) {
-                                pw[q] = swap ? yw[v][q] : xw[q];
-                                tw[q] = swap ? xw[q] : yw[v][q];
+                        for (int u = 0; u < 4; ++u)
+                            packed |= closed_distance<TB>(xw, xm, lim, __builtin_amdgcn_perm(0u, yw[u], 0u),
+                                                          __builtin_amdgcn_perm(0u, yw[u], 0x01010101u), (int)(rec[u] & 0x7Fu))
+                                      << (8 * u);
+                    }
+                }
+                if (!done) {
+                    constexpr int kBatch = TB <= 8 ? 4 : 1;  // target slots loaded together (within 64 VGPRs)
+#pragma unroll
+                    for (int u0 = 0; u0 < 4; u0 += kBatch) {
+                        uint32_t yw[kBatch][TB / 4];
+                        int yn[kBatch];
+#pragma unroll
+                        for (int v = 0; v < kBatch; ++v) {
+                            read_slot<TB>(tp + (u0 + v) * TS, yw[v]);
+                            yn[v] = tlen[jb + u0 + v - 1 + kTPad];
+                        }
+#pragma unroll
+                        for (int v = 0; v < kBatch; ++v) {
+                            if (closed) {
+                                packed |= closed_distance<TB>(yw[v], yn[v], low_mask(yn[v]), bc1, bc2, xm) << (8 * (u0 + v));
+                            } else {
+                                const bool swap = yn[v] > xm;
+                                uint32_t pw[TB / 4], tw[TB / 4];
+#pragma unroll
+                                for (int q = 0; q < TB / 4; ++q) {
+                                    pw[q] = swap ? yw[v][q] : xw[q];
+                                    tw[q] = swap ? xw[q] : yw[v][q];
+                                }
+                                packed |= myers_distance<TB>(pw, tw, swap ? xm : yn[v], low_mask(swap ? yn[v] : xm)) << (8 * (u0 + v));
                             }
-                            d[u0 + v] = myers_distance<TB>(pw, tw, swap ? xm : yn[v], low_mask(swap ? yn[v] : xm));
                         }
                     }
                 }
-                packed = 0;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int j = jb + u;
-                    packed |= ((j >= jl && j <= jh) ? d[u] : 0x80u) << (8 * u);
+                if (jb < jl || jb + 3 > jh) {  // cells outside the band
+                    uint32_t out = jb < jl ? (1u << (8 * (jl - jb))) - 1u : 0u;  // jl - jb, jb + 3 - jh <= 3
+                    if (jb + 3 > jh) out |= ~(~0u >> (8 * (jb + 3 - jh)));
+                    packed = (packed & ~out) | (kOutOfBand & out);
                 }
             } else {
 #pragma unroll 1
@@ -285,7 +344,7 @@ __device__ __forceinline__ void chunk_costs(const Band &g, const Strip &st, int 
                     const int j = jb + u;
                     if (j >= jl && j <= jh) {
                         uint32_t yw[TB / 4];
-                        read_slot<TB>(tslot + (j - 1 + kTPad) * ts, yw);
+                        read_slot<TB>(tslot + (j - 1 + kTPad) * TS, yw);
                         const uint32_t d = (uint32_t)token_distance<TB>(xw, xm, yw, tlen[j - 1 + kTPad]);
                         packed = (packed & ~(0xFFu << (8 * u))) | (d << (8 * u));
                     }
@@ -388,9 +447,10 @@ dtw_band(AlignArgs a, LdsPlan lp, uint32_t *gcodes, size_t gcode_stride,
     int bad = shape_ok ? 0 : 1;
     if (shape_ok) {
         for (int e = tid; e < K + M; e += kThreads) {
+            uint32_t *slot = tslot + (e - K + kTPad) * ts;
             const bool ok = e < K ? stage_token<TB>(a.vd, a.draft_ids[d0 + e], dslot + e * (TB / 4), dlen + e)
-                                  : stage_token<TB>(a.vt, a.target_ids[t0 + e - K], tslot + (e - K + kTPad) * ts,
-                                                    tlen + (e - K + kTPad));
+                                  : stage_token<TB>(a.vt, a.target_ids[t0 + e - K], slot, tlen + (e - K + kTPad));
+            if (TS > TB / 4 && e >= K && ok) slot[TB / 4] = token_record(tlen[e - K + kTPad]);
             bad |= ok ? 0 : 1;
         }
         // the empty slots around the target tokens (read by items that straddle the band's ends)
@@ -429,7 +489,7 @@ dtw_band(AlignArgs a, LdsPlan lp, uint32_t *gcodes, size_t gcode_stride,
         }
     }
     Strip st = strip_at(g, 0);
-    chunk_costs<TB>(g, st, 0, costbuf, tslot, ts, tlen, dslot, dlen, tid, kThreads);
+    chunk_costs<TB, TS>(g, st, 0, costbuf, tslot, tlen, dslot, dlen, tid, kThreads);
     __syncthreads();
     // the sweep is the critical path: its wave wins issue arbitration on its SIMD
     if (wave == 0) __builtin_amdgcn_s_setprio(3);
@@ -454,9 +514,9 @@ dtw_band(AlignArgs a, LdsPlan lp, uint32_t *gcodes, size_t gcode_stride,
             if (wave == 0) {
                 sweep_chunk(sw, cur_buf, rowIn, rowOut, c * kChunk, st.jfirst, rw);
             } else if (c + 1 < st.nchunks) {
-                chunk_costs<TB>(g, st, (c + 1) * kChunk, next_buf, tslot, ts, tlen, dslot, dlen, tid - kWave, kHelpers);
+                chunk_costs<TB, TS>(g, st, (c + 1) * kChunk, next_buf, tslot, tlen, dslot, dlen, tid - kWave, kHelpers);
             } else if (s + 1 < nstrips) {
-                chunk_costs<TB>(g, nxt, 0, next_buf, tslot, ts, tlen, dslot, dlen, tid - kWave, kHelpers);
+                chunk_costs<TB, TS>(g, nxt, 0, next_buf, tslot, tlen, dslot, dlen, tid - kWave, kHelpers);
             }
             __syncthreads();
             ++gidx;

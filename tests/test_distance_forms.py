@@ -75,6 +75,37 @@ def closed(draft: bytes, target: bytes) -> int:
     return xm + yn if (xm == 0 or yn == 0) else (d1 if xm == 1 else d2)
 
 
+def closed_word(draft, target):
+    """The one-word form for target tokens of one to four bytes, as the strip kernel evaluates it: match flags at
+    bit 7 of every byte, the target's record (length, and bit 7 of its bytes) in one word."""
+    W = 0xFFFFFFFF
+    xm, yn = len(draft), len(target)
+    y = int.from_bytes(target.ljust(4, b"\0"), "little")
+    rec = yn | (0x80808080 & ((1 << (8 * yn)) - 1))
+
+    def flags(k, m):
+        t = y ^ ((draft[k] if k < xm else 0) * 0x01010101)
+        return ~((((t & 0x7F7F7F7F) + 0x7F7F7F7F) & W) | t) & rec & m & W
+
+    m1, m2, sh = 0x80808080 * (xm >= 1), 0x80808080 * (xm == 2), 8 * (xm == 2)
+    e1, e2 = flags(0, m1), flags(1, m2)
+    low1 = e1 & (-e1 & W)
+    in_order = (e2 & ~(((low1 << 1) - 1) & W)) != 0
+    one = ((e1 & ((rec & 0x80808080) >> sh)) | (e2 & 0xFFFFFF00)) != 0
+    extra = 1 if yn == 1 and sh and not e1 | e2 else 0
+    return ((rec & 0x7F) - 2 + (0 if in_order else (1 if one else 2)) + extra) & W
+
+
+def test_closed_word_every_short_pair(orc):
+    """Every draft string of 0-2 bytes against every target string of 1-4 bytes over four symbols."""
+    alphabet = [0x00, 0x7F, 0x80, 0xFF]
+    for lx in range(3):
+        for x in itertools.product(alphabet, repeat=lx):
+            for ly in range(1, 5):
+                for y in itertools.product(alphabet, repeat=ly):
+                    assert closed_word(bytes(x), bytes(y)) == orc.levenshtein(bytes(x), bytes(y)), (x, y)
+
+
 def test_closed_form_every_short_pair(orc):
     """Every draft string of 0-2 bytes against every target string of 0-6 bytes over three
     symbols, one of them NUL (the padding byte of a packed slot)."""
