@@ -301,3 +301,44 @@ def verify_case(n, V, dense):
     assert np.array_equal(nacc.cpu().numpy(), o_nacc)
     assert np.array_equal(tok.cpu().numpy(), o_tok)
     assert 0 < (o_nacc < Ms).sum() or n < 8
+
+
+@pytest.mark.parametrize("maxlen,n", [(8, 5), (8, 257), (16, 5), (16, 256), (16, 257)])
+def test_distance_forms_of_the_strip_kernel(maxlen, n):
+    """Every form of the token distance (short drafts, short targets, neither), mixed and alone, empty tokens among
+    them, in strips of one chunk (M = 1) and of several, with and without the match tables and the ranking."""
+    rng = np.random.default_rng(100 * maxlen + n)
+    alphabet = b"ab\x00\xff"
+    kinds = [random_tokens(rng, 10, 1, 2, alphabet), random_tokens(rng, 40, 3, 4, alphabet),
+             random_tokens(rng, 60, 5, maxlen, alphabet)]
+    toks = [b""] + [t for k in kinds for t in k]
+    first = np.cumsum([0, 1] + [len(k) for k in kinds])  # ids of the empty token and of each kind
+    v = vocab_of(toks)
+    choose = {"empty": (0, 1), "short": (1, 2), "four": (1, 3), "long": (3, 4), "any": (0, 4)}
+
+    def ids(kind, count):
+        a, b = choose[kind]
+        return list(rng.integers(first[a], first[b], count))
+
+    mixes = [("short", "four"), ("short", "any"), ("long", "short"), ("long", "four"), ("any", "short"), ("any", "any"),
+             ("long", "long"), ("empty", "short"), ("short", "empty")]
+    sizes = [(130, 40), (65, 1), (70, 150), (3, 80), (64, 64), (129, 2)]
+    pairs = [(ids(mixes[p % len(mixes)][0], sizes[p // 2 % len(sizes)][0]), ids(mixes[p % len(mixes)][1], sizes[p // 2 % len(sizes)][1]))
+             for p in range(n)]
+    wl = workload(v, v, pairs, len(toks), len(toks), probs=False)
+    for w in (8, -1):
+        compare_align(wl, gpu_run(wl, w=w), oracle_run(wl, w=w))
+
+
+@pytest.mark.parametrize("n_bins", [1, 3, 255, 256, 257, 1024, 8191, 8192])
+def test_delta_quantile_sizes(n_bins):
+    """One bin to the most, against the definition in Python integers."""
+    import paper_2510_15545_amd as tt
+
+    rng = np.random.default_rng(n_bins)
+    for h in (rng.integers(0, 2 ** 31 - 1, n_bins), rng.integers(0, 2, n_bins), np.eye(1, n_bins, n_bins - 1)[0], np.zeros(n_bins)):
+        h = h.astype(np.int32)
+        cum = np.cumsum(h.astype(np.int64))
+        for num, den in ((9, 10), (0, 1), (1, 1), (65535, 65536)):
+            want = 0 if cum[-1] == 0 else next(d for d in range(n_bins) if int(cum[d]) * den >= num * int(cum[-1]))
+            assert tt.w_at_quantile(to_dev(h), num, den) == want, (n_bins, num, den)
