@@ -76,8 +76,8 @@ constexpr int band_threads() {
     return TB <= 16 ? 512 : 256;
 }
 constexpr int kChunk = 64;                       // sweep steps per cost chunk
-constexpr int kOrderThreads = 256;               // dispatch-order ranks: threads per workgroup
-constexpr int kOrderSplit = 4;                   // lanes counting one pair's rank
+constexpr int kOrderThreads = 1024;              // dispatch-order ranks: threads per workgroup
+constexpr int kOrderSplit = 16;                  // lanes counting one pair's rank
 constexpr int kOrderPairsPerGroup = kOrderThreads / kOrderSplit;
 constexpr int kOrderMax = 2048;                  // pairs it orders (11-bit index in the key); more keep their order
 constexpr int kGroups = kChunk / 4;              // cost dwords per lane and chunk
@@ -92,6 +92,7 @@ __host__ __device__ inline size_t align16(size_t v) { return (v + 15) & ~size_t(
 
 struct LdsPlan {
     size_t tslot, tlen, dslot, dlen, row0, row1, cost, path, total;
+    size_t eq;  // match tables (0: none)
     int tstride;  // dwords per target token slot
 };
 
@@ -140,12 +141,38 @@ __host__ __device__ inline LdsPlan plan_lds_with(int32_t max_k, int32_t max_m, i
     p.path = off;
     off = align16(off + 8 * (size_t)max_k);
     p.total = off;
+    p.eq = 0;
     return p;
 }
 
 __host__ __device__ inline LdsPlan plan_lds(int32_t max_k, int32_t max_m, int32_t w, int tb) {
     const LdsPlan wide = plan_lds_with(max_k, max_m, w, tb, tb / 4 + 1);
     return wide.total <= kLdsLimit ? wide : plan_lds_with(max_k, max_m, w, tb, tb / 4);
+}
+
+// Match tables of a strip's draft tokens (16-byte slots): entry [r][c] has bit k set where byte k of
+// row r's token is c.  At 16 bytes a mask gathered from the token costs about 26 VALU instructions and
+// a distance needs two or more; a table turns each into one LDS read.  Two strips' tables take
+// 64 KB, so only batches that leave every pair a compute unit of its own have them: 96 pairs of
+// 16-128 tokens (up to 16 bytes) without a band take 144 us (193 with masks gathered and a ranking kernel).
+constexpr int kEqBytes = 2 * kWave * 256 * 2;
+constexpr int kCus = 256;
+
+// The table of strip st, one wave per row in turn (hw of nhw).
+__device__ __forceinline__ void build_eq(int i0, int R, uint32_t *eq, const uint32_t *dslot, const uint8_t *dlen, int tb,
+                                         int hw, int nhw) {
+    const int lane = threadIdx.x % kWave;
+    for (int r = hw; r < R; r += nhw) {
+        uint32_t *t = eq + r * 128;
+        t[lane] = 0u;
+        t[lane + kWave] = 0u;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const int i = i0 + r - 1;
+        if (lane < dlen[i]) {
+            const uint32_t c = reinterpret_cast<const uint8_t *>(dslot)[i * tb + lane];
+            atomicOr(&t[c >> 1], 1u << (lane + 16 * (c & 1u)));
+        }
+    }
 }
 
 struct Band {
@@ -247,6 +274,40 @@ __device__ __forceinline__ uint32_t myers_distance(const uint32_t (&pw)[TB / 4],
     return (uint32_t)(tn + __popc(vp & lim) - __popc(vn & lim));
 }
 
+// closed_distance with the target token (one or two bytes, y and its record) as the text and the draft
+// token (xm >= 1 bytes, its table row eq) as the pattern.
+__device__ __forceinline__ uint32_t closed_table(const uint16_t *eq, uint32_t y, uint32_t rec, int xm, uint32_t lim) {
+    const bool two = (rec & 0x7Fu) == 2u;
+    const uint32_t e1 = eq[y & 0xFFu];
+    const uint32_t e2 = two ? (uint32_t)eq[(y >> 8) & 0xFFu] : 0u;
+    const uint32_t low1 = e1 & (0u - e1);
+    const bool in_order = (e2 & ~((low1 << 1) - 1u)) != 0;
+    const bool one = ((e1 & (two ? lim >> 1 : lim)) | (e2 & ~1u)) != 0;  // (one byte counts at the last position too)
+    const uint32_t extra = xm == 1 && two && (e1 | e2) == 0u ? 1u : 0u;
+    return (uint32_t)xm - 2u + (in_order ? 0u : (one ? 1u : 2u)) + extra;
+}
+
+// myers_distance with the draft token (its table row eq, its bits lim) as the pattern.
+template <int TB>
+__device__ __forceinline__ uint32_t myers_table(const uint16_t *eq, const uint32_t (&tw)[TB / 4], int tn, uint32_t lim) {
+    uint32_t vp = 0xFFFFFFFFu, vn = 0;
+#pragma unroll
+    for (int k = 0; k < TB; ++k) {
+        const bool act = k < tn;
+        if (!__any(act)) break;
+        const uint32_t e = eq[(tw[k >> 2] >> (8 * (k & 3))) & 0xFFu];
+        const uint32_t xv = e | vn;
+        const uint32_t xh = (((e & vp) + vp) ^ vp) | e;
+        const uint32_t hp = ((vn | ~(xh | vp)) << 1) | 1u;
+        const uint32_t hn = (vp & xh) << 1;
+        const uint32_t nvp = hn | ~(xv | hp);
+        const uint32_t nvn = hp & xv;
+        vp = act ? nvp : vp;
+        vn = act ? nvn : vn;
+    }
+    return (uint32_t)(tn + __popc(vp & lim) - __popc(vn & lim));
+}
+
 // Token distances of chunk T0 / 64 of strip st: cell (i0 + r, jfirst + t - r) for
 // t in [T0, T0 + 64) goes to byte t & 3 of dword buf[r][(t - T0) / 4]; out-of-band
 // cells get 0x80.  Threads h, h + nh, ... each take four consecutive steps of one row, and
@@ -255,8 +316,8 @@ __device__ __forceinline__ uint32_t myers_distance(const uint32_t (&pw)[TB / 4],
 // load their target tokens together (columns clamped into [1, M], results masked) and take
 // the closed form with the draft token as the text unless some lane of the wave has a draft
 // token of more than two bytes.
-template <int TB, int TS>
-__device__ __forceinline__ void chunk_costs(const Band &g, const Strip &st, int T0, uint32_t *buf,
+template <int TB, int TS, bool EQ>
+__device__ __forceinline__ void chunk_costs(const Band &g, const Strip &st, int T0, uint32_t *buf, const uint16_t *eq,
                                             const uint32_t *tslot, const uint8_t *tlen, const uint32_t *dslot,
                                             const uint8_t *dlen, int h, int nh) {
     for (int item = h; item < st.R * kGroups; item += nh) {
@@ -298,11 +359,17 @@ __device__ __forceinline__ void chunk_costs(const Band &g, const Strip &st, int 
                         // the target token as the text
                         done = true;
                         const uint32_t lim = low_mask(xm);
+                        if constexpr (EQ) {
+#pragma unroll
+                            for (int u = 0; u < 4; ++u)
+                                packed |= closed_table(eq + r * 256, yw[u], rec[u], xm, lim) << (8 * u);
+                        } else {
 #pragma unroll
                         for (int u = 0; u < 4; ++u)
                             packed |= closed_distance<TB>(xw, xm, lim, __builtin_amdgcn_perm(0u, yw[u], 0u),
                                                           __builtin_amdgcn_perm(0u, yw[u], 0x01010101u), (int)(rec[u] & 0x7Fu))
                                       << (8 * u);
+                        }
                     }
                 }
                 if (!done) {
@@ -318,7 +385,9 @@ __device__ __forceinline__ void chunk_costs(const Band &g, const Strip &st, int 
                         }
 #pragma unroll
                         for (int v = 0; v < kBatch; ++v) {
-                            if (closed) {
+                            if (EQ && !closed) {
+                                packed |= myers_table<TB>(eq + r * 256, yw[v], yn[v], low_mask(xm)) << (8 * (u0 + v));
+                            } else if (closed) {
                                 packed |= closed_distance<TB>(yw[v], yn[v], low_mask(yn[v]), bc1, bc2, xm) << (8 * (u0 + v));
                             } else {
                                 const bool swap = yn[v] > xm;
@@ -416,8 +485,8 @@ __device__ __forceinline__ void sweep_chunk(Sweep &sw, const uint32_t *buf, cons
     }
 }
 
-template <int TB, int TS>
-__global__ void __launch_bounds__(band_threads<TB>()) __attribute__((amdgpu_waves_per_eu(band_threads<TB>() / 64)))
+template <int TB, int TS, bool EQ>
+__global__ void __launch_bounds__(band_threads<TB>()) __attribute__((amdgpu_waves_per_eu(EQ ? 2 : band_threads<TB>() / 64)))
 dtw_band(AlignArgs a, LdsPlan lp, uint32_t *gcodes, size_t gcode_stride,
                                                      int rw, const int32_t *order) {
     constexpr int kThreads = band_threads<TB>();
@@ -489,7 +558,14 @@ dtw_band(AlignArgs a, LdsPlan lp, uint32_t *gcodes, size_t gcode_stride,
         }
     }
     Strip st = strip_at(g, 0);
-    chunk_costs<TB, TS>(g, st, 0, costbuf, tslot, tlen, dslot, dlen, tid, kThreads);
+    uint32_t *eqtab = reinterpret_cast<uint32_t *>(lds + lp.eq);  // EQ: the tables of strip s in half s & 1
+    auto eq_of = [&](int s) { return eqtab + (s & 1) * kWave * 128; };
+    auto eq16 = [&](int s) { return reinterpret_cast<const uint16_t *>(eq_of(s)); };
+    if (EQ) {
+        build_eq(st.i0, st.R, eq_of(0), dslot, dlen, TB, wave, kThreads / kWave);
+        __syncthreads();
+    }
+    chunk_costs<TB, TS, EQ>(g, st, 0, costbuf, eq16(0), tslot, tlen, dslot, dlen, tid, kThreads);
     __syncthreads();
     // the sweep is the critical path: its wave wins issue arbitration on its SIMD
     if (wave == 0) __builtin_amdgcn_s_setprio(3);
@@ -508,15 +584,21 @@ dtw_band(AlignArgs a, LdsPlan lp, uint32_t *gcodes, size_t gcode_stride,
             sw.cw = 0;
         }
         const Strip nxt = (s + 1 < nstrips) ? strip_at(g, s + 1) : st;
+        if (EQ && st.nchunks == 1 && s + 1 < nstrips) {  // the next strip's distances start with this chunk
+            if (wave != 0) build_eq(nxt.i0, nxt.R, eq_of(s + 1), dslot, dlen, TB, wave - 1, kThreads / kWave - 1);
+            __syncthreads();
+        }
         for (int c = 0; c < st.nchunks; ++c) {
             uint32_t *cur_buf = costbuf + (gidx & 1) * kWave * kCostStride;
             uint32_t *next_buf = costbuf + ((gidx + 1) & 1) * kWave * kCostStride;
             if (wave == 0) {
                 sweep_chunk(sw, cur_buf, rowIn, rowOut, c * kChunk, st.jfirst, rw);
             } else if (c + 1 < st.nchunks) {
-                chunk_costs<TB, TS>(g, st, (c + 1) * kChunk, next_buf, tslot, tlen, dslot, dlen, tid - kWave, kHelpers);
+                if (EQ && c == 0 && s + 1 < nstrips)  // complete at this chunk's barrier, first read after it
+                    build_eq(nxt.i0, nxt.R, eq_of(s + 1), dslot, dlen, TB, wave - 1, kThreads / kWave - 1);
+                chunk_costs<TB, TS, EQ>(g, st, (c + 1) * kChunk, next_buf, eq16(s), tslot, tlen, dslot, dlen, tid - kWave, kHelpers);
             } else if (s + 1 < nstrips) {
-                chunk_costs<TB, TS>(g, nxt, 0, next_buf, tslot, tlen, dslot, dlen, tid - kWave, kHelpers);
+                chunk_costs<TB, TS, EQ>(g, nxt, 0, next_buf, eq16(s + 1), tslot, tlen, dslot, dlen, tid - kWave, kHelpers);
             }
             __syncthreads();
             ++gidx;
@@ -807,10 +889,11 @@ dtw_band(AlignArgs a, LdsPlan lp, uint32_t *gcodes, size_t gcode_stride,
 // Dispatch order for the strip kernel: pairs by descending band work K * W (in units of 16
 // cells), ties by index.  Workgroups are handed to compute units in launch order, so the
 // longest pairs start first and the short ones fill in around them (on the 1,024 long pairs:
-// 393 us in generator order, about 254 us sorted).  Every 256-thread workgroup builds all n
-// 32-bit keys (work class, index) in LDS and ranks its own 64 pairs: a pair's slot is the number
-// of keys below its own, counted by four lanes over a quarter of the keys each with broadcast
-// LDS reads.
+// 393 us in generator order, about 254 us sorted).  Every workgroup builds all n 32-bit
+// keys (work class, index) in LDS and ranks its own 64 pairs: a pair's slot is the number of keys
+// below its own, counted by 16 lanes that take the keys in turn (with a contiguous part of the
+// keys each, the lanes met on the same banks: 9.4 us for 1,024 pairs, 4.8 so).  Batches that
+// give every pair a compute unit of its own need no order.
 __device__ __forceinline__ uint32_t order_key(const AlignArgs &a, int i) {
     const int K = a.draft_off[i + 1] - a.draft_off[i], M = a.target_off[i + 1] - a.target_off[i];
     uint32_t work = 0;
@@ -829,27 +912,25 @@ __global__ void __launch_bounds__(kOrderThreads) order_pairs(AlignArgs a, int32_
     __shared__ __align__(16) uint32_t keys[kOrderMax];
     const int n = a.n_pairs;
     const int n16 = (n + 15) & ~15;
-    for (int i = threadIdx.x; i < n16; i += kOrderThreads) keys[i] = i < n ? order_key(a, i) : ~0u;  // pad: never below a key
+#pragma unroll
+    for (int u = 0; u < kOrderMax / kOrderThreads; ++u) {  // a thread's loads all in flight
+        const int i = u * kOrderThreads + (int)threadIdx.x;
+        if (i < n16) keys[i] = i < n ? order_key(a, i) : ~0u;  // pad: never below a key
+    }
     __syncthreads();
     const uint4 *k4 = reinterpret_cast<const uint4 *>(keys);
-    // four lanes per pair, each counting a quarter of the keys; partial counts meet by shuffles
+    // kOrderSplit lanes per pair, each counting its part of the keys; partial counts meet by shuffles
     const int i = blockIdx.x * kOrderPairsPerGroup + (int)threadIdx.x / kOrderSplit;
     const int part = threadIdx.x % kOrderSplit;
     const uint32_t mine = i < n ? keys[i] : 0u;
-    const int quads = n16 >> 2;  // a multiple of 4
-    const int per = ((quads / kOrderSplit) + 3) & ~3;
-    const int q0 = part * per;
-    const int q1 = q0 + per < quads ? q0 + per : quads;
+    const int quads = n16 >> 2;
     int r = 0;
-    for (int q = q0; q < q1; q += 4) {  // every lane of a quarter reads the same 16 keys
-        uint4 k[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) k[u] = q + u < q1 ? k4[q + u] : make_uint4(~0u, ~0u, ~0u, ~0u);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) r += (k[u].x < mine) + (k[u].y < mine) + (k[u].z < mine) + (k[u].w < mine);
+#pragma unroll 4
+    for (int q = part; q < quads; q += kOrderSplit) {  // neighbouring lanes, neighbouring keys: no bank conflicts
+        const uint4 k = k4[q];
+        r += (k.x < mine) + (k.y < mine) + (k.z < mine) + (k.w < mine);
     }
-    r += __shfl_xor(r, 1);
-    r += __shfl_xor(r, 2);
+    for (int d = 1; d < kOrderSplit; d <<= 1) r += __shfl_xor(r, d);
     if (i < n && part == 0) order[r] = i;
 }
 
@@ -857,11 +938,16 @@ inline size_t order_offset(size_t code_words) { return (4 * code_words + 255) & 
 
 template <int TB>
 int launch_tb(const AlignArgs &a, void *workspace, size_t workspace_bytes, hipStream_t stream) {
-    const LdsPlan lp = plan_lds(a.max_k, a.max_m, a.w, TB);
+    LdsPlan lp = plan_lds(a.max_k, a.max_m, a.w, TB);
     if (lp.total > kLdsLimit) return TT_EUNSUPPORTED;
+    if (TB == 16 && a.n_pairs <= kCus && lp.tstride == TB / 4 + 1 && lp.total + kEqBytes <= kLdsLimit) {
+        lp.eq = lp.total;
+        lp.total += kEqBytes;
+    }
     const int rw = row_words_bound(a.max_k, a.max_m, a.w);
     const size_t stride = (size_t)a.max_k * (size_t)rw;  // code words per pair
-    const bool sorted = a.n_pairs >= 2 && a.n_pairs <= kOrderMax;
+    // (pairs that all get a compute unit of their own start together in any order)
+    const bool sorted = a.n_pairs > kCus && a.n_pairs <= kOrderMax;
     const size_t need = sorted ? order_offset(stride * (size_t)a.n_pairs) + 4 * (size_t)a.n_pairs
                                : 4 * stride * (size_t)a.n_pairs;
     if (workspace == nullptr || workspace_bytes < need) return TT_EWORKSPACE;
@@ -881,7 +967,9 @@ int launch_tb(const AlignArgs &a, void *workspace, size_t workspace_bytes, hipSt
                            static_cast<uint32_t *>(workspace), stride, rw, order);
         return hipGetLastError() == hipSuccess ? TT_OK : TT_ELAUNCH;
     };
-    return lp.tstride == TB / 4 + 1 ? launch(&dtw_band<TB, TB / 4 + 1>) : launch(&dtw_band<TB, TB / 4>);
+    if constexpr (TB == 16)
+        if (lp.eq != 0) return launch(&dtw_band<TB, TB / 4 + 1, true>);
+    return lp.tstride == TB / 4 + 1 ? launch(&dtw_band<TB, TB / 4 + 1, false>) : launch(&dtw_band<TB, TB / 4, false>);
 }
 
 }  // namespace
