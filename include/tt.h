@@ -445,6 +445,18 @@ int tt_verify_tli(int32_t n_streams, int32_t v_d, int32_t v_t, const int32_t *d2
                   const float *u_sample, int32_t max_m, int32_t *n_accepted, int32_t *out_token, void *stream);
 
 /*
+ * tt_verify_tli_ws is the same call with a workspace of tt_verify_tli_workspace_size bytes (0 where
+ * the one kernel is the better one; no initialisation; calls that overlap in time must not share
+ * it): a stream's row is then spread over workgroups, three kernels on `stream`, with the same
+ * results.  A null workspace is tt_verify_tli; TT_EWORKSPACE when it is too small.
+ */
+int tt_verify_tli_workspace_size(int32_t n_streams, int32_t v_t, size_t *bytes);
+int tt_verify_tli_ws(int32_t n_streams, int32_t v_d, int32_t v_t, const int32_t *d2t, const int32_t *t2d,
+                  const int32_t *target_ids, const int32_t *target_off, const float *draft_probs, int64_t draft_ld,
+                  const float *draft_mass, const float *target_probs, int64_t target_ld, const float *u_accept,
+                  const float *u_sample, int32_t max_m, int32_t *n_accepted, int32_t *out_token, void *workspace, size_t workspace_bytes, void *stream);
+
+/*
  * Workspace bytes tt_step needs: the larger of tt_align_workspace_size and
  * tt_verify_workspace_size for the same arguments (the two stages run one after
  * the other and share it).

@@ -102,6 +102,10 @@ def lib():
         L.tt_tli_proposal.restype = ctypes.c_int
         L.tt_verify_tli.argtypes = [i32, i32, i32, P, P, P, P, P, i64, P, P, i64, P, P, i32, P, P, P]
         L.tt_verify_tli.restype = ctypes.c_int
+        L.tt_verify_tli_workspace_size.argtypes = [i32, i32, ctypes.POINTER(sz)]
+        L.tt_verify_tli_workspace_size.restype = ctypes.c_int
+        L.tt_verify_tli_ws.argtypes = [i32, i32, i32, P, P, P, P, P, i64, P, P, i64, P, P, i32, P, P, P, sz, P]
+        L.tt_verify_tli_ws.restype = ctypes.c_int
         L.tt_step_workspace_size.argtypes = [i32, i32, i32, i32, i32, i32, ctypes.POINTER(sz)]
         L.tt_step_workspace_size.restype = ctypes.c_int
         L.tt_step.argtypes = [VP, VP, i32, i32, i32, P, P, P, P, i32, i32, i32, P, i64, P, i64, P, P,
@@ -465,12 +469,16 @@ def verify_tli(d2t, t2d, target_ids, target_off, draft_probs, target_probs, u_ac
     nacc, tok = out
     ids = target_ids if target_ids.numel() else torch.zeros(1, dtype=i32, device=dev)
     ua = u_accept if u_accept.numel() else torch.zeros(1, dtype=f32, device=dev)
-    st = lib().tt_verify_tli(n, v_d, v_t, _ptr(d2t, i32, "d2t"), _ptr(t2d, i32, "t2d"), _ptr(ids, i32, "target_ids"),
+    nb = ctypes.c_size_t(0)
+    st = lib().tt_verify_tli_workspace_size(n, v_t, ctypes.byref(nb))
+    ws = _scratch(nb.value, dev, stream) if st == TT_OK and nb.value else None
+    st = lib().tt_verify_tli_ws(n, v_d, v_t, _ptr(d2t, i32, "d2t"), _ptr(t2d, i32, "t2d"), _ptr(ids, i32, "target_ids"),
                              _ptr(target_off, i32, "target_off"), draft_probs.data_ptr(),
                              int(draft_probs.stride(0)), _ptr(draft_mass, f32, "draft_mass", allow_none=True),
                              target_probs.data_ptr(), int(target_probs.stride(0)),
                              _ptr(ua, f32, "u_accept"), _ptr(u_sample, f32, "u_sample"), int(max_m),
-                             _ptr(nacc, i32, "n_accepted"), _ptr(tok, i32, "out_token"), _stream_handle(stream))
+                             _ptr(nacc, i32, "n_accepted"), _ptr(tok, i32, "out_token"), None if ws is None else ws.data_ptr(), nb.value,
+                             _stream_handle(stream))
     _check(st, "tt_verify_tli")
     return out
 

@@ -17,8 +17,8 @@
 // the XCD's L2.  A row's slices run together on one XCD (3 to 4 rows of 512 KB in flight there);
 // with one workgroup per row 32 rows (16 MB) were, and nearly every gather went to the Infinity
 // Cache.  1,024 rows of 128,256 -> 151,936 ids with 60% shared: 1,215 us with one workgroup per
-// row, 530 so (tli_fill about 200 G gathers/s).  Rows of small vocabularies keep the one
-// kernel (tli_rows).  The maps are shared by every row and stay in cache.
+// row, 530 so (tli_fill about 200 G gathers/s).  Short rows keep the one kernel
+// (tli_rows).  The maps are shared by every row and stay in cache.
 #include "verify_core.h"
 
 TT_STAMPS_TABLE(tli)
@@ -36,13 +36,25 @@ constexpr int kSlice = 2048;  // target ids of a workgroup of tli_fill
 constexpr int kFillThreads = 256;
 constexpr int kXcds = 8;
 constexpr int kCus = 256;
-// Both vocabularies up to here: one workgroup per row does both passes (tli_rows).  Its rows in
-// flight (one per CU, 32 per XCD) then fit the XCD's 4 MB L2, and one launch beats two: 300 rows of
-// 8,000 -> 12,000 ids 13.3 us against 17.7, of 16,000 -> 20,000 21.7 against 23.9; past it, 300 rows
-// of 32,000 -> 50,257 with 70% shared take 49.6 us in two kernels against 65.8 in one.
-constexpr int kSmallVocab = 16384;
+// When the proposal rows take two kernels.  Few rows: once they are long enough to be worth spreading
+// (16 rows of 78,456 -> 14,532 ids 9.9 us against 15.7 in one kernel, of 128,256 -> 151,936 17.4
+// against 87; of 30,000 -> 4,000 10.6 against 7.9).  Many rows: when the draft rows in flight in one
+// kernel (one per CU, 32 per XCD) overflow the XCD's 4 MB L2 and there are target ids enough to
+// gather for, whatever their share (300 rows of 32,000 -> 50,257: 34.5 us against 36.3 with few shared
+// tokens, 49.6 against 65.8 with 70%; 256 rows of 40,000 -> 22,000: 23.7 against 17.2, 32.8 against
+// 35.3; 256 of 12,000 -> 50,000: 18.8 against 16.0, 23.0 against 20.7).
+constexpr int kFewRows = 64, kFewRowsVocab = 65536;
+constexpr int kManyRowsDraft = 16384, kManyRowsTarget = 32768;
 constexpr int64_t kCacheBytes = int64_t(256) << 20;  // the Infinity Cache
 constexpr int64_t kMaxItems = int64_t(1) << 21;      // workgroups of one grid
+// Verification with the proposal formed on the fly: a row is spread over workgroups from this many
+// chunks on and up to this many streams, more for long rows.  128,256 -> 151,936 ids with the
+// drafter's masses: one stream 11.8 us against 35 to 66 on one compute unit (few to many shared
+// tokens), 32 streams 24-32 against 46-105, 128 streams 44-80 against 50-157, but 256 streams
+// 69 against 64 with few; 32 streams of 50,257 14.4-15.9 against 21.9-31.0, 128 24.6-33.1 against
+// 25.2-36.2 (without masses 37.5 against 35.7); 32 of 12,000 14.1 against 11.1.
+constexpr int kTliSplitChunks = 32, kTliLongChunks = 128;
+constexpr int kTliSplitStreams = 64, kTliLongStreams = 128;
 constexpr int kMaxSplits = 16;  // workgroups a row's mass is split over at most
 
 struct U128 {
@@ -138,7 +150,7 @@ __device__ float row_mass(const float *q, const int32_t *d2t, int v_d, U128 *sh_
 // outside [0, v_d): the entry is 0 either way); 0 when S is not positive.
 __device__ __forceinline__ float qprime(float g, float S) { return S > 0.0f ? clamp01(g) / S : 0.0f; }
 
-// Small vocabularies: one 1024-thread workgroup per row, the mass and then the row.
+// Short rows: one 1024-thread workgroup per row, the mass and then the row.
 __global__ void __launch_bounds__(kThreads) tli_rows(TliArgs a) {
     const int r = blockIdx.x;
     const int tid = threadIdx.x;
@@ -280,9 +292,16 @@ __global__ void __launch_bounds__(kFillThreads) tli_fill(TliArgs a, int row0, in
 //     for element.
 constexpr int kWaves = kThreads / kWave;
 
+struct TliRec {
+    int r;    // gamma (-1: a sentinel stream)
+    float S;  // the rejected row's mass
+};
+
 struct TliVerifyParams {
     TliVerifyArgs a;
-    int32_t nc;
+    int32_t nc, splits, cps;  // chunks of a row, workgroups per stream, chunks of one
+    TliRec *rec;              // [n_streams]
+    uint64_t *sums;           // [n_streams][nc] Q62 chunk sums
 };
 
 // The 16 draft ids t2d of a lane's elements x0 .. x0+15 (x0 = c*1024 + lane*16; -1 past v_t).
@@ -366,6 +385,103 @@ __device__ __forceinline__ uint64_t residual_sum_strided(const float4 (&pv)[4], 
     return sum;
 }
 
+// Whether every proposal's id lies inside the target vocabulary (one wave).
+__device__ __forceinline__ bool ids_ok(const TliVerifyArgs &a, int t0, int M, int lane) {
+    bool ok = true;
+    for (int base = 0; ok && base < M; base += kWave) {
+        const int j = base + lane;
+        ok = !__any(j < M && (a.target_ids[t0 + j] < 0 || a.target_ids[t0 + j] >= a.v_t));
+    }
+    return ok;
+}
+
+// gamma and S_gamma with the drafter's masses (one wave, 64 positions a ballot).
+__device__ __forceinline__ void mass_scan(const TliVerifyArgs &a, int b, int t0, int M, int lane, int &gamma, float &S_r) {
+    gamma = M;
+    S_r = 0.0f;
+    for (int base = 0; base < M && gamma == M; base += kWave) {
+        const int j = base + lane;
+        bool rej = false;
+        float Sj = 0.0f;
+        if (j < M) {
+            const int tok = a.target_ids[t0 + j];
+            const float uj = a.u_accept[t0 + j];
+            Sj = a.draft_mass[t0 + j];
+            if (tok >= 0 && tok < a.v_t) {
+                const float pt = a.target_probs[(int64_t)(t0 + b + j) * a.target_ld + tok];
+                const int32_t x = a.t2d[tok];
+                const float g = (x >= 0 && x < a.v_d) ? a.draft_probs[(int64_t)(t0 + j) * a.draft_ld + x] : 0.0f;
+                const float qj = qprime(g, Sj);
+                rej = !((qj <= 0.0f) || (uj < pt / qj));
+            }
+        }
+        const unsigned long long rm = __ballot(rej);
+        if (rm != 0ull) {
+            const int l = __ffsll(rm) - 1;
+            gamma = base + l;
+            S_r = __shfl(Sj, l);
+        }
+    }
+}
+
+// gamma and S_gamma without masses (the whole workgroup of kThreads): S_j of each tested row, formed as
+// tt_tli_proposal forms it, row after row.
+__device__ void row_scan(const TliVerifyArgs &a, int b, int t0, int M, U128 *sh_red, float *sh_S, int *sh_rej, int &gamma,
+                         float &S_r) {
+    gamma = M;
+    S_r = 0.0f;
+    for (int j = 0; j < M; ++j) {
+        const float *drow = a.draft_probs + (int64_t)(t0 + j) * a.draft_ld;
+        const float Sj = row_mass(drow, a.d2t, a.v_d, sh_red, sh_S);
+        if (threadIdx.x == 0) {
+            const int tok = a.target_ids[t0 + j];
+            const float pt = a.target_probs[(int64_t)(t0 + b + j) * a.target_ld + tok];
+            const int32_t x = a.t2d[tok];
+            const float g = (x >= 0 && x < a.v_d) ? drow[x] : 0.0f;
+            const float qj = qprime(g, Sj);
+            *sh_rej = !((qj <= 0.0f) || (a.u_accept[t0 + j] < pt / qj)) ? 1 : 0;
+        }
+        __syncthreads();
+        if (*sh_rej) {
+            gamma = j;
+            S_r = Sj;
+            return;
+        }
+    }
+}
+
+// The token of the residual (or bonus, drow null) row from its chunk sums part(c), by one wave.
+template <class Part>
+__device__ __forceinline__ int sample_residual(const TliVerifyArgs &a, const float *prow, const float *drow, float S_r, int nc,
+                                               float u, Part part) {
+    const int lane = threadIdx.x % kWave;
+    uint64_t Z, T, base;
+    int cs;
+    const int st = vcore::find_crossing(nc, part, u, Z, T, cs, base);
+    if (st == 1) return vcore::wave_first_argmax(prow, a.v_t);
+    if (st == 2) return a.v_t - 1;
+    const int x0 = cs * vcore::kChunk + lane * 16;
+    float pv[16], gv[16];
+    int32_t xs[16];
+    load_px(a, prow, x0, pv, xs);
+    gather16(a, drow, xs, gv);
+    uint64_t qv[16];
+    const uint64_t sum = residual16(pv, gv, S_r, x0, a.v_t, qv);
+    const uint64_t lincl = vcore::wave_inclusive_scan(sum) + base;
+    const uint64_t lexcl = lincl - sum;
+    const unsigned long long lhit = __ballot(lexcl <= T && T < lincl);
+    if (lhit == 0ull) return a.v_t - 1;
+    const int tl = __ffsll(lhit) - 1;
+    uint64_t run = lexcl;
+    int k_at = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        run += qv[k];
+        k_at += run <= T ? 1 : 0;
+    }
+    return __builtin_amdgcn_readlane(x0 + k_at, tl);
+}
+
 __global__ void __launch_bounds__(kThreads) verify_tli_row(TliVerifyParams p) {
     const TliVerifyArgs &a = p.a;
     const int b = blockIdx.x;
@@ -386,86 +502,37 @@ __global__ void __launch_bounds__(kThreads) verify_tli_row(TliVerifyParams p) {
         }
         return;
     }
-    if (wave == kWaves - 1) {  // every proposal's id inside the target vocabulary
-        bool ok = true;
-        for (int base = 0; ok && base < M; base += kWave) {
-            const int j = base + lane;
-            ok = !__any(j < M && (a.target_ids[t0 + j] < 0 || a.target_ids[t0 + j] >= a.v_t));
-        }
+    if (wave == kWaves - 1) {
+        const bool ok = ids_ok(a, t0, M, lane);
         if (lane == 0) {
             sh_ok = ok ? 1 : 0;
             sh_ctr = kWaves;
         }
     }
-    int gamma = M;
-    float S_r = 0.0f;
+    if (a.draft_mass != nullptr && wave == 0) {
+        int g;
+        float S;
+        mass_scan(a, b, t0, M, lane, g, S);
+        if (lane == 0) {
+            sh_gamma = g;
+            sh_Sr = S;
+        }
+    }
+    __syncthreads();
+    if (!sh_ok) {
+        if (tid == 0) {
+            a.n_accepted[b] = -1;
+            a.out_token[b] = -1;
+        }
+        return;
+    }
+    int gamma;
+    float S_r;
     if (a.draft_mass != nullptr) {
-        if (wave == 0) {
-            for (int base = 0; base < M && gamma == M; base += kWave) {
-                const int j = base + lane;
-                bool rej = false;
-                float Sj = 0.0f;
-                if (j < M) {
-                    const int tok = a.target_ids[t0 + j];
-                    const float uj = a.u_accept[t0 + j];
-                    Sj = a.draft_mass[t0 + j];
-                    if (tok >= 0 && tok < a.v_t) {
-                        const float pt = a.target_probs[(int64_t)(t0 + b + j) * a.target_ld + tok];
-                        const int32_t x = a.t2d[tok];
-                        const float g = (x >= 0 && x < a.v_d) ? a.draft_probs[(int64_t)(t0 + j) * a.draft_ld + x] : 0.0f;
-                        const float qj = qprime(g, Sj);
-                        rej = !((qj <= 0.0f) || (uj < pt / qj));
-                    }
-                }
-                const unsigned long long rm = __ballot(rej);
-                if (rm != 0ull) {
-                    const int l = __ffsll(rm) - 1;
-                    gamma = base + l;
-                    S_r = __shfl(Sj, l);
-                }
-            }
-            if (lane == 0) {
-                sh_gamma = gamma;
-                sh_Sr = S_r;
-            }
-        }
-        __syncthreads();
-        if (!sh_ok) {
-            if (tid == 0) {
-                a.n_accepted[b] = -1;
-                a.out_token[b] = -1;
-            }
-            return;
-        }
         gamma = sh_gamma;
         S_r = sh_Sr;
     } else {
-        __syncthreads();
-        if (!sh_ok) {
-            if (tid == 0) {
-                a.n_accepted[b] = -1;
-                a.out_token[b] = -1;
-            }
-            return;
-        }
-        for (int j = 0; j < M; ++j) {  // S_j of each tested row, formed as tt_tli_proposal forms it
-            const float *drow = a.draft_probs + (int64_t)(t0 + j) * a.draft_ld;
-            const float Sj = row_mass(drow, a.d2t, a.v_d, sh_red, &sh_S);
-            if (tid == 0) {
-                const int tok = a.target_ids[t0 + j];
-                const float pt = a.target_probs[(int64_t)(t0 + b + j) * a.target_ld + tok];
-                const int32_t x = a.t2d[tok];
-                const float g = (x >= 0 && x < a.v_d) ? drow[x] : 0.0f;
-                const float qj = qprime(g, Sj);
-                sh_rej = !((qj <= 0.0f) || (a.u_accept[t0 + j] < pt / qj)) ? 1 : 0;
-            }
-            __syncthreads();
-            if (sh_rej) {
-                gamma = j;
-                S_r = Sj;
-                break;
-            }
-        }
+        row_scan(a, b, t0, M, sh_red, &sh_S, &sh_rej, gamma, S_r);
     }
     TT_STAMP(1);
     // residual (or bonus) row: Q62 chunk sums of max(0, p - q') into LDS
@@ -503,39 +570,7 @@ __global__ void __launch_bounds__(kThreads) verify_tli_row(TliVerifyParams p) {
     __syncthreads();
     TT_STAMP(2);
     if (wave != 0) return;
-    uint64_t Z, T, base;
-    int cs;
-    const int st = vcore::find_crossing(nc, [&](int c) { return sh_part[c]; }, a.u_sample[b], Z, T, cs, base);
-    int token;
-    if (st == 1) {
-        token = vcore::wave_first_argmax(prow, a.v_t);
-    } else if (st == 2) {
-        token = a.v_t - 1;
-    } else {
-        const int x0 = cs * vcore::kChunk + lane * 16;
-        float pv[16], gv[16];
-        int32_t xs[16];
-        load_px(a, prow, x0, pv, xs);
-        gather16(a, drow, xs, gv);
-        uint64_t qv[16];
-        const uint64_t sum = residual16(pv, gv, S_r, x0, a.v_t, qv);
-        const uint64_t lincl = vcore::wave_inclusive_scan(sum) + base;
-        const uint64_t lexcl = lincl - sum;
-        const unsigned long long lhit = __ballot(lexcl <= T && T < lincl);
-        if (lhit == 0ull) {
-            token = a.v_t - 1;
-        } else {
-            const int tl = __ffsll(lhit) - 1;
-            uint64_t run = lexcl;
-            int k_at = 0;
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                run += qv[k];
-                k_at += run <= T ? 1 : 0;
-            }
-            token = __builtin_amdgcn_readlane(x0 + k_at, tl);
-        }
-    }
+    const int token = sample_residual(a, prow, drow, S_r, nc, a.u_sample[b], [&](int c) { return sh_part[c]; });
     if (lane == 0) {
         a.n_accepted[b] = gamma;
         a.out_token[b] = token;
@@ -543,11 +578,89 @@ __global__ void __launch_bounds__(kThreads) verify_tli_row(TliVerifyParams p) {
     TT_STAMP(3);
 }
 
+// The same in three kernels for batches that leave compute units idle (one workgroup per stream reads
+// its whole row, and gathers for it, on one): the acceptance (tli_gamma), the residual row's chunk
+// sums by `splits` workgroups a stream, a stream's together on one XCD (tli_stream), and the sample
+// (tli_sample).  A few streams' draft rows stay in L2 while they are gathered from, as in tli_fill.
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS) tli_gamma(TliVerifyParams p) {
+    const TliVerifyArgs &a = p.a;
+    const int b = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid % kWave;
+    __shared__ U128 sh_red[kWaves];
+    __shared__ float sh_S;
+    __shared__ int sh_rej;
+    const int t0 = a.target_off[b];
+    const int M = a.target_off[b + 1] - t0;
+    // (every wave checks the ids: the result is the same in all)
+    const bool ok = M >= 0 && M <= a.max_m && ids_ok(a, t0, M, lane);
+    int gamma = -1;
+    float S_r = 0.0f;
+    if (ok) {
+        if constexpr (THREADS == kWave) mass_scan(a, b, t0, M, lane, gamma, S_r);
+        else row_scan(a, b, t0, M, sh_red, &sh_S, &sh_rej, gamma, S_r);
+    }
+    if (tid == 0) {
+        p.rec[b] = TliRec{gamma, S_r};
+        if (!ok) {
+            a.n_accepted[b] = -1;
+            a.out_token[b] = -1;
+        }
+    }
+}
+
+__global__ void __launch_bounds__(kFillThreads) tli_stream(TliVerifyParams p) {
+    const TliVerifyArgs &a = p.a;
+    const int G = gridDim.x, g = blockIdx.x;
+    const int work = (g % kXcds) * (G / kXcds) + g / kXcds;
+    if (work >= a.n_streams * p.splits) return;
+    const int b = work / p.splits, sp = work % p.splits;
+    const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    constexpr int kW = kFillThreads / kWave;
+    const TliRec rec = p.rec[b];
+    if (rec.r < 0) return;
+    const int t0 = a.target_off[b];
+    const int M = a.target_off[b + 1] - t0;
+    const float *prow = a.target_probs + (int64_t)(t0 + b + rec.r) * a.target_ld;
+    const float *drow = rec.r < M ? a.draft_probs + (int64_t)(t0 + rec.r) * a.draft_ld : nullptr;
+    const int c1 = (sp + 1) * p.cps < p.nc ? (sp + 1) * p.cps : p.nc;
+    for (int c = sp * p.cps + wave; c < c1; c += kW) {
+        float4 pv[4];
+        float gv[16];
+        int32_t xs[16];
+        load_px_strided(a, prow, c, pv, xs);
+        gather16(a, drow, xs, gv);
+        const uint64_t acc = vcore::wave_total(residual_sum_strided(pv, gv, rec.S));
+        if (lane == kWave - 1) p.sums[(int64_t)b * p.nc + c] = acc;
+    }
+}
+
+__global__ void __launch_bounds__(kWave) tli_sample(TliVerifyParams p) {
+    const TliVerifyArgs &a = p.a;
+    const int b = blockIdx.x;
+    const TliRec rec = p.rec[b];
+    if (rec.r < 0) return;  // sentinel stream, outputs already written
+    const int t0 = a.target_off[b];
+    const int M = a.target_off[b + 1] - t0;
+    const float *prow = a.target_probs + (int64_t)(t0 + b + rec.r) * a.target_ld;
+    const float *drow = rec.r < M ? a.draft_probs + (int64_t)(t0 + rec.r) * a.draft_ld : nullptr;
+    const uint64_t *sums = p.sums + (int64_t)b * p.nc;
+    const int token = sample_residual(a, prow, drow, rec.S, p.nc, a.u_sample[b], [&](int c) { return sums[c]; });
+    if (threadIdx.x == 0) {
+        a.n_accepted[b] = rec.r;
+        a.out_token[b] = token;
+    }
+}
+
+inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
+
 }  // namespace
 
 int launch_tli_proposal(const TliArgs &a, hipStream_t stream) {
     if (a.n_rows == 0) return TT_OK;
-    if (a.v_d <= kSmallVocab && a.v_t <= kSmallVocab) {
+    const bool two = a.n_rows <= kFewRows ? (int64_t)a.v_d + a.v_t >= kFewRowsVocab
+                                          : a.v_d > kManyRowsDraft && a.v_t > kManyRowsTarget;
+    if (!two) {
         hipLaunchKernelGGL(tli_rows, dim3(a.n_rows), dim3(kThreads), 0, stream, a);
         return hipGetLastError() == hipSuccess ? TT_OK : TT_ELAUNCH;
     }
@@ -558,7 +671,7 @@ int launch_tli_proposal(const TliArgs &a, hipStream_t stream) {
     chunk = chunk < kCus ? kCus : chunk / kCus * kCus;
     if (chunk > kMaxItems / slices) chunk = kMaxItems / slices;
     if (chunk > a.n_rows || (4 * (int64_t)a.v_d * a.n_rows <= kCacheBytes && a.n_rows <= kMaxItems / slices)) chunk = a.n_rows;
-    int splits = (int)((kCus + chunk / 2) / chunk);
+    int splits = (int)(kCus / chunk);
     if (splits > kMaxSplits) splits = kMaxSplits;
     while (splits > 1 && (splits * 4 > a.v_t || a.v_d / splits < 4096)) --splits;
     if (splits < 1) splits = 1;
@@ -572,12 +685,33 @@ int launch_tli_proposal(const TliArgs &a, hipStream_t stream) {
     return hipGetLastError() == hipSuccess ? TT_OK : TT_ELAUNCH;
 }
 
-int launch_verify_tli(const TliVerifyArgs &a, hipStream_t stream) {
+size_t tli_workspace_bytes(int32_t n_streams, int32_t v_t) {
+    const int64_t nc = ((int64_t)v_t + vcore::kChunk - 1) / vcore::kChunk;
+    if (n_streams == 0 || nc < kTliSplitChunks || n_streams > (nc >= kTliLongChunks ? kTliLongStreams : kTliSplitStreams))
+        return 0;
+    return align256(sizeof(TliRec) * (size_t)n_streams) + 8 * (size_t)n_streams * (size_t)nc;
+}
+
+int launch_verify_tli(const TliVerifyArgs &a, void *workspace, size_t workspace_bytes, hipStream_t stream) {
     if (a.n_streams == 0) return TT_OK;
-    TliVerifyParams p;
+    TliVerifyParams p{};
     p.a = a;
     p.nc = (a.v_t + vcore::kChunk - 1) / vcore::kChunk;
-    hipLaunchKernelGGL(verify_tli_row, dim3(a.n_streams), dim3(kThreads), 8 * (size_t)p.nc, stream, p);
+    const size_t need = tli_workspace_bytes(a.n_streams, a.v_t);
+    if (workspace == nullptr || need == 0) {
+        hipLaunchKernelGGL(verify_tli_row, dim3(a.n_streams), dim3(kThreads), 8 * (size_t)p.nc, stream, p);
+        return hipGetLastError() == hipSuccess ? TT_OK : TT_ELAUNCH;
+    }
+    if (workspace_bytes < need) return TT_EWORKSPACE;
+    p.rec = static_cast<TliRec *>(workspace);
+    p.sums = reinterpret_cast<uint64_t *>(static_cast<uint8_t *>(workspace) + align256(sizeof(TliRec) * (size_t)a.n_streams));
+    p.cps = kFillThreads / kWave;  // a chunk a wave
+    p.splits = (p.nc + p.cps - 1) / p.cps;
+    if (a.draft_mass != nullptr) hipLaunchKernelGGL(tli_gamma<kWave>, dim3(a.n_streams), dim3(kWave), 0, stream, p);
+    else hipLaunchKernelGGL(tli_gamma<kThreads>, dim3(a.n_streams), dim3(kThreads), 0, stream, p);
+    const int items = a.n_streams * p.splits;
+    hipLaunchKernelGGL(tli_stream, dim3((items + kXcds - 1) / kXcds * kXcds), dim3(kFillThreads), 0, stream, p);
+    hipLaunchKernelGGL(tli_sample, dim3(a.n_streams), dim3(kWave), 0, stream, p);
     return hipGetLastError() == hipSuccess ? TT_OK : TT_ELAUNCH;
 }
 

@@ -165,10 +165,27 @@ int tt_verify_dense(int32_t n_streams, int32_t v, const int32_t *draft_ids, cons
     return tt::launch_verify(a, static_cast<hipStream_t>(stream));
 }
 
+int tt_verify_tli_workspace_size(int32_t n_streams, int32_t v_t, size_t *bytes) {
+    if (bytes == nullptr || n_streams < 0 || v_t < 1) return TT_EINVAL;
+    if (v_t > kMaxTliRow) return TT_EUNSUPPORTED;
+    *bytes = tt::tli_workspace_bytes(n_streams, v_t);
+    return TT_OK;
+}
+
 int tt_verify_tli(int32_t n_streams, int32_t v_d, int32_t v_t, const int32_t *d2t, const int32_t *t2d,
                   const int32_t *target_ids, const int32_t *target_off, const float *draft_probs, int64_t draft_ld,
                   const float *draft_mass, const float *target_probs, int64_t target_ld, const float *u_accept,
                   const float *u_sample, int32_t max_m, int32_t *n_accepted, int32_t *out_token, void *stream) {
+    return tt_verify_tli_ws(n_streams, v_d, v_t, d2t, t2d, target_ids, target_off, draft_probs, draft_ld, draft_mass,
+                            target_probs, target_ld, u_accept, u_sample, max_m, n_accepted, out_token, nullptr, 0, stream);
+}
+
+
+int tt_verify_tli_ws(int32_t n_streams, int32_t v_d, int32_t v_t, const int32_t *d2t, const int32_t *t2d,
+                  const int32_t *target_ids, const int32_t *target_off, const float *draft_probs, int64_t draft_ld,
+                  const float *draft_mass, const float *target_probs, int64_t target_ld, const float *u_accept,
+                  const float *u_sample, int32_t max_m, int32_t *n_accepted, int32_t *out_token, void *workspace,
+                     size_t workspace_bytes, void *stream) {
     if (n_streams < 0 || v_d < 1 || v_t < 1 || draft_ld < v_d || target_ld < v_t || max_m < 0 ||
         max_m > kMaxVerifyLen)
         return TT_EINVAL;
@@ -195,7 +212,7 @@ int tt_verify_tli(int32_t n_streams, int32_t v_d, int32_t v_t, const int32_t *d2
     a.max_m = max_m;
     a.n_accepted = n_accepted;
     a.out_token = out_token;
-    return tt::launch_verify_tli(a, static_cast<hipStream_t>(stream));
+    return tt::launch_verify_tli(a, workspace, workspace_bytes, static_cast<hipStream_t>(stream));
 }
 
 int tt_verify_logits_workspace_size(int32_t n_streams, int32_t v_t, int32_t max_m, int32_t with_lse, size_t *bytes) {

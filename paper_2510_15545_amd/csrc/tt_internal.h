@@ -142,7 +142,10 @@ struct TliVerifyArgs {
     int32_t max_m;
     int32_t *n_accepted, *out_token;
 };
-int launch_verify_tli(const TliVerifyArgs &a, hipStream_t stream);
+// Workspace of the kernels that spread a row over workgroups (0: one workgroup per stream is better).
+size_t tli_workspace_bytes(int32_t n_streams, int32_t v_t);
+// workspace null: one workgroup per stream.
+int launch_verify_tli(const TliVerifyArgs &a, void *workspace, size_t workspace_bytes, hipStream_t stream);
 size_t retok_lds_bytes(int32_t max_bytes);
 int launch_retokenize(const RetokArgs &a, hipStream_t stream);
 

@@ -134,8 +134,9 @@ def test_proposal_at_the_benchmark_vocabulary_sizes():
     assert np.allclose(got.sum(axis=1, dtype=np.float64), 1.0, atol=1e-5)
 
 
-@pytest.mark.parametrize("v_d,v_t,n", [(16385, 5, 3), (16385, 63, 3), (16385, 64, 3), (40000, 2047, 9), (40000, 2049, 70),
-                                       (33000, 4095, 130), (65537, 6145, 1), (100, 16385, 2), (16384, 16384, 3)])
+@pytest.mark.parametrize("v_d,v_t,n", [(65531, 5, 3), (65531, 4, 3), (65500, 63, 3), (65500, 64, 4), (63600, 2047, 9),
+                                       (63600, 2049, 64), (63600, 2049, 65), (33000, 36863, 130), (16385, 32769, 70),
+                                       (16384, 32769, 70), (65537, 6145, 1), (100, 65436, 2)])
 def test_proposal_rows_in_two_kernels(v_d, v_t, n):
     """Around the rule's line, slices with and without a remainder, a row's mass in 1 to 16 parts."""
     rng = np.random.default_rng(v_d + v_t + n)
@@ -156,7 +157,7 @@ def test_proposal_rows_past_the_cache():
 
     import paper_2510_15545_amd as tt
 
-    v_d, v_t, n = 262144, 20000, 261
+    v_d, v_t, n = 262144, 33000, 261
     d2t, t2d = (to_dev(x) for x in random_maps(np.random.default_rng(7), v_d, v_t, 0.8))
     q = torch.rand((n, v_d), generator=torch.Generator(device="cuda").manual_seed(7), device="cuda") / v_d
     whole = tt.tli_proposal(d2t, t2d, q)
@@ -356,3 +357,37 @@ def test_fused_tli_at_the_row_limit(v_t):
     want = oracle_tli(c, 2)
     for got in (fused(c, 2), fused(c, 2, intersected_mass(c))):
         assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("v_d,v_t,N,M", [(3000, 31744, 6, 3), (3000, 31745, 6, 3), (5001, 33001, 64, 2), (5001, 33001, 65, 2),
+                                         (2000, 131072, 3, 4), (400, 130049, 128, 1), (400, 130049, 129, 1)])
+def test_fused_tli_rows_over_workgroups(v_d, v_t, N, M):
+    """Around the lines where a row is spread over workgroups, against the two calls (compared with the
+    oracle above), with and without the drafter's masses, sentinel streams among them."""
+    rng = np.random.default_rng(v_d + v_t + N)
+    d2t, t2d = random_maps(rng, v_d, v_t, 0.6)
+    Ms = rng.integers(0, M + 1, N)
+    Ms[0] = M
+    off = np.zeros(N + 1, np.int32)
+    off[1:] = np.cumsum(Ms)
+    nt = int(off[-1])
+    q = (rng.random((nt, v_d), dtype=np.float32) ** 6)
+    q /= q.sum(axis=1, keepdims=True)
+    p = rng.random((nt + N, v_t), dtype=np.float32) ** 3
+    p /= p.sum(axis=1, keepdims=True)
+    shared = np.nonzero(t2d >= 0)[0]
+    ys = np.where(rng.random(nt) < 0.8, rng.choice(shared, nt), rng.integers(0, v_t, nt)).astype(np.int32)
+    rows_of = (off[:-1] + np.arange(N))[np.repeat(np.arange(N), Ms)] + (np.arange(nt) - np.repeat(off[:-1], Ms))
+    p[rows_of[::2], ys[::2]] += 0.01  # acceptances
+    c = dict(d2t=d2t, t2d=t2d, off=off, Ms=Ms, q=q, qd=q, ys=ys, p=p, pt=p, ua=rng.random(nt, dtype=np.float32),
+             us=rng.random(N, dtype=np.float32), v_d=v_d, v_t=v_t)
+    want = two_calls(c, M)
+    for got in (fused(c, M), fused(c, M, intersected_mass(c))):
+        assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+    bad = dict(c, ys=ys.copy())
+    bad["ys"][0] = v_t
+    for mass in (None, intersected_mass(c)):
+        n1, t1 = fused(bad, M, mass)
+        assert n1[0] == -1 and t1[0] == -1 and np.array_equal(n1[1:], want[0][1:]) and np.array_equal(t1[1:], want[1][1:])
+        n2, t2 = fused(c, M - 1, mass)
+        assert np.array_equal(n2, np.where(Ms < M, want[0], -1)) and np.array_equal(t2, np.where(Ms < M, want[1], -1))
