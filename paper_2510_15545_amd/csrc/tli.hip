@@ -374,13 +374,52 @@ __device__ __forceinline__ void load_px_strided(const TliVerifyArgs &a, const fl
     }
 }
 
+// q' of a row's masses by its reciprocal: with r = RN(1 / S), a quotient estimate within one unit in
+// the last place and the exact remainder (fused multiply-adds), one more step gives the correctly
+// rounded quotient (Markstein 1990), so q' is the IEEE quotient in 5 instructions instead of the 10 of
+// a division.  The first step takes g * r (within two units) to within one.  Exact while nothing
+// underflows: S in [2^-30, 2^10] and g = 0 or g >= 2^-60; else the division.  256 streams of
+// 151,936 ids: 61.6 us, 63.6 with divisions.
+struct RowMass {
+    float S, r;
+    bool fast;
+};
+
+__device__ __forceinline__ RowMass row_reciprocal(float S) {
+    RowMass m;
+    m.S = S;
+    m.r = 1.0f / S;
+    m.fast = S >= 0x1p-30f && S <= 0x1p10f;
+    return m;
+}
+
+__device__ __forceinline__ float quotient(float g, const RowMass &m) {
+    const float q0 = g * m.r;
+    const float q1 = fmaf(fmaf(-q0, m.S, g), m.r, q0);
+    return fmaf(fmaf(-q1, m.S, g), m.r, q1);
+}
+
 // Q62 sum of the 16 residual entries in that order (p = g = 0 past v_t gives 0).
-__device__ __forceinline__ uint64_t residual_sum_strided(const float4 (&pv)[4], const float (&gv)[16], float S) {
+__device__ __forceinline__ uint64_t residual_sum_strided(const float4 (&pv)[4], float (&gv)[16], const RowMass &m) {
     uint64_t sum = 0;
+    uint32_t least = 0xFFFFFFFFu;  // the least positive mass, as bits less one (0 wraps to the top)
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        gv[k] = clamp01(gv[k]);
+        const uint32_t bits = __float_as_uint(gv[k]) - 1u;
+        least = bits < least ? bits : least;
+    }
+    if (__all(m.fast && least >= 0x21800000u - 1u)) {  // 2^-60
+#pragma unroll
+        for (int k = 0; k < 16; ++k) gv[k] = quotient(gv[k], m);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) gv[k] = qprime(gv[k], m.S);
+    }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        sum += q62(clamp01(pv[u].x - qprime(gv[4 * u], S))) + q62(clamp01(pv[u].y - qprime(gv[4 * u + 1], S))) +
-               q62(clamp01(pv[u].z - qprime(gv[4 * u + 2], S))) + q62(clamp01(pv[u].w - qprime(gv[4 * u + 3], S)));
+        sum += q62(clamp01(pv[u].x - gv[4 * u])) + q62(clamp01(pv[u].y - gv[4 * u + 1])) +
+               q62(clamp01(pv[u].z - gv[4 * u + 2])) + q62(clamp01(pv[u].w - gv[4 * u + 3]));
     }
     return sum;
 }
@@ -546,6 +585,7 @@ __global__ void __launch_bounds__(kThreads) verify_tli_row(TliVerifyParams p) {
         float gv[16];
         int32_t xs[16];
         int c = wave, cn = nc;
+        const RowMass mass = row_reciprocal(S_r);
         if (c < nc) {
             load_px_strided(a, prow, c, pv, xs);
             gather16(a, drow, xs, gv);
@@ -553,7 +593,7 @@ __global__ void __launch_bounds__(kThreads) verify_tli_row(TliVerifyParams p) {
             if (cn < nc) load_px_strided(a, prow, cn, pn, xs);
         }
         while (c < nc) {
-            uint64_t acc = residual_sum_strided(pv, gv, S_r);
+            uint64_t acc = residual_sum_strided(pv, gv, mass);
             acc = vcore::wave_total(acc);
             if (lane == kWave - 1) sh_part[c] = acc;
             c = cn;
@@ -624,13 +664,14 @@ __global__ void __launch_bounds__(kFillThreads) tli_stream(TliVerifyParams p) {
     const float *prow = a.target_probs + (int64_t)(t0 + b + rec.r) * a.target_ld;
     const float *drow = rec.r < M ? a.draft_probs + (int64_t)(t0 + rec.r) * a.draft_ld : nullptr;
     const int c1 = (sp + 1) * p.cps < p.nc ? (sp + 1) * p.cps : p.nc;
+    const RowMass mass = row_reciprocal(rec.S);
     for (int c = sp * p.cps + wave; c < c1; c += kW) {
         float4 pv[4];
         float gv[16];
         int32_t xs[16];
         load_px_strided(a, prow, c, pv, xs);
         gather16(a, drow, xs, gv);
-        const uint64_t acc = vcore::wave_total(residual_sum_strided(pv, gv, rec.S));
+        const uint64_t acc = vcore::wave_total(residual_sum_strided(pv, gv, mass));
         if (lane == kWave - 1) p.sums[(int64_t)b * p.nc + c] = acc;
     }
 }

@@ -373,6 +373,8 @@ def test_fused_tli_rows_over_workgroups(v_d, v_t, N, M):
     nt = int(off[-1])
     q = (rng.random((nt, v_d), dtype=np.float32) ** 6)
     q /= q.sum(axis=1, keepdims=True)
+    q[0] *= np.float32(2.0 ** -50)  # outside the range of the quotient by a reciprocal: a small mass,
+    q[1::3, ::7] *= np.float32(2.0 ** -64)  # and small entries
     p = rng.random((nt + N, v_t), dtype=np.float32) ** 3
     p /= p.sum(axis=1, keepdims=True)
     shared = np.nonzero(t2d >= 0)[0]
