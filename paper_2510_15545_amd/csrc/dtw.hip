@@ -1,4 +1,4 @@
-// Dynamic Token Warping on gfx950 for pairs of any length: one 256-thread workgroup per
+// Dynamic Token Warping on gfx950 for pairs of any length: one 256- or 512-thread workgroup per
 // (draft, proxy-target) pair, small enough in LDS that several pairs share a compute unit.
 //
 // Computes Alg. 1 of the paper (cumulative cost C over draft x target tokens with the

@@ -17,7 +17,7 @@
 //            after full acceptance the bonus row's e31 is sampled as is
 //   token  = first index whose prefix exceeds floor(u * Z); first largest y when Z = 0.
 //
-// One 1024-thread workgroup per stream.  Without normalisers it walks its rows 0, 1, ...
+// verify_logits_row: one 1024-thread workgroup per stream.  Without normalisers it walks its rows 0, 1, ...
 // until the first rejection (each row: a max pass, then a pass of chunk sums into LDS -- the
 // second read mostly from the caches).  With per-row log-sum-exp values L from the caller
 // (an LM head can emit them with its logits) it uses m = L and S = 1: the acceptance test
@@ -25,6 +25,9 @@
 // Wave 0 samples: the chunk sums lane-blocked, the crossing chunk's e31 recomputed from its
 // 1024 logits.  In the row passes a lane reads 16 bf16 with two 16-byte loads, each load
 // instruction covering 1 KB of the row; the sampler reads 16 consecutive bf16 a lane.
+// With a workspace, rows are spread over the GPU: without normalisers they are screened many at once
+// and the walk starts where the screen stopped; with them, and after the screen, few streams form the
+// selected row's sums with several workgroups each (the sections below).
 #include "verify_core.h"
 
 TT_STAMPS_TABLE(logits)
