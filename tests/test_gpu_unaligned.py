@@ -54,3 +54,44 @@ def test_same_bits_at_any_alignment(v, offset, pad):
     for w, x in zip(want, got):
         for a, b in zip(w, x):
             assert torch.equal(a, b[..., :a.shape[-1]] if a.dim() == 2 else b)
+
+
+def test_spread_calls_replay_in_a_graph():
+    """The calls that take several kernels and scratch memory, captured once and replayed on new inputs in the same
+    buffers, other work in between: every replay equals the eager call."""
+    import paper_2510_15545_amd as tt
+
+    n, m, v = 6, 5, 40000
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rnd = lambda *s: torch.rand(s, generator=g, device="cuda")  # noqa: E731
+    off = (torch.arange(n + 1, device="cuda") * m).int()
+    order = torch.randperm(v, generator=g, device="cuda").int()
+    d2t, t2d = order, torch.empty_like(order)
+    t2d[d2t.long()] = torch.arange(v, device="cuda").int()
+    buf = dict(p=rnd(n * (m + 1), v), q=rnd(n * m, v), x=(3 * rnd(n * (m + 1), v)).bfloat16(), u=rnd(n * m), s=rnd(n),
+               ids=torch.zeros(n * m, dtype=torch.int32, device="cuda"), it=0.5 + rnd(n), qs=rnd(n * m) * 1e-4)
+    out = torch.zeros((n * m, v), device="cuda")
+
+    def calls():
+        lse = torch.zeros(n * (m + 1), device="cuda") + 12.0
+        return (*tt.verify_logits(v, buf["ids"], off, buf["qs"], buf["x"], buf["it"], buf["u"], buf["s"], m),
+                *tt.verify_logits(v, buf["ids"], off, buf["qs"], buf["x"], buf["it"], buf["u"], buf["s"], m, lse=lse),
+                *tt.verify_tli(d2t, t2d, buf["ids"], off, buf["q"], buf["p"], buf["u"], buf["s"], m),
+                tt.tli_proposal(d2t, t2d, buf["q"], out=out))
+
+    calls()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = calls()
+    for _ in range(3):
+        for k, t in buf.items():
+            if k == "ids":
+                t.copy_(torch.randint(0, v, t.shape, generator=g, device="cuda"))
+            else:
+                t.copy_((rnd(*t.shape) * (6 if k == "x" else 1e-4 if k == "qs" else 1) + (0.5 if k == "it" else 0)).to(t.dtype))
+        graph.replay()
+        replayed = [t.clone() for t in got]
+        torch.cuda.synchronize()
+        eager = calls()
+        assert all(torch.equal(a, b) for a, b in zip(replayed, eager))
