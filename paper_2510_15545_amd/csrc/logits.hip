@@ -448,12 +448,18 @@ __device__ __forceinline__ uint64_t lse_residual(const LseScan &rec) {
 // batch takes 88 us (rounds of 18, 23 and 12 us, the walk 22); 64 streams 48 against 195, 32
 // streams of 32,000 25 against 59, 512 of 32,000 96 against 113.
 //
-// The margin: P = E / S and its estimate differ by the estimate's exponents (a fused multiply-add
-// and a subtraction, each within 2^-19 for weights that count: 2.7e-6 relative), the hardware
-// exponential (2^-22), the polynomial of the exact weights (3.3e-6), the roundings of mu and
-// of 31 - mu where the exact exponent is held at 31 (4.3e-5 for |mu| < 512), fp32 sums of depth
-// at most 16 + a lane's chunks (below 300 * 2^-24 = 1.8e-5 at 2^23 logits), and the truncation
-// of the exact weights, which only lowers S (a larger P): below 8e-5 in all.
+// The margin: P = E / S and its estimate e / s differ (relative, |mu| < 512, q < 2^60) by
+//   3.2e-5  exponents of the exact weights held at 31 (mu rounded by at most 2^-16, 31 - mu by
+//           2^-15; a shift common to a row's weights cancels in E / S)
+//   5.4e-6  the polynomial of the exact weights, in E and in S (below 2.7e-6 each)
+//   2.7e-6  roundings of the exponents of both sides (2^-20 each where a weight counts)
+//   6.2e-5  a lane's running sum: up to 256 chunks (2^23 logits in at least 8 splits of four waves), each
+//           may raise the largest y and rescale the sum (hardware exponential 2^-23, product and
+//           sum 2^-24 each), and the sum of its 16 terms
+//   3.8e-6  lanes, waves and up to 32 splits combined
+//   0.5e-6  S, the quotients and the products of the test
+// below 1.1e-4 in all; the truncation of the exact weights only lowers S (a larger P), and weights too
+// small for these figures only raise s (a smaller estimate).
 constexpr int kScreenThreads = 256;
 constexpr int kScreenWaves = kScreenThreads / kWave;
 constexpr float kMargin = 2e-4f;
@@ -518,9 +524,9 @@ __device__ __forceinline__ bool screen_accepts(const ScreenParams &p, int b, int
     const float2 ms = screen_combine(p, b, j);
     if (q <= 0.0f) return true;
     const float e = __builtin_amdgcn_exp2f(fmaf(bf16_value(x), a.inv_temp[b] * kLog2e, -ms.x));
-    // (the exact weight is 0 below 2^-31; NaN, overlarge q and overlarge logits are left to the
-    // exact test)
-    return e >= 0x1.01p-31f && fabsf(ms.x) < 512.0f && q < 1e30f && u * q < e / ms.y * (1.0f - kMargin);
+    // (the exact weight is 0 below 2^-31; NaN, overlarge logits and overlarge q are left to the
+    // exact test: here P >= 2^-31 / 2^23, so P / q is a normal number while q < 2^60)
+    return e >= 0x1.01p-31f && fabsf(ms.x) < 512.0f && q < 0x1p60f && u * q < e / ms.y * (1.0f - kMargin);
 }
 
 // Where the exact walk of stream b starts, by one wave: the last round's window is tested here.

@@ -9,6 +9,7 @@ import pytest
 import oracle
 from gpu_util import to_dev
 from test_oracle_logits import bf16_bits, row_lse
+from util_logits import accept_probs
 
 pytestmark = pytest.mark.gpu
 
@@ -250,3 +251,48 @@ def test_logits_lse_split_rows(n, V):
     case = (ids, off, q, bits, it, ua, us, Ms)
     run_both(V, case, 5, lse=case_lse(V, case))
     run_both(V, case, 4, lse=case_lse(V, case, -1.0))
+
+
+@pytest.mark.parametrize("n,V,rows,max_m", [(300, 700, "plain", 6), (300, 700, "high", 6), (200, 9000, "rising", 4), (40, 33000, "rising", 8),
+                                            (260, 3000, "falling", 3), (2, 1 << 20, "rising", 2)])
+def test_logits_screen_at_the_accept_boundary(n, V, rows, max_m):
+    """P / q around u: equal up to fp32 steps, and off by 1e-6 to 3e-4 on both sides, on rows whose largest
+    logit rises (or falls) from chunk to chunk and rows with |mu| just under 512.  A position that the screen took
+    for accepted without the exact rule's consent would show."""
+    ids, off, q, bits, it, ua, us, Ms = logits_case(n, V, seed=21, max_m=max_m)
+    rng = np.random.default_rng(V + n)
+    x = rng.normal(0, 1, bits.shape).astype(np.float32)
+    slope = {"plain": 0.0, "high": 0.0, "rising": 3.0, "falling": -3.0}[rows]
+    x += np.float32(slope) * np.linspace(0, 1, V, dtype=np.float32)
+    if rows == "high":
+        it[:] = 1.0
+        x += np.where(np.arange(len(x)) % 2, np.float32(348), np.float32(-352))[:, None]
+    bits = bf16_bits(x)
+    ua = (0.25 + 0.75 * rng.random(len(ids))).astype(np.float32)
+    case = (ids, off, q, bits, it, ua, us, Ms)
+    offsets = np.array([0, 1e-7, 2e-7, 1e-6, 1e-5, 5e-5, 1e-4, 2e-4, 3e-4, 1e-3])
+    delta = rng.choice(np.concatenate([offsets, -offsets, offsets[5:], offsets[5:]]), len(ids))
+    q = (accept_probs(V, case) / (ua * (1.0 + delta))).astype(np.float32)
+    nacc, Ms = run_both(V, (ids, off, q, bits, it, ua, us, Ms), max_m)
+    assert n < 10 or ((nacc > 0).sum() > n // 8 and (nacc < Ms).sum() > n // 8)
+
+
+def test_logits_screen_with_overlarge_q():
+    """q about 2^98, where P / q falls among the subnormal numbers and rounds by percents: u at the rounded quotient
+    rejects, however the unrounded product compares."""
+    V, n = 30000, 64
+    ids, off, q, bits, it, ua, us, Ms = logits_case(n, V, seed=8, max_m=1)
+    Ms = np.ones(n, np.int64)
+    off = np.arange(n + 1, dtype=np.int32)
+    ids = np.arange(n, dtype=np.int32)
+    x = np.zeros((2 * n, V), np.float32)
+    x[2 * ids, ids] = -21.0  # weight 2^-30.3: a P of 2^-45
+    bits = bf16_bits(x)
+    it = np.ones(n, np.float32)
+    ua = np.full(n, 0.5, np.float32)
+    case = (ids, off, q, bits, it, ua, us, Ms)
+    q = (2.0 ** np.random.default_rng(8).uniform(97, 99.5, n)).astype(np.float32)
+    ua = (accept_probs(V, case).astype(np.float32) / q).astype(np.float32)
+    assert np.all((ua > 0) & (ua < 2.0 ** -126))
+    nacc, _ = run_both(V, (ids, off, q, bits, it, ua, us, Ms), 1)
+    assert not nacc.any()
