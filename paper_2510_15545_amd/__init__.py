@@ -28,7 +28,7 @@ import torch
 
 __all__ = ["Vocab", "align", "align_workspace", "transfer", "verify", "verify_noalloc", "verify_dense", "verify_workspace", "lib",
            "delta_histogram", "delta_quantile", "w_at_quantile", "token_index", "retokenize", "LIB_PATH",
-           "vocab_intersection", "tli_proposal", "verify_tli", "verify_logits",
+           "vocab_intersection", "tli_proposal", "verify_tli", "verify_logits", "verify_logits_workspace", "verify_tli_workspace",
            "TTError", "path_capacity"]
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libtt.so")
@@ -136,13 +136,28 @@ def _ptr(t, dtype, name, allow_none=False):
     raise ValueError(f"{name} must be contiguous")
 
 
-def _scratch(nbytes: int, device, stream):
-    """Device memory for one call on `stream`, from that stream's pool: once the call has returned, the
-    allocator hands it only to work that the same stream runs later."""
+def _on_stream(stream, f, *args, **kwargs):
+    """f(...) with `stream` and its device current (None: as they are)."""
     if stream is None:
-        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        return f(*args, **kwargs)
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream)
     with torch.cuda.stream(stream):
-        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        return f(*args, **kwargs)
+
+
+def _spread_workspace(workspace, nbytes: int, caller_out: bool, stream):
+    """The workspace tensor (or None) of a call that can do without one: the caller's, if given (an empty one:
+    none), else nbytes on the stream's device and from its pool, which the allocator hands on only to work that
+    the same stream runs later.  Nothing is allocated while a capture is under way that would otherwise need
+    nothing from this module: a capture begun outside torch keeps an address without keeping the memory."""
+    if workspace is not None:
+        if not workspace.is_cuda or not workspace.is_contiguous():
+            raise ValueError("workspace must be a contiguous device tensor")
+        return workspace if workspace.numel() else None
+    if nbytes == 0 or (caller_out and _on_stream(stream, torch.cuda.is_current_stream_capturing)):
+        return None
+    return _on_stream(stream, torch.empty, nbytes, dtype=torch.uint8, device="cuda")
 
 
 def _check(status: int, where: str):
@@ -322,14 +337,25 @@ def verify_dense(v: int, draft_ids, off, draft_probs, target_probs, u_accept, u_
     return out
 
 
+def verify_logits_workspace(n_streams: int, v_t: int, max_m: int, lse: bool = False, device="cuda"):
+    """A workspace for verify_logits with these bounds (empty when none is of use), reusable by calls that do not
+    overlap in time."""
+    n = ctypes.c_size_t(0)
+    _check(lib().tt_verify_logits_workspace_size(int(n_streams), int(v_t), int(max_m), 1 if lse else 0, ctypes.byref(n)),
+           "tt_verify_logits_workspace_size")
+    return torch.empty(n.value, dtype=torch.uint8, device=device)
+
+
 def verify_logits(v_t: int, target_ids, target_off, q, target_logits, inv_temperature, u_accept, u_sample,
-                  max_m: int, lse=None, out=None, stream=None):
-    """tt_verify_logits: target_logits is a 2-D row-major device tensor of bf16 (or its int16 / uint16
+                  max_m: int, lse=None, out=None, stream=None, workspace=None):
+    """tt_verify_logits_ws: target_logits is a 2-D row-major device tensor of bf16 (or its int16 / uint16
     bit patterns); inv_temperature float32 [n_streams]; lse optional float32 [rows], the rows'
-    log-sum-exp of logit * inv_temperature.  Returns (n_accepted, out_token)."""
+    log-sum-exp of logit * inv_temperature.  workspace: from verify_logits_workspace(), or an empty tensor
+    for the one kernel that needs none; allocated here when useful and not given.  Returns (n_accepted, out_token)."""
     i32, f32 = torch.int32, torch.float32
     n = int(target_off.numel()) - 1
     dev = target_off.device
+    caller_out = out is not None
     if target_logits.dim() != 2 or target_logits.stride(1) != 1 or not target_logits.is_cuda or \
             target_logits.element_size() != 2:
         raise ValueError("target_logits must be a 2-D row-major 16-bit device tensor")
@@ -340,14 +366,16 @@ def verify_logits(v_t: int, target_ids, target_off, q, target_logits, inv_temper
     qq = q if q.numel() else torch.zeros(1, dtype=f32, device=dev)
     ua = u_accept if u_accept.numel() else torch.zeros(1, dtype=f32, device=dev)
     nb = ctypes.c_size_t(0)
-    st = lib().tt_verify_logits_workspace_size(n, int(v_t), int(max_m), 0 if lse is None else 1, ctypes.byref(nb))
-    ws = _scratch(nb.value, dev, stream) if st == TT_OK and nb.value else None
+    if workspace is None:  # (an argument that the size query refuses is the call's own error)
+        lib().tt_verify_logits_workspace_size(n, int(v_t), int(max_m), 0 if lse is None else 1, ctypes.byref(nb))
+    ws = _spread_workspace(workspace, nb.value, caller_out, stream)
     st = lib().tt_verify_logits_ws(n, int(v_t), _ptr(ids, i32, "target_ids"), _ptr(target_off, i32, "target_off"),
                                 _ptr(qq, f32, "q"), target_logits.data_ptr(),
                                 int(target_logits.stride(0)), _ptr(inv_temperature, f32, "inv_temperature"),
                                 _ptr(lse, f32, "lse", allow_none=True), _ptr(ua, f32, "u_accept"), _ptr(u_sample, f32, "u_sample"), int(max_m),
                                 _ptr(nacc, i32, "n_accepted"), _ptr(tok, i32, "out_token"),
-                                None if ws is None else ws.data_ptr(), nb.value, _stream_handle(stream))
+                                None if ws is None else ws.data_ptr(), 0 if ws is None else ws.nbytes,
+                                _stream_handle(stream))
     _check(st, "tt_verify_logits")
     return out
 
@@ -450,13 +478,22 @@ def tli_proposal(d2t, t2d, draft_probs, v_d: int | None = None, out=None, stream
     return out
 
 
+def verify_tli_workspace(n_streams: int, v_t: int, device="cuda"):
+    """A workspace for verify_tli with these bounds (empty when none is of use), reusable by calls that do not
+    overlap in time."""
+    n = ctypes.c_size_t(0)
+    _check(lib().tt_verify_tli_workspace_size(int(n_streams), int(v_t), ctypes.byref(n)), "tt_verify_tli_workspace_size")
+    return torch.empty(n.value, dtype=torch.uint8, device=device)
+
+
 def verify_tli(d2t, t2d, target_ids, target_off, draft_probs, target_probs, u_accept, u_sample, max_m: int,
-               draft_mass=None, v_d: int | None = None, out=None, stream=None):
+               draft_mass=None, v_d: int | None = None, out=None, stream=None, workspace=None):
     """tt_verify_tli: standard speculative sampling with the TLI proposal formed on the fly from
     draft rows [sum M, >= V_d] float32 (row target_off[b] + j for position j) against target rows
-    [rows, >= V_t]; draft_mass optional float32 [sum M], the drafter's S_j.  Returns
-    (n_accepted, out_token)."""
+    [rows, >= V_t]; draft_mass optional float32 [sum M], the drafter's S_j.  workspace:
+    as for verify_logits(), from verify_tli_workspace().  Returns (n_accepted, out_token)."""
     i32, f32 = torch.int32, torch.float32
+    caller_out = out is not None
     v_d = int(d2t.numel()) if v_d is None else int(v_d)
     v_t = int(t2d.numel())
     n = int(target_off.numel()) - 1
@@ -470,15 +507,16 @@ def verify_tli(d2t, t2d, target_ids, target_off, draft_probs, target_probs, u_ac
     ids = target_ids if target_ids.numel() else torch.zeros(1, dtype=i32, device=dev)
     ua = u_accept if u_accept.numel() else torch.zeros(1, dtype=f32, device=dev)
     nb = ctypes.c_size_t(0)
-    st = lib().tt_verify_tli_workspace_size(n, v_t, ctypes.byref(nb))
-    ws = _scratch(nb.value, dev, stream) if st == TT_OK and nb.value else None
+    if workspace is None:
+        lib().tt_verify_tli_workspace_size(n, v_t, ctypes.byref(nb))
+    ws = _spread_workspace(workspace, nb.value, caller_out, stream)
     st = lib().tt_verify_tli_ws(n, v_d, v_t, _ptr(d2t, i32, "d2t"), _ptr(t2d, i32, "t2d"), _ptr(ids, i32, "target_ids"),
                              _ptr(target_off, i32, "target_off"), draft_probs.data_ptr(),
                              int(draft_probs.stride(0)), _ptr(draft_mass, f32, "draft_mass", allow_none=True),
                              target_probs.data_ptr(), int(target_probs.stride(0)),
                              _ptr(ua, f32, "u_accept"), _ptr(u_sample, f32, "u_sample"), int(max_m),
-                             _ptr(nacc, i32, "n_accepted"), _ptr(tok, i32, "out_token"), None if ws is None else ws.data_ptr(), nb.value,
-                             _stream_handle(stream))
+                             _ptr(nacc, i32, "n_accepted"), _ptr(tok, i32, "out_token"),
+                             None if ws is None else ws.data_ptr(), 0 if ws is None else ws.nbytes, _stream_handle(stream))
     _check(st, "tt_verify_tli")
     return out
 
