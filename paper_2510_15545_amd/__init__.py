@@ -24,8 +24,6 @@ from __future__ import annotations
 import ctypes
 import os
 
-import torch
-
 __all__ = ["Vocab", "align", "align_workspace", "transfer", "verify", "verify_noalloc", "verify_dense", "verify_workspace", "lib",
            "delta_histogram", "delta_quantile", "w_at_quantile", "token_index", "retokenize", "LIB_PATH",
            "vocab_intersection", "tli_proposal", "verify_tli", "verify_logits", "verify_logits_workspace", "verify_tli_workspace",
@@ -115,10 +113,26 @@ def lib():
     return _lib
 
 
+class _Torch:
+    """Stands in the module's `torch` until the first use replaces it by the real one: the workload
+    generator and the build script import this package without torch."""
+
+    def __getattr__(self, name):
+        global torch
+        import torch
+
+        return getattr(torch, name)
+
+
+torch = _Torch()
+
+
 def _stream_handle(stream):
-    if stream is None:  # the current stream's handle without a Stream object around it
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    # the current stream's handle without a Stream object around it, where torch has that call
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
 
 
 def _ptr(t, dtype, name, allow_none=False):

@@ -3,6 +3,9 @@ and rejects host-visible argument errors before touching the device."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
+import types
 
 import pytest
 
@@ -215,3 +218,23 @@ def test_delta_quantile_argument_checks():
     assert L.tt_delta_quantile(dummy, 8, -1, 10, dummy, None) == tt.TT_EINVAL
     assert L.tt_delta_quantile(dummy, 8, 1, 0, dummy, None) == tt.TT_EINVAL
     assert L.tt_delta_quantile(dummy, 8, 1, 65537, dummy, None) == tt.TT_EINVAL
+
+
+def test_package_imports_without_torch():
+    """The workload generator and the build script need no torch."""
+    code = ("import sys; sys.modules['torch'] = None\n"
+            "import paper_2510_15545_amd as tt\n"
+            "from paper_2510_15545_amd import build, synth\n"
+            "assert tt.lib().tt_version() >= 100 and synth.make(1, n_streams=1).n == 1 and build.sources()")
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT)
+
+
+def test_stream_handles(monkeypatch):
+    """The caller's stream, the current stream's raw handle, and the current stream where torch has no such call."""
+    raw = types.SimpleNamespace(_cuda_getCurrentRawStream=lambda device: 100 + device)
+    cuda = types.SimpleNamespace(current_device=lambda: 2, current_stream=lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(tt, "torch", types.SimpleNamespace(_C=raw, cuda=cuda))
+    assert tt._stream_handle(types.SimpleNamespace(cuda_stream=5)) == 5
+    assert tt._stream_handle(None) == 102
+    monkeypatch.setattr(tt, "torch", types.SimpleNamespace(_C=types.SimpleNamespace(), cuda=cuda))
+    assert tt._stream_handle(None) == 77
