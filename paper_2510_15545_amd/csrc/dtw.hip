@@ -155,7 +155,13 @@ __host__ __device__ inline LdsPlan plan_lds(int32_t max_k, int32_t max_m, int32_
 // a distance needs two or more; a table turns each into one LDS read.  Two strips' tables take
 // 64 KB, so only batches that leave every pair a compute unit of its own have them: 96 pairs of
 // 16-128 tokens (up to 16 bytes) without a band take 144 us (193 with masks gathered and a ranking kernel).
+// The table makes the target token the text; gathered masks let the shorter token be it, so the
+// tables pay only where draft tokens are long: a pair uses them when a quarter of its draft
+// tokens have more than kEqLong bytes.  Tokens of 1-16 bytes, evenly: 0.84 of the time without tables; drafts so and
+// targets of about two bytes 0.89; but 97% of 1-3 bytes on both sides 1.30 times it, against
+// long targets 1.44 (1.00 by this rule), drafts of about four 1.17 (1.00).
 constexpr int kEqBytes = 2 * kWave * 256 * 2;
+constexpr int kEqLong = 6, kEqShare = 4;
 constexpr int kCus = 256;
 
 // The table of strip st, one wave per row in turn (hw of nhw).
@@ -365,10 +371,10 @@ __device__ __forceinline__ void chunk_costs(const Band &g, const Strip &st, int 
                                 packed |= closed_table(eq + r * 256, yw[u], rec[u], xm, lim) << (8 * u);
                         } else {
 #pragma unroll
-                        for (int u = 0; u < 4; ++u)
-                            packed |= closed_distance<TB>(xw, xm, lim, __builtin_amdgcn_perm(0u, yw[u], 0u),
-                                                          __builtin_amdgcn_perm(0u, yw[u], 0x01010101u), (int)(rec[u] & 0x7Fu))
-                                      << (8 * u);
+                            for (int u = 0; u < 4; ++u)
+                                packed |= closed_distance<TB>(xw, xm, lim, __builtin_amdgcn_perm(0u, yw[u], 0u),
+                                                              __builtin_amdgcn_perm(0u, yw[u], 0x01010101u), (int)(rec[u] & 0x7Fu))
+                                          << (8 * u);
                         }
                     }
                 }
@@ -422,6 +428,16 @@ __device__ __forceinline__ void chunk_costs(const Band &g, const Strip &st, int 
         }
         buf[r * kCostStride + gq] = packed;
     }
+}
+
+// The same for a pair that uses match tables or not (tables, uniform; false without EQ).  Both forms are whole: one
+// that chose tables or masks by wave ran 1.25 times as long for every pair.
+template <int TB, int TS, bool EQ>
+__device__ __forceinline__ void pair_costs(bool tables, const Band &g, const Strip &st, int T0, uint32_t *buf, const uint16_t *eq,
+                                           const uint32_t *tslot, const uint8_t *tlen, const uint32_t *dslot,
+                                           const uint8_t *dlen, int h, int nh) {
+    if (EQ && tables) chunk_costs<TB, TS, EQ>(g, st, T0, buf, eq, tslot, tlen, dslot, dlen, h, nh);
+    else chunk_costs<TB, TS, false>(g, st, T0, buf, eq, tslot, tlen, dslot, dlen, h, nh);
 }
 
 // Per-lane state of the strip sweep (wave 0, lane r = row i0 + r).
@@ -510,16 +526,18 @@ dtw_band(AlignArgs a, LdsPlan lp, uint32_t *gcodes, size_t gcode_stride,
     uint32_t *poff = seg + a.max_k;                               // [K]: index of the row's first path cell
     __shared__ int votes[kThreads / kWave];
     __shared__ int s_imin, s_n;
+    __shared__ int s_longs[kThreads / kWave];  // EQ: long draft tokens by wave
 
     // ---- staging + validation: one token (draft or target) per thread and pass
     const bool shape_ok = K >= 1 && K <= a.max_k && M >= 1 && M <= a.max_m;
-    int bad = shape_ok ? 0 : 1;
+    int bad = shape_ok ? 0 : 1, longs = 0;
     if (shape_ok) {
         for (int e = tid; e < K + M; e += kThreads) {
             uint32_t *slot = tslot + (e - K + kTPad) * ts;
             const bool ok = e < K ? stage_token<TB>(a.vd, a.draft_ids[d0 + e], dslot + e * (TB / 4), dlen + e)
                                   : stage_token<TB>(a.vt, a.target_ids[t0 + e - K], slot, tlen + (e - K + kTPad));
             if (TS > TB / 4 && e >= K && ok) slot[TB / 4] = token_record(tlen[e - K + kTPad]);
+            if (EQ && ok && e < K) longs += dlen[e] > kEqLong ? 1 : 0;
             bad |= ok ? 0 : 1;
         }
         // the empty slots around the target tokens (read by items that straddle the band's ends)
@@ -530,6 +548,10 @@ dtw_band(AlignArgs a, LdsPlan lp, uint32_t *gcodes, size_t gcode_stride,
             if (q == 0) tlen[slot] = 0;
         }
     }
+    if (EQ) {  // (complete at the votes' barrier)
+        longs = dtw::wave_prefix_sum(longs);
+        if (lane == kWave - 1) s_longs[wave] = longs;
+    }
     if (dtw::block_or(bad, votes, kThreads / kWave)) {
         if (tid == 0) {
             a.cost[b] = -1;
@@ -537,6 +559,13 @@ dtw_band(AlignArgs a, LdsPlan lp, uint32_t *gcodes, size_t gcode_stride,
         }
         for (int j = tid; j < M; j += kThreads) a.map[t0 + j] = -1;
         return;
+    }
+
+    bool tables = false;  // uniform: this pair's distances come from match tables
+    if (EQ) {
+        int all = 0;
+        for (int w = 0; w < kThreads / kWave; ++w) all += s_longs[w];
+        tables = kEqShare * all >= K;
     }
 
     // ---- band geometry for this pair
@@ -561,11 +590,11 @@ dtw_band(AlignArgs a, LdsPlan lp, uint32_t *gcodes, size_t gcode_stride,
     uint32_t *eqtab = reinterpret_cast<uint32_t *>(lds + lp.eq);  // EQ: the tables of strip s in half s & 1
     auto eq_of = [&](int s) { return eqtab + (s & 1) * kWave * 128; };
     auto eq16 = [&](int s) { return reinterpret_cast<const uint16_t *>(eq_of(s)); };
-    if (EQ) {
+    if (EQ && tables) {
         build_eq(st.i0, st.R, eq_of(0), dslot, dlen, TB, wave, kThreads / kWave);
         __syncthreads();
     }
-    chunk_costs<TB, TS, EQ>(g, st, 0, costbuf, eq16(0), tslot, tlen, dslot, dlen, tid, kThreads);
+    pair_costs<TB, TS, EQ>(tables, g, st, 0, costbuf, eq16(0), tslot, tlen, dslot, dlen, tid, kThreads);
     __syncthreads();
     // the sweep is the critical path: its wave wins issue arbitration on its SIMD
     if (wave == 0) __builtin_amdgcn_s_setprio(3);
@@ -584,7 +613,7 @@ dtw_band(AlignArgs a, LdsPlan lp, uint32_t *gcodes, size_t gcode_stride,
             sw.cw = 0;
         }
         const Strip nxt = (s + 1 < nstrips) ? strip_at(g, s + 1) : st;
-        if (EQ && st.nchunks == 1 && s + 1 < nstrips) {  // the next strip's distances start with this chunk
+        if (EQ && tables && st.nchunks == 1 && s + 1 < nstrips) {  // the next strip's distances start with this chunk
             if (wave != 0) build_eq(nxt.i0, nxt.R, eq_of(s + 1), dslot, dlen, TB, wave - 1, kThreads / kWave - 1);
             __syncthreads();
         }
@@ -594,11 +623,11 @@ dtw_band(AlignArgs a, LdsPlan lp, uint32_t *gcodes, size_t gcode_stride,
             if (wave == 0) {
                 sweep_chunk(sw, cur_buf, rowIn, rowOut, c * kChunk, st.jfirst, rw);
             } else if (c + 1 < st.nchunks) {
-                if (EQ && c == 0 && s + 1 < nstrips)  // complete at this chunk's barrier, first read after it
+                if (EQ && tables && c == 0 && s + 1 < nstrips)  // complete at this chunk's barrier, first read after it
                     build_eq(nxt.i0, nxt.R, eq_of(s + 1), dslot, dlen, TB, wave - 1, kThreads / kWave - 1);
-                chunk_costs<TB, TS, EQ>(g, st, (c + 1) * kChunk, next_buf, eq16(s), tslot, tlen, dslot, dlen, tid - kWave, kHelpers);
+                pair_costs<TB, TS, EQ>(tables, g, st, (c + 1) * kChunk, next_buf, eq16(s), tslot, tlen, dslot, dlen, tid - kWave, kHelpers);
             } else if (s + 1 < nstrips) {
-                chunk_costs<TB, TS, EQ>(g, nxt, 0, next_buf, eq16(s + 1), tslot, tlen, dslot, dlen, tid - kWave, kHelpers);
+                pair_costs<TB, TS, EQ>(tables, g, nxt, 0, next_buf, eq16(s + 1), tslot, tlen, dslot, dlen, tid - kWave, kHelpers);
             }
             __syncthreads();
             ++gidx;

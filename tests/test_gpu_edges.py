@@ -342,3 +342,22 @@ def test_delta_quantile_sizes(n_bins):
         for num, den in ((9, 10), (0, 1), (1, 1), (65535, 65536)):
             want = 0 if cum[-1] == 0 else next(d for d in range(n_bins) if int(cum[d]) * den >= num * int(cum[-1]))
             assert tt.w_at_quantile(to_dev(h), num, den) == want, (n_bins, num, den)
+
+
+@pytest.mark.parametrize("K,M,short_of", [(4, 70, 0), (4, 70, 1), (67, 90, 0), (67, 90, 1), (130, 65, 0), (130, 65, 1)])
+def test_match_tables_by_the_share_of_long_drafts(K, M, short_of):
+    """Pairs with a quarter of their draft tokens longer than six bytes, and with one less: distances from match tables
+    and from gathered masks, pairs of both kinds in one batch."""
+    rng = np.random.default_rng(K + M + short_of)
+    alphabet = b"ab\x00\xff"
+    short, long_ = random_tokens(rng, 40, 1, 6, alphabet), random_tokens(rng, 60, 7, 16, alphabet)
+    toks = short + long_
+    v = vocab_of(toks)
+    pairs = []
+    for p in range(9):
+        n_long = -(-K // 4) - short_of * (p % 2)
+        d = np.concatenate([rng.integers(40, 100, n_long), rng.integers(0, 40, K - n_long)])
+        pairs.append((list(rng.permutation(d)), list(rng.integers(0, (100, 40, 100)[p % 3], M))))
+    wl = workload(v, v, pairs, len(toks), len(toks), probs=False)
+    for w in (8, -1):
+        compare_align(wl, gpu_run(wl, w=w, bounds=(max(K, 70), M)), oracle_run(wl, w=w))
