@@ -231,6 +231,11 @@ __device__ __forceinline__ uint32_t closed_distance(const uint32_t (&yw)[TB / 4]
     return (xm == 0 || yn == 0) ? (uint32_t)(xm + yn) : (xm == 1 ? d1 : d2);
 }
 
+// Whether target slots hold records: where there is the dword, and not at 32 and 64 bytes, where most waves meet a
+// token too long for the forms that use them and the look costs 2 to 4%.
+template <int TB, int TS>
+constexpr bool kRecords = TB <= 16 && TS > TB / 4;
+
 // The record a target token keeps in its slot's pad dword: its length in bits 0-6 and bit 7 of every
 // one of its first four bytes.
 __device__ __forceinline__ uint32_t token_record(int len) {
@@ -343,7 +348,7 @@ __device__ __forceinline__ void chunk_costs(const Band &g, const Strip &st, int 
                 const uint32_t *tp = tslot + (jb - 1 + kTPad) * TS;  // jb - 1 + kTPad >= 0: the item meets the band
                 packed = 0;
                 bool done = false;
-                if constexpr (TS > TB / 4) {
+                if constexpr (kRecords<TB, TS>) {
                     uint32_t yw[4], rec[4];
                     bool words = true, texts = true;  // every target token of one to four (two) bytes
 #pragma unroll
@@ -536,7 +541,7 @@ dtw_band(AlignArgs a, LdsPlan lp, uint32_t *gcodes, size_t gcode_stride,
             uint32_t *slot = tslot + (e - K + kTPad) * ts;
             const bool ok = e < K ? stage_token<TB>(a.vd, a.draft_ids[d0 + e], dslot + e * (TB / 4), dlen + e)
                                   : stage_token<TB>(a.vt, a.target_ids[t0 + e - K], slot, tlen + (e - K + kTPad));
-            if (TS > TB / 4 && e >= K && ok) slot[TB / 4] = token_record(tlen[e - K + kTPad]);
+            if (kRecords<TB, TS> && e >= K && ok) slot[TB / 4] = token_record(tlen[e - K + kTPad]);
             if (EQ && ok && e < K) longs += dlen[e] > kEqLong ? 1 : 0;
             bad |= ok ? 0 : 1;
         }
