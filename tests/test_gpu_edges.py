@@ -361,3 +361,40 @@ def test_match_tables_by_the_share_of_long_drafts(K, M, short_of):
     wl = workload(v, v, pairs, len(toks), len(toks), probs=False)
     for w in (8, -1):
         compare_align(wl, gpu_run(wl, w=w, bounds=(max(K, 70), M)), oracle_run(wl, w=w))
+
+
+@pytest.mark.parametrize("V", [1, 2, 3, 4, 5, 1023, 1027, 2047, 2048, 2049, 2051, 3071, 3074, 4095, 6147])
+@pytest.mark.parametrize("dense", [False, True])
+def test_residual_rows_of_any_width(V, dense):
+    """Whole spans of 2,048 entries, ragged ends of 16-byte groups and of one to three entries, a row without mass."""
+    import torch
+
+    import paper_2510_15545_amd as tt
+
+    n, M = 5, 2
+    g = torch.Generator(device="cuda").manual_seed(V)
+    p = torch.rand((n * (M + 1), V), generator=g, device="cuda") / V
+    q = torch.rand((n * M, V), generator=g, device="cuda") / V
+    p[3], q[2] = 0.0, 1.0  # stream 1 stops at its first row, and has no mass there
+    ids = torch.randint(0, V, (n * M,), generator=g, device="cuda", dtype=torch.int32)
+    off = (torch.arange(n + 1, device="cuda") * M).int()
+    ua, us = torch.full((n * M,), 0.9, device="cuda"), torch.rand(n, generator=g, device="cuda")
+    if dense:
+        nacc, tok, res = tt.verify_dense(V, ids, off, q, p, ua, us, M, residual=True)
+    else:
+        one = torch.rand(n * M, generator=g, device="cuda")
+        nacc, tok, res = tt.verify(V, ids, off, one, p, ua, us, M, residual=True)
+    torch.cuda.synchronize()
+    for b in range(n):
+        r = int(nacc[b])
+        R = p[b * (M + 1) + r].clone()
+        if r < M and dense:
+            R -= q[b * M + r]
+        elif r < M:
+            R[ids[b * M + r]] -= one[b * M + r]
+        R = R.clamp(0, 1)
+        Z = sum(int(float(x) * 2.0 ** 62) for x in R.tolist())
+        want = R / torch.tensor(Z * 2.0 ** -62, dtype=torch.float32, device="cuda") if Z else \
+            torch.nn.functional.one_hot(tok[b].long(), V).float()
+        # (Z rounds to fp32 here through a double: within one step, and the quotient within another)
+        assert torch.allclose(res[b, :V], want, rtol=3 * 2.0 ** -24, atol=0), (b, r)
