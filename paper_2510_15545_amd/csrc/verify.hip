@@ -284,18 +284,19 @@ __global__ void __launch_bounds__(kWave) verify_sample(VParams p) {
 }
 
 // Optional normalised residual row: res[x] = R(x) / fp32(Z * 2^-62), one-hot when Z = 0.
-// Bound by its reads (one or two rows) and its write.  A workgroup takes kResSpan entries, its
+// Bound by its reads (one or two rows) and its write.  A workgroup takes kResSpan entries at a time, its
 // loads all in flight before the first quotient: with a few streams that is what fills the chip
 // (48 rows of 50,257: about 1,200 workgroups, where spans of 8,192 read 4 bytes a lane at a time
 // by 336 workgroups took 14 us).  A ragged end takes 16-byte accesses too, as far as they reach: 512 rows of
 // 32,000 with dense proposals 58.5 us a call, 69.4 with the end's 1,280 entries a row written one by one.
 constexpr int kResUnroll = 2;
 constexpr int kResSpan = kSplitThreads * 4 * kResUnroll;
+constexpr int kResGrid = 1 << 18;  // workgroups of a launch at most (or one per stream); the next spans take another
 
 template <bool DENSE>
-__global__ void __launch_bounds__(kSplitThreads) residual_write(VParams p, int rsplit) {
+__global__ void __launch_bounds__(kSplitThreads) residual_write(VParams p, int rsplit, int span0) {
     const VerifyArgs &a = p.a;
-    const int b = blockIdx.x / rsplit, sidx = blockIdx.x % rsplit;
+    const int b = blockIdx.x / rsplit, sidx = span0 + blockIdx.x % rsplit;
     const int r = p.rsel[b];
     if (r < 0) return;  // sentinel stream
     const uint64_t Z = p.zsum[b];
@@ -388,13 +389,13 @@ VParams make_params(const VerifyArgs &a) {
 }
 
 int launch_residual(const VParams &p, hipStream_t stream) {
-    const int rsplit = (p.a.v_t + kResSpan - 1) / kResSpan;
-    if (p.a.q_rows != nullptr)
-        hipLaunchKernelGGL(residual_write<true>, dim3(p.a.n_streams * rsplit), dim3(kSplitThreads), 0, stream, p,
-                           rsplit);
-    else
-        hipLaunchKernelGGL(residual_write<false>, dim3(p.a.n_streams * rsplit), dim3(kSplitThreads), 0, stream, p,
-                           rsplit);
+    const int spans = (p.a.v_t - 1) / kResSpan + 1, most = kResGrid / p.a.n_streams;
+    const int rsplit = spans <= most ? spans : most < 1 ? 1 : most;
+    auto kernel = p.a.q_rows != nullptr ? &residual_write<true> : &residual_write<false>;
+    for (int span0 = 0; span0 < spans; span0 += rsplit) {
+        const int n = spans - span0 < rsplit ? spans - span0 : rsplit;
+        hipLaunchKernelGGL(kernel, dim3(p.a.n_streams * n), dim3(kSplitThreads), 0, stream, p, n, span0);
+    }
     return hipGetLastError() == hipSuccess ? TT_OK : TT_ELAUNCH;
 }
 

@@ -398,3 +398,20 @@ def test_residual_rows_of_any_width(V, dense):
             torch.nn.functional.one_hot(tok[b].long(), V).float()
         # (Z rounds to fp32 here through a double: within one step, and the quotient within another)
         assert torch.allclose(res[b, :V], want, rtol=3 * 2.0 ** -24, atol=0), (b, r)
+
+
+def test_residual_rows_in_several_launches():
+    """More spans than a launch takes: every stream's row equals that of the stream in a small batch."""
+    import torch
+
+    import paper_2510_15545_amd as tt
+
+    n, V = 4100, 131073  # 65 spans a row, 266,500 in all
+    p = torch.rand((n, V), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    off = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    none_i, none_f = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.zeros(1, device="cuda")
+    us = torch.rand(n, device="cuda")
+    _, tok, res = tt.verify(V, none_i, off, none_f, p, none_f, us, 0, residual=True)
+    for a in (0, 2040, n - 8):
+        _, t, r = tt.verify(V, none_i, off[:9], none_f, p[a:a + 8], none_f, us[a:a + 8].clone(), 0, residual=True)
+        assert torch.equal(tok[a:a + 8], t) and torch.equal(res[a:a + 8], r)
