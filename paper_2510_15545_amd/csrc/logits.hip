@@ -35,6 +35,7 @@ TT_STAMPS_TABLE(logits)
 namespace tt {
 namespace {
 
+using vcore::entry_or;
 using vcore::exact_threshold;
 using vcore::lane_value;
 using vcore::wave_inclusive_scan;
@@ -145,8 +146,8 @@ __device__ __forceinline__ void load16s(const uint16_t *row, int c, int lane, in
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const int x = xb + (k >> 2) * 512 + lane * 8 + 2 * (k & 3);
-            const uint32_t lo = x < v ? row[x] : 0u;
-            const uint32_t hi = x + 1 < v ? row[x + 1] : 0u;
+            const uint32_t lo = entry_or(row, x, v, uint16_t(0));
+            const uint32_t hi = entry_or(row, x + 1, v, uint16_t(0));
             w[k] = lo | (hi << 16);
         }
     }

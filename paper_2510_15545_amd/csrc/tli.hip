@@ -317,7 +317,7 @@ __device__ __forceinline__ void load_x(const TliVerifyArgs &a, int x0, int32_t (
         }
     } else {
 #pragma unroll
-        for (int k = 0; k < 16; ++k) xs[k] = x0 + k < a.v_t ? a.t2d[x0 + k] : -1;
+        for (int k = 0; k < 16; ++k) xs[k] = vcore::entry_or(a.t2d, x0 + k, a.v_t, -1);
     }
 }
 
@@ -369,7 +369,7 @@ __device__ __forceinline__ void load_px_strided(const TliVerifyArgs &a, const fl
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             const int y = xb + (k >> 2) * 256 + lane * 4 + (k & 3);
-            xs[k] = y < a.v_t ? a.t2d[y] : -1;
+            xs[k] = vcore::entry_or(a.t2d, y, a.v_t, -1);
         }
     }
 }
