@@ -466,8 +466,17 @@ constexpr int kScreenWaves = kScreenThreads / kWave;
 constexpr float kMargin = 2e-4f;
 constexpr float kLowest = -3e38f;  // below every scaled logit that counts
 constexpr int kScreenRows = 64;    // positions screened at most; the exact walk goes on from there
-constexpr int kScreenStreams = 512;  // streams of a screened batch at most
-constexpr int kMaxRounds = 8;
+// Streams of a screened batch at most: 1,024 streams of 32,000 to 64,000 logits gain nothing (0.8 to 1.06 times the
+// speed of the one kernel at any acceptance), 512 gain 1.1 to 1.3 times.
+constexpr int kScreenStreams = 512;
+// The first round's window: the positions whose rows make kWindowBytes, from about a row per compute
+// unit to kWindowRows.  A round costs about 8 us with its tests, which is what 40 MB take, so short rows go
+// in one round (256 streams of 4,000 logits, up to 8 positions: 25 us at any acceptance, 33 in three);
+// past 2,048 rows a batch that stops at once pays for rows that none of it needs.  Each later window is three
+// times as long; the fourth takes all that is left (few streams get there).
+constexpr int64_t kWindowBytes = int64_t(20) << 20;
+constexpr int kWindowRows = 2048;
+constexpr int kMaxRounds = 4;
 
 struct Window {
     int a, b;  // positions [a, b)
@@ -552,40 +561,26 @@ __device__ __forceinline__ Screened screen_result(const ScreenParams &p, int b, 
     return r;
 }
 
-// Between rounds: the streams whose window was accepted whole go on (the list of round `round`), the
-// others' positions are final.  One workgroup: done by every workgroup of the next round instead,
-// the tests' scattered loads took more than the rows (256 streams, second round: 40 us for 270 rows,
-// 17 us without them).
-__global__ void __launch_bounds__(kThreads) logits_advance(ScreenParams p, int round) {
-    const int tid = threadIdx.x, lane = tid % kWave;
-    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    __shared__ uint8_t sh_acc[kScreenStreams * kScreenRows / 2];  // [stream of the list][position]
+// Between rounds: the streams whose window was accepted whole go on (the list of round `round`, in any
+// order), the others' positions are final; a wave per stream.  A kernel of its own: done by every workgroup
+// of the next round instead, the tests' scattered loads took more than the rows (256 streams, second
+// round: 40 us for 270 rows, 17 us without them).
+__global__ void __launch_bounds__(kScreenThreads) logits_advance(ScreenParams p, int round) {
+    const int lane = threadIdx.x % kWave;
+    const int i = blockIdx.x * kScreenWaves + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int n = p.a.n_streams;
     const Window pw = p.win[round - 1];
-    const int prows = pw.b - pw.a;
     const int32_t *list = p.alive + (int64_t)(round - 1) * (n + 1);
     int32_t *out = p.alive + (int64_t)round * (n + 1);
-    const int n_prev = round > 1 ? list[0] : n;
-    auto stream = [&](int i) { return round > 1 ? list[1 + i] : i; };
-    for (int i = tid; i < n_prev * prows; i += kThreads)
-        sh_acc[i] = screen_accepts(p, stream(i / prows), pw.a + i % prows) ? 1 : 0;
-    __syncthreads();
-    if (wave != 0) return;
-    int count = 0;
-    for (int base = 0; base < n_prev; base += kWave) {
-        const int i = base + lane;
-        int f = 0, b = 0;
-        if (i < n_prev) {
-            b = stream(i);
-            while (f < prows && sh_acc[i * prows + f]) ++f;
-            p.from[b] = pw.a + f;
-        }
-        const bool stay = i < n_prev && f == prows;
-        const uint64_t m = __ballot(stay);
-        if (stay) out[1 + count + __popcll(m & ((1ull << lane) - 1ull))] = b;
-        count += __popcll(m);
+    if (i >= (round > 1 ? list[0] : n)) return;
+    const int b = round > 1 ? list[1 + i] : i;
+    const int rows = pw.b - pw.a;  // at most kScreenRows = kWave
+    const uint64_t no = ~__ballot(lane < rows && screen_accepts(p, b, pw.a + lane));
+    const int f = no != 0 ? __ffsll((unsigned long long)no) - 1 : kWave;
+    if (lane == 0) {
+        p.from[b] = pw.a + (f < rows ? f : rows);
+        if (f >= rows) out[1 + atomicAdd(out, 1)] = b;
     }
-    if (lane == 0) out[0] = count;
 }
 
 // One round: the splits of the window's rows of the streams still undecided, a workgroup each.
@@ -599,6 +594,7 @@ __global__ void __launch_bounds__(kScreenThreads) logits_screen(ScreenParams p, 
     const int32_t *list = p.alive + (int64_t)round * (a.n_streams + 1);
     const int n_alive = round > 0 ? list[0] : a.n_streams;
     const int items = n_alive * rows * p.splits;
+    if (round + 1 < p.n_rounds && blockIdx.x == 0 && tid == 0) p.alive[(int64_t)(round + 1) * (a.n_streams + 1)] = 0;
     for (int item = blockIdx.x; item < items; item += gridDim.x) {
         const int sp = item % p.splits, row_item = item / p.splits;
         const int i = row_item / rows, j = w.a + row_item % rows;
@@ -950,7 +946,16 @@ enum Route { kRowRoute, kLseSplit, kScreenRow, kScreenSplit };
 
 Route route(const LogitsArgs &a, int nc) {
     if (a.lse != nullptr) return a.n_streams <= kLseSplitStreams && nc >= kLseSplitChunks ? kLseSplit : kRowRoute;
-    if (a.n_streams > kScreenStreams || a.max_m < 1) return kRowRoute;
+    // Speed against the one kernel where half of the tests accept.  One test a stream: two kernels more cost what
+    // the second row's walk takes, so only few streams of long rows gain (64 streams of 32,000 logits 1.17 times; of
+    // 4,000 below 0.95, 200 of 32,000 0.73).  Two tests: not while rows of middling length fill the chip (200 streams of
+    // 32,000 to 64,000 logits 0.84 to 0.95; of 4,000 1.09, of 151,936 1.05).  From three on 1.0 to 4 times; one
+    // stream alone gains or loses by its own luck.  A batch that rejects every first proposal loses with any
+    // number (0.4 to 0.75 times; 8 streams of 151,936 logits 1.0): a caller that knows gives no workspace.
+    const bool screened = a.n_streams <= kScreenStreams &&
+                          (a.max_m >= 3 || (a.max_m == 2 && (a.n_streams <= 128 || nc <= 8 || nc >= 128)) ||
+                           (a.max_m == 1 && a.n_streams <= 64 && nc >= 16));
+    if (!screened) return kRowRoute;
     return a.n_streams < kCus ? kScreenSplit : kScreenRow;
 }
 
@@ -971,12 +976,12 @@ size_t layout(ScreenParams &p, Route rt, uint8_t *ws) {
     if (rt == kRowRoute) return 0;
     if (rt == kScreenRow || rt == kScreenSplit) {
         const int last = a.max_m + 1 < kScreenRows ? a.max_m + 1 : kScreenRows;  // rows 0 .. M, the bonus row among them
-        // the first window: about a row per compute unit
-        int len = kCus / a.n_streams < 1 ? 1 : kCus / a.n_streams;
+        int64_t rows = kWindowBytes / (2 * (int64_t)a.v_t);
+        rows = rows < kCus ? kCus : rows > kWindowRows ? kWindowRows : rows;
+        int len = rows < a.n_streams ? 1 : (int)(rows / a.n_streams);
         for (int at = 0; at < last;) {
-            // (half a window or less left over goes along; sh_acc holds half of the positions)
             int b = at + len;
-            if (last - b <= len / 2 || p.n_rounds == kMaxRounds - 1) b = last;
+            if (last - b <= len / 2 || p.n_rounds == kMaxRounds - 1) b = last;  // (half a window or less goes along)
             p.win[p.n_rounds++] = Window{at, b};
             at = b;
             len *= 3;
@@ -1032,7 +1037,9 @@ int launch_verify_logits(const LogitsArgs &a, void *workspace, size_t workspace_
     if (layout(p, rt, static_cast<uint8_t *>(workspace)) > workspace_bytes) return TT_EWORKSPACE;
     for (int r = 0; r < p.n_rounds; ++r) {
         const int items = a.n_streams * (p.win[r].b - p.win[r].a) * p.splits;
-        if (r > 0) hipLaunchKernelGGL(logits_advance, dim3(1), dim3(kThreads), 0, stream, p, r);
+        if (r > 0)
+            hipLaunchKernelGGL(logits_advance, dim3((a.n_streams + kScreenWaves - 1) / kScreenWaves), dim3(kScreenThreads), 0,
+                               stream, p, r);
         hipLaunchKernelGGL(logits_screen, dim3(items < kScreenGrid ? items : kScreenGrid), dim3(kScreenThreads), 0, stream, p, r);
     }
     if (rt == kScreenRow) return launch_row<kFrom>(p, stream);

@@ -296,3 +296,29 @@ def test_logits_screen_with_overlarge_q():
     assert np.all((ua > 0) & (ua < 2.0 ** -126))
     nacc, _ = run_both(V, (ids, off, q, bits, it, ua, us, Ms), 1)
     assert not nacc.any()
+
+
+def test_logits_screened_rows_with_a_loose_bound():
+    """Four rounds, the last with all that is left, for a batch in which most streams end in the first two; two
+    streams with more positions than are screened."""
+    n, V, max_m = 300, 21000, 90
+    ids, off, q, bits, it, ua, us, Ms = logits_case(n, V, seed=31, max_m=2)
+    many = {7: 90, 100: 70, 101: 40, 299: 13}
+    Ms = np.array([many.get(b, m) for b, m in enumerate(Ms)])
+    off = np.concatenate([[0], np.cumsum(Ms)]).astype(np.int32)
+    rng = np.random.default_rng(31)
+    bits = bf16_bits(rng.normal(0, 3, (int(off[-1]) + n, V)).astype(np.float32))
+    ids = rng.integers(0, V, int(off[-1])).astype(np.int32)
+    q = np.where(rng.random(len(ids)) < 0.93, 2.0 ** -45, 0.5).astype(np.float32)
+    q[off[7]:off[7] + 80] = q[off[100]:off[100] + 64] = 0.0
+    ua = rng.random(len(ids)).astype(np.float32)
+    nacc, _ = run_both(V, (ids, off, q, bits, it, ua, us, Ms), max_m)
+    assert nacc[7] >= 80 and nacc[100] >= 64
+
+
+@pytest.mark.parametrize("n,V,max_m", [(64, 16385, 1), (65, 16385, 1), (64, 15000, 1), (128, 9000, 2), (129, 9000, 2), (129, 8000, 2),
+                                       (129, 700, 3)])
+def test_logits_around_the_screens_lines(n, V, max_m):
+    """Batches on both sides of the lines between the one kernel and the screened rows."""
+    case = logits_case(n, V, seed=41, max_m=max_m)
+    run_both(V, case, max_m)
