@@ -937,9 +937,9 @@ constexpr int kScreenGrid = 2048;  // workgroups of a screening round
 // With normalisers, the row split over workgroups and sampled by a second kernel: for rows long enough
 // to pay for that launch and streams too few to fill the chip.  32 streams of 151,936: 10.9 us against
 // 17.9 in one kernel, 128: 18.1 against 19.9, 200: 22.9 against 20.9; 32 of 32,000: 8.8 against 10.1,
-// 32 of 12,000: no difference.
+// 32 of 16,000: 10.2 against 9.6, 128 of 20,000 11.0 against 10.2.
 constexpr int kLseSplitStreams = 128;
-constexpr int kLseSplitChunks = 16;
+constexpr int kLseSplitChunks = 28;
 
 // Which kernels a call takes (with a workspace).
 enum Route { kRowRoute, kLseSplit, kScreenRow, kScreenSplit };

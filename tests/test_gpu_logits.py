@@ -240,7 +240,8 @@ def test_logits_screened_rows(n, V, max_m):
     run_both(V, (ids, off, q, bits, it * np.float32(300), ua, us, Ms), max_m)
 
 
-@pytest.mark.parametrize("n,V", [(1, 15361), (3, 16384), (128, 15400), (129, 15400), (2, 40001)])
+@pytest.mark.parametrize("n,V", [(1, 15361), (3, 16384), (128, 15400), (129, 15400), (2, 40001), (1, 27648), (1, 27649),
+                                 (128, 27700), (129, 27700)])
 def test_logits_lse_split_rows(n, V):
     """With normalisers, around the line to the split kernels; ragged rows, sentinels among the streams."""
     ids, off, q, bits, it, ua, us, Ms = logits_case(n, V, seed=6, max_m=5)
