@@ -967,7 +967,7 @@ size_t layout(ScreenParams &p, Route rt, uint8_t *ws) {
     const size_t n = a.n_streams > 0 ? (size_t)a.n_streams : 0;
     size_t off = 0;
     auto take = [&](size_t bytes) {
-        uint8_t *at = ws + off;
+        const uintptr_t at = reinterpret_cast<uintptr_t>(ws) + off;  // (ws is null in a size query)
         off = align256(off + bytes);
         return at;
     };

@@ -65,6 +65,22 @@ int main(void) {
     EXPECT(tt_verify_tli(1, 10, 12, D, D, D, D, F, 9, NULL, F, 12, F, F, 4, D, D, NULL) == TT_EINVAL);
     EXPECT(tt_verify_tli(0, 10, 12, NULL, NULL, NULL, NULL, NULL, 10, NULL, NULL, 12, NULL, NULL, 4, NULL, NULL,
                          NULL) == TT_OK);
+    EXPECT(tt_verify_logits_workspace_size(4, 40000, 4, 0, &n) == TT_OK && n > 0);
+    EXPECT(tt_verify_logits_ws(4, 40000, D, D, F, (const uint16_t *)W, 40000, F, NULL, F, F, 4, D, D, W, n - 1, NULL) ==
+           TT_EWORKSPACE);
+    EXPECT(tt_verify_logits_workspace_size(512, 1 << 23, 65536, 0, &n) == TT_OK && n > 0);
+    EXPECT(tt_verify_logits_workspace_size(4, 40000, 4, 1, &n) == TT_OK && n > 0);
+    EXPECT(tt_verify_logits_ws(4, 40000, D, D, F, (const uint16_t *)W, 40000, F, F, F, F, 4, D, D, W, n - 1, NULL) ==
+           TT_EWORKSPACE);
+    EXPECT(tt_verify_logits_ws(0, 10, NULL, NULL, NULL, NULL, 10, NULL, NULL, NULL, NULL, 4, NULL, NULL, NULL, 0, NULL) ==
+           TT_OK);
+    EXPECT(tt_verify_logits_workspace_size(4, 0, 4, 0, &n) == TT_EINVAL);
+    EXPECT(tt_verify_tli_workspace_size(4, 40000, &n) == TT_OK && n > 0);
+    EXPECT(tt_verify_tli_ws(4, 10, 40000, D, D, D, D, F, 10, NULL, F, 40000, F, F, 4, D, D, W, n - 1, NULL) ==
+           TT_EWORKSPACE);
+    EXPECT(tt_verify_tli_ws(0, 10, 12, NULL, NULL, NULL, NULL, NULL, 10, NULL, NULL, 12, NULL, NULL, 4, NULL, NULL, NULL, 0,
+                            NULL) == TT_OK);
+    EXPECT(tt_verify_tli_workspace_size(-1, 40000, &n) == TT_EINVAL);
     printf("done\n");
     return 0;
 }

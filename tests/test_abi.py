@@ -220,6 +220,64 @@ def test_delta_quantile_argument_checks():
     assert L.tt_delta_quantile(dummy, 8, 1, 65537, dummy, None) == tt.TT_EINVAL
 
 
+def test_calls_with_an_optional_workspace():
+    """tt_verify_logits_ws and tt_verify_tli_ws: size queries, a workspace that is too small, and the checks that
+    they share with the calls without one."""
+    L = tt.lib()
+    P = ctypes.c_void_p
+    dummy = P(0x1000)  # never dereferenced: every call below fails validation first, or is empty
+    n = ctypes.c_size_t(7)
+    lsize = lambda *a: L.tt_verify_logits_workspace_size(*a, ctypes.byref(n))  # noqa: E731
+    assert L.tt_verify_logits_workspace_size(4, 40000, 4, 0, None) == tt.TT_EINVAL
+    for bad in ((-1, 40000, 4, 0), (4, 0, 4, 0), (4, 40000, -1, 0), (4, 40000, 65537, 0)):
+        assert lsize(*bad) == tt.TT_EINVAL, bad
+    assert lsize(4, (1 << 23) + 1, 4, 0) == tt.TT_EUNSUPPORTED
+    # few streams: per row the estimates, and per stream the selected row's 40 exact chunk sums
+    assert lsize(4, 40000, 4, 0) == 0 and n.value >= 4 * 5 * 8 + 4 * 40 * 8
+    assert lsize(4, 40000, 4, 1) == 0 and n.value >= 4 * 40 * 8
+    for none in ((0, 40000, 4, 0), (4, 40000, 0, 0), (513, 40000, 4, 0), (4, 20000, 4, 1), (129, 40000, 4, 1), (65, 40000, 1, 0)):
+        n.value = 7
+        assert lsize(*none) == 0 and n.value == 0, none  # the one kernel is the better one
+    assert lsize(512, 1 << 23, 65536, 0) == 0 and n.value < 64 << 20
+
+    def logits(ws=dummy, size=1 << 30, n=4, v=40000, ld=40000, max_m=4, it=dummy, lse=None):
+        return L.tt_verify_logits_ws(n, v, dummy, dummy, dummy, dummy, ld, it, lse, dummy, dummy, max_m, dummy, dummy, ws,
+                                     size, None)
+    assert logits(n=-1) == tt.TT_EINVAL
+    assert logits(ld=39999) == tt.TT_EINVAL
+    assert logits(max_m=65537) == tt.TT_EINVAL
+    assert logits(it=None) == tt.TT_EINVAL
+    assert logits(v=(1 << 23) + 1, ld=(1 << 23) + 1) == tt.TT_EUNSUPPORTED
+    assert logits(n=0, it=None) == tt.TT_OK
+    assert logits(n=0, ws=None, size=0) == tt.TT_OK
+    for lse in (None, dummy):
+        assert lsize(4, 40000, 4, 0 if lse is None else 1) == 0
+        assert logits(size=n.value - 1, lse=lse) == tt.TT_EWORKSPACE
+        assert logits(size=0, lse=lse) == tt.TT_EWORKSPACE
+
+    tsize = lambda *a: L.tt_verify_tli_workspace_size(*a, ctypes.byref(n))  # noqa: E731
+    assert L.tt_verify_tli_workspace_size(4, 40000, None) == tt.TT_EINVAL
+    assert tsize(-1, 40000) == tt.TT_EINVAL
+    assert tsize(4, 0) == tt.TT_EINVAL
+    assert tsize(4, (1 << 21) + 1) == tt.TT_EUNSUPPORTED
+    for none in ((0, 40000), (4, 31744), (65, 40000), (129, 151936)):
+        n.value = 7
+        assert tsize(*none) == 0 and n.value == 0, none
+    assert tsize(128, 151936) == 0 and n.value >= 128 * (8 + 149 * 8)
+
+    def tli(ws=dummy, size=1 << 30, n=4, v_d=10, v_t=40000, ld_d=10, ld_t=40000, max_m=4, q=dummy, mass=None):
+        return L.tt_verify_tli_ws(n, v_d, v_t, dummy, dummy, dummy, dummy, q, ld_d, mass, dummy, ld_t, dummy, dummy, max_m,
+                                  dummy, dummy, ws, size, None)
+    assert tli(n=-1) == tt.TT_EINVAL
+    assert tli(ld_t=39999) == tt.TT_EINVAL
+    assert tli(q=None) == tt.TT_EINVAL
+    assert tli(v_t=(1 << 21) + 1, ld_t=(1 << 21) + 1) == tt.TT_EUNSUPPORTED
+    assert tli(n=0, ws=None, size=0) == tt.TT_OK
+    assert tsize(4, 40000) == 0
+    assert tli(size=n.value - 1) == tt.TT_EWORKSPACE
+    assert tli(size=n.value - 1, mass=dummy) == tt.TT_EWORKSPACE
+
+
 def test_package_imports_without_torch():
     """The workload generator and the build script need no torch."""
     code = ("import sys; sys.modules['torch'] = None\n"

@@ -49,13 +49,14 @@ def run_both(V, case, max_m, lse=None):
     import paper_2510_15545_amd as tt
 
     ids, off, q, bits, it, ua, us, Ms = case
-    nacc, tok = tt.verify_logits(V, to_dev(ids), to_dev(off), to_dev(q), to_dev(bits.view(np.int16)),
-                                 to_dev(it), to_dev(ua), to_dev(us), max_m,
-                                 lse=None if lse is None else to_dev(lse))
-    torch.cuda.synchronize()
+    args = [to_dev(a) for a in (ids, off, q, bits.view(np.int16), it, ua, us)]
     o_nacc, o_tok, _ = oracle.verify_logits(V, ids, off, q, bits, it, ua, us, max_m=max_m, lse=lse)
-    assert np.array_equal(nacc.cpu().numpy(), o_nacc), np.nonzero(nacc.cpu().numpy() != o_nacc)[0][:5]
-    assert np.array_equal(tok.cpu().numpy(), o_tok), np.nonzero(tok.cpu().numpy() != o_tok)[0][:5]
+    # the kernels that a workspace allows, and the one kernel of a call without (an empty workspace)
+    for workspace in (None, torch.empty(0, dtype=torch.uint8, device="cuda")):
+        nacc, tok = tt.verify_logits(V, *args, max_m, lse=None if lse is None else to_dev(lse), workspace=workspace)
+        torch.cuda.synchronize()
+        assert np.array_equal(nacc.cpu().numpy(), o_nacc), np.nonzero(nacc.cpu().numpy() != o_nacc)[0][:5]
+        assert np.array_equal(tok.cpu().numpy(), o_tok), np.nonzero(tok.cpu().numpy() != o_tok)[0][:5]
     return o_nacc, Ms
 
 

@@ -230,10 +230,13 @@ def fused(c, max_m, mass=None):
 
     import paper_2510_15545_amd as tt
 
-    nacc, tok = tt.verify_tli(to_dev(c["d2t"]), to_dev(c["t2d"]), to_dev(c["ys"]), to_dev(c["off"]), to_dev(c["qd"]),
-                              to_dev(c["pt"]), to_dev(c["ua"]), to_dev(c["us"]), max_m,
-                              draft_mass=None if mass is None else to_dev(np.asarray(mass, np.float32)), v_d=c["v_d"])
+    args = [to_dev(c[k]) for k in ("d2t", "t2d", "ys", "off", "qd", "pt", "ua", "us")]
+    mass = None if mass is None else to_dev(np.asarray(mass, np.float32))
+    nacc, tok = tt.verify_tli(*args, max_m, draft_mass=mass, v_d=c["v_d"])
+    # the one kernel of a call without a workspace gives the same
+    one = tt.verify_tli(*args, max_m, draft_mass=mass, v_d=c["v_d"], workspace=torch.empty(0, dtype=torch.uint8, device="cuda"))
     torch.cuda.synchronize()
+    assert torch.equal(nacc, one[0]) and torch.equal(tok, one[1])
     return nacc.cpu().numpy(), tok.cpu().numpy()
 
 
