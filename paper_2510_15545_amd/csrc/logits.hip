@@ -859,14 +859,14 @@ __global__ void __launch_bounds__(kThreads) verify_logits_row(ScreenParams p) {
             for (int c = wave; c < nc; c += kWaves) {
                 if (c + kWaves < nc) load16s<false>(row, c + kWaves, lane, v, nx);
                 if ((c + 1) * kChunk <= v) {
-    #pragma unroll
+#pragma unroll
                     for (int k = 0; k < 16; ++k) m = fmaxf(m, scaled(elem(w, k), cb));
                 } else {
-    #pragma unroll
+#pragma unroll
                     for (int k = 0; k < 16; ++k)
                         if (elem_index_s(c, lane, k) < v) m = fmaxf(m, scaled(elem(w, k), cb));
                 }
-    #pragma unroll
+#pragma unroll
                 for (int k = 0; k < 8; ++k) w[k] = nx[k];
             }
             for (int off = kWave / 2; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
@@ -1041,15 +1041,18 @@ int launch_verify_logits(const LogitsArgs &a, void *workspace, size_t workspace_
             hipLaunchKernelGGL(logits_advance, dim3((a.n_streams + kScreenWaves - 1) / kScreenWaves), dim3(kScreenThreads), 0,
                                stream, p, r);
         hipLaunchKernelGGL(logits_screen, dim3(items < kScreenGrid ? items : kScreenGrid), dim3(kScreenThreads), 0, stream, p, r);
+        if (hipGetLastError() != hipSuccess) return TT_ELAUNCH;
     }
     if (rt == kScreenRow) return launch_row<kFrom>(p, stream);
     if (rt == kRowRoute) return launch_row<kWalk>(p, stream);
     const dim3 grid(a.n_streams * p.sum_splits);
     if (rt == kScreenSplit) {
         hipLaunchKernelGGL(logits_sums<false>, grid, dim3(kScreenThreads), 0, stream, p);
+        if (hipGetLastError() != hipSuccess) return TT_ELAUNCH;
         return launch_row<kSums>(p, stream);
     }
     hipLaunchKernelGGL(logits_sums<true>, grid, dim3(kScreenThreads), 0, stream, p);
+    if (hipGetLastError() != hipSuccess) return TT_ELAUNCH;
     hipLaunchKernelGGL(logits_sample, dim3(a.n_streams), dim3(kWave), 0, stream, p);
     return hipGetLastError() == hipSuccess ? TT_OK : TT_ELAUNCH;
 }

@@ -725,9 +725,11 @@ int launch_tli_proposal(const TliArgs &a, hipStream_t stream) {
     for (int64_t r0 = 0; r0 < a.n_rows; r0 += chunk) {
         const int rows = (int)(a.n_rows - r0 < chunk ? a.n_rows - r0 : chunk);
         hipLaunchKernelGGL(tli_mass, dim3(rows * splits), dim3(kThreads), 0, stream, a, (int)r0, splits, slices);
+        if (hipGetLastError() != hipSuccess) return TT_ELAUNCH;
         const int items = rows * slices;
         hipLaunchKernelGGL(tli_fill, dim3((items + kXcds - 1) / kXcds * kXcds), dim3(kFillThreads), 0, stream, a, (int)r0,
                            splits, slices, items);
+        if (hipGetLastError() != hipSuccess) return TT_ELAUNCH;
     }
     return hipGetLastError() == hipSuccess ? TT_OK : TT_ELAUNCH;
 }
@@ -756,8 +758,10 @@ int launch_verify_tli(const TliVerifyArgs &a, void *workspace, size_t workspace_
     p.splits = (p.nc + p.cps - 1) / p.cps;
     if (a.draft_mass != nullptr) hipLaunchKernelGGL(tli_gamma<kWave>, dim3(a.n_streams), dim3(kWave), 0, stream, p);
     else hipLaunchKernelGGL(tli_gamma<kThreads>, dim3(a.n_streams), dim3(kThreads), 0, stream, p);
+    if (hipGetLastError() != hipSuccess) return TT_ELAUNCH;
     const int items = a.n_streams * p.splits;
     hipLaunchKernelGGL(tli_stream, dim3((items + kXcds - 1) / kXcds * kXcds), dim3(kFillThreads), 0, stream, p);
+    if (hipGetLastError() != hipSuccess) return TT_ELAUNCH;
     hipLaunchKernelGGL(tli_sample, dim3(a.n_streams), dim3(kWave), 0, stream, p);
     return hipGetLastError() == hipSuccess ? TT_OK : TT_ELAUNCH;
 }
