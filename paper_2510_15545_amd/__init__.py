@@ -22,6 +22,7 @@ raised.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 __all__ = ["Vocab", "align", "align_workspace", "transfer", "verify", "verify_noalloc", "verify_dense", "verify_workspace", "lib",
@@ -150,28 +151,39 @@ def _ptr(t, dtype, name, allow_none=False):
     raise ValueError(f"{name} must be contiguous")
 
 
-def _on_stream(stream, f, *args, **kwargs):
-    """f(...) with `stream` and its device current (None: as they are)."""
-    if stream is None:
-        return f(*args, **kwargs)
+def _on_stream(stream, f, *args):
+    """f(...) with `stream` and its device current."""
     if not isinstance(stream, torch.cuda.Stream):
         stream = torch.cuda.ExternalStream(stream.cuda_stream)
     with torch.cuda.stream(stream):
-        return f(*args, **kwargs)
+        return f(*args)
+
+
+@functools.lru_cache(maxsize=256)
+def _spread_bytes(query: str, *sizes) -> int:
+    """Bytes that a size query gives (0 where it refuses the sizes: the call itself reports them)."""
+    n = ctypes.c_size_t(0)
+    return n.value if getattr(lib(), query)(*sizes, ctypes.byref(n)) == TT_OK else 0
 
 
 def _spread_workspace(workspace, nbytes: int, caller_out: bool, stream):
-    """The workspace tensor (or None) of a call that can do without one: the caller's, if given (an empty one:
-    none), else nbytes on the stream's device and from its pool, which the allocator hands on only to work that
+    """(tensor, address, bytes) of the workspace of a call that can do without one: the caller's, if given (an empty
+    one: none), else nbytes on the stream's device and from its pool, which the allocator hands on only to work that
     the same stream runs later.  Nothing is allocated while a capture is under way that would otherwise need
     nothing from this module: a capture begun outside torch keeps an address without keeping the memory."""
-    if workspace is not None:
-        if not workspace.is_cuda or not workspace.is_contiguous():
-            raise ValueError("workspace must be a contiguous device tensor")
-        return workspace if workspace.numel() else None
-    if nbytes == 0 or (caller_out and _on_stream(stream, torch.cuda.is_current_stream_capturing)):
-        return None
-    return _on_stream(stream, torch.empty, nbytes, dtype=torch.uint8, device="cuda")
+    if workspace is None:
+        if nbytes == 0:
+            return None, None, 0
+        if stream is not None:
+            return _on_stream(stream, _spread_workspace, None, nbytes, caller_out, None)
+        if caller_out and torch.cuda.is_current_stream_capturing():
+            return None, None, 0
+        workspace = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        return workspace, workspace.data_ptr(), nbytes
+    if not workspace.is_cuda or not workspace.is_contiguous():
+        raise ValueError("workspace must be a contiguous device tensor")
+    size = workspace.numel() * workspace.element_size()
+    return (workspace, workspace.data_ptr(), size) if size else (None, None, 0)
 
 
 def _check(status: int, where: str):
@@ -379,17 +391,14 @@ def verify_logits(v_t: int, target_ids, target_off, q, target_logits, inv_temper
     ids = target_ids if target_ids.numel() else torch.zeros(1, dtype=i32, device=dev)
     qq = q if q.numel() else torch.zeros(1, dtype=f32, device=dev)
     ua = u_accept if u_accept.numel() else torch.zeros(1, dtype=f32, device=dev)
-    nb = ctypes.c_size_t(0)
-    if workspace is None:  # (an argument that the size query refuses is the call's own error)
-        lib().tt_verify_logits_workspace_size(n, int(v_t), int(max_m), 0 if lse is None else 1, ctypes.byref(nb))
-    ws = _spread_workspace(workspace, nb.value, caller_out, stream)
+    nbytes = _spread_bytes("tt_verify_logits_workspace_size", n, int(v_t), int(max_m), 0 if lse is None else 1)
+    _ws, ws, ws_bytes = _spread_workspace(workspace, nbytes, caller_out, stream)
     st = lib().tt_verify_logits_ws(n, int(v_t), _ptr(ids, i32, "target_ids"), _ptr(target_off, i32, "target_off"),
                                 _ptr(qq, f32, "q"), target_logits.data_ptr(),
                                 int(target_logits.stride(0)), _ptr(inv_temperature, f32, "inv_temperature"),
                                 _ptr(lse, f32, "lse", allow_none=True), _ptr(ua, f32, "u_accept"), _ptr(u_sample, f32, "u_sample"), int(max_m),
                                 _ptr(nacc, i32, "n_accepted"), _ptr(tok, i32, "out_token"),
-                                None if ws is None else ws.data_ptr(), 0 if ws is None else ws.nbytes,
-                                _stream_handle(stream))
+                                ws, ws_bytes, _stream_handle(stream))
     _check(st, "tt_verify_logits")
     return out
 
@@ -520,17 +529,15 @@ def verify_tli(d2t, t2d, target_ids, target_off, draft_probs, target_probs, u_ac
     nacc, tok = out
     ids = target_ids if target_ids.numel() else torch.zeros(1, dtype=i32, device=dev)
     ua = u_accept if u_accept.numel() else torch.zeros(1, dtype=f32, device=dev)
-    nb = ctypes.c_size_t(0)
-    if workspace is None:
-        lib().tt_verify_tli_workspace_size(n, v_t, ctypes.byref(nb))
-    ws = _spread_workspace(workspace, nb.value, caller_out, stream)
+    nbytes = _spread_bytes("tt_verify_tli_workspace_size", n, v_t)
+    _ws, ws, ws_bytes = _spread_workspace(workspace, nbytes, caller_out, stream)
     st = lib().tt_verify_tli_ws(n, v_d, v_t, _ptr(d2t, i32, "d2t"), _ptr(t2d, i32, "t2d"), _ptr(ids, i32, "target_ids"),
                              _ptr(target_off, i32, "target_off"), draft_probs.data_ptr(),
                              int(draft_probs.stride(0)), _ptr(draft_mass, f32, "draft_mass", allow_none=True),
                              target_probs.data_ptr(), int(target_probs.stride(0)),
                              _ptr(ua, f32, "u_accept"), _ptr(u_sample, f32, "u_sample"), int(max_m),
                              _ptr(nacc, i32, "n_accepted"), _ptr(tok, i32, "out_token"),
-                             None if ws is None else ws.data_ptr(), 0 if ws is None else ws.nbytes, _stream_handle(stream))
+                             ws, ws_bytes, _stream_handle(stream))
     _check(st, "tt_verify_tli")
     return out
 
