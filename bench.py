@@ -52,12 +52,15 @@ def source_digest(files):
     return h.hexdigest()
 
 
+# the kernels of tt_verify_logits without normalisers, measured as one
+SCREENED = "logits_screen + logits_advance + verify_logits_row"
 # sources each measured kernel is built from (a change to any of them voids its counters)
 KERNEL_SOURCES = {
     "step_fused": ("step.hip", "dtw_rows.h", "dtw_common.h", "verify_core.h"),
     "verify_row": ("verify.hip", "verify_core.h"),
     "dtw_band": ("dtw.hip", "dtw_common.h"),
     "verify_logits_row": ("logits.hip", "verify_core.h"),
+    SCREENED: ("logits.hip", "verify_core.h"),
     "verify_tli_row": ("tli.hip", "verify_core.h"),
 }
 # int32 VALU issue peak of MI355X: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz (a wave64 instruction
@@ -887,10 +890,11 @@ def main_tli(args):
     nacc = torch.empty(n, dtype=torch.int32, device=dev)
     tok = torch.empty(n, dtype=torch.int32, device=dev)
     outs = {}
+    tli_ws = tt.verify_tli_workspace(n, v_t)
 
     def fused(with_mass):
         return lambda i: tt.verify_tli(d2t, t2d, ys, off, qs[i % R], ps[i % R], ua, us, M,
-                                       draft_mass=mass if with_mass else None, out=(nacc, tok))
+                                       draft_mass=mass if with_mass else None, out=(nacc, tok), workspace=tli_ws)
     qbuf = torch.empty((nt, v_t), dtype=torch.float32, device=dev)
     ws = tt.verify_workspace(n, v_t, dev)
 
@@ -1010,11 +1014,12 @@ def main_logits(args):
         row_it = it.repeat_interleave(torch.from_numpy(m + 1).to(dev))
         lse = torch.cat([(logits[0][i:i + 256].float() * row_it[i:i + 256, None]).logsumexp(dim=1)
                          for i in range(0, rows, 256)]).contiguous()
+    ws = tt.verify_logits_workspace(n, V, max_m, lse=lse is not None)
     torch.cuda.synchronize()
     t_gen = time.time() - t_gen
 
     def step(r):
-        tt.verify_logits(V, ids, off, q, logits[r], it, ua, us, max_m, lse=lse, out=(nacc, tok))
+        tt.verify_logits(V, ids, off, q, logits[r], it, ua, us, max_m, lse=lse, out=(nacc, tok), workspace=ws)
 
     for i in range(args.warmup):
         step(i % R)
@@ -1063,9 +1068,10 @@ def main_logits(args):
     elems_per_s = V * rows_read / (ms * 1e-3)
     draft_tokens = int(S.draft_off[-1])
     wl_name = f"{n} streams V_t={V} bf16 logits T=0.7 30% forced" + (" with row log-sum-exp" if lse is not None else "")
+    kernel = "verify_logits_row" if not ws.numel() else SCREENED if lse is None else "logits_sums + logits_sample"
     traffic, note = read_traffic(args.traffic or os.path.join(
-        ROOT, "profiles", "verify_logits_row" + ("_lse" if lse is not None else "") + "_counters.txt"),
-        wl_name, "verify_logits_row")
+        ROOT, "profiles", "verify_logits_row_lse_counters.txt" if lse is not None else "verify_logits_screened_counters.txt"),
+        wl_name, kernel)
     result = {
         "metric": "verified draft tokens/s from bf16 logits (T=0.7) at V_t=151,936; HBM GB/s vs peak",
         "value": round(draft_tokens / (ms * 1e-3), 1), "unit": "draft tokens/s", "n_gpus": 1,
@@ -1075,7 +1081,7 @@ def main_logits(args):
                    "target_positions": int(m.sum()), "v_t": V, "replicas": R, "path": "tt_verify_logits" + ("+lse" if lse is not None else ""),
                    "launch": "eager" if args.eager else "hip-graph of %d steps" % gs},
         "accept": {"mean_gamma": round(float(acc.mean()), 3), "rows_read": rows_read},
-        "roofline": {"kernel": "verify_logits_row", "bound": "hbm", "achieved": round(gbs, 1),
+        "roofline": {"kernel": kernel, "bound": "hbm", "achieved": round(gbs, 1),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "traffic_note": note, "algorithmic_bytes_per_launch": kbytes,
                      "launch_us": round(ms * 1e3, 2), "logits_per_s": round(elems_per_s, 1)},
