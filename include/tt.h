@@ -277,8 +277,9 @@ int tt_verify_dense(int32_t n_streams, int32_t v,
  * tt_verify_logits_ws is the same call with a workspace of tt_verify_logits_workspace_size bytes
  * (with_lse: whether lse will be given; 0 bytes where the one kernel is the better one; no
  * initialisation; calls that overlap in time must not share it): the rows of a stream are then
- * spread over the GPU, several kernels on `stream`, with the same results.  A null workspace is
- * tt_verify_logits; TT_EWORKSPACE when it is too small.
+ * spread over the GPU, up to nine kernels on `stream`, with the same results.  A null workspace is
+ * tt_verify_logits, the better call where nearly every stream stops at its first position;
+ * TT_EWORKSPACE when the workspace is too small.
  */
 int tt_verify_logits_workspace_size(int32_t n_streams, int32_t v_t, int32_t max_m, int32_t with_lse, size_t *bytes);
 int tt_verify_logits_ws(int32_t n_streams, int32_t v_t, const int32_t *target_ids, const int32_t *target_off,
@@ -410,8 +411,12 @@ int tt_vocab_intersection(const tt_vocab *vd, const void *vd_index, size_t vd_in
  * q is clamped to [0, 1] (NaN -> 0); S is the sum of the intersected q(x), each
  * truncated to a multiple of 2^-62, formed exactly and rounded once to the nearest
  * fp32 (ties to even); q'(y) is the fp32 quotient.  A row with S = 0 is written as
- * zeros.  One kernel on `stream` (a workgroup per row), no workspace.  TT_EINVAL for
- * n_rows < 0, v_d or v_t < 1, a stride below its row length or a missing pointer.
+ * zeros.  No workspace: one kernel on `stream` (a workgroup per row), or for long rows two
+ * per part of the rows (the masses, then the rows), which hand the masses over in q_out: it
+ * is read as well as written during the call, so it must be readable device memory, must
+ * not overlap draft_probs or the maps, and must not be touched by other work until the
+ * call's last kernel is done.  TT_EINVAL for n_rows < 0, v_d or v_t < 1, a stride below
+ * its row length or a missing pointer.
  */
 int tt_tli_proposal(int32_t n_rows, int32_t v_d, int32_t v_t, const int32_t *d2t, const int32_t *t2d,
                     const float *draft_probs, int64_t draft_ld, float *q_out, int64_t q_ld, void *stream);
@@ -452,9 +457,10 @@ int tt_verify_tli(int32_t n_streams, int32_t v_d, int32_t v_t, const int32_t *d2
  */
 int tt_verify_tli_workspace_size(int32_t n_streams, int32_t v_t, size_t *bytes);
 int tt_verify_tli_ws(int32_t n_streams, int32_t v_d, int32_t v_t, const int32_t *d2t, const int32_t *t2d,
-                  const int32_t *target_ids, const int32_t *target_off, const float *draft_probs, int64_t draft_ld,
-                  const float *draft_mass, const float *target_probs, int64_t target_ld, const float *u_accept,
-                  const float *u_sample, int32_t max_m, int32_t *n_accepted, int32_t *out_token, void *workspace, size_t workspace_bytes, void *stream);
+                     const int32_t *target_ids, const int32_t *target_off, const float *draft_probs,
+                     int64_t draft_ld, const float *draft_mass, const float *target_probs, int64_t target_ld,
+                     const float *u_accept, const float *u_sample, int32_t max_m, int32_t *n_accepted,
+                     int32_t *out_token, void *workspace, size_t workspace_bytes, void *stream);
 
 /*
  * Workspace bytes tt_step needs: the larger of tt_align_workspace_size and

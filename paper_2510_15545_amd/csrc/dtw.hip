@@ -154,7 +154,7 @@ __host__ __device__ inline LdsPlan plan_lds(int32_t max_k, int32_t max_m, int32_
 // row r's token is c.  At 16 bytes a mask gathered from the token costs about 26 VALU instructions and
 // a distance needs two or more; a table turns each into one LDS read.  Two strips' tables take
 // 64 KB, so only batches that leave every pair a compute unit of its own have them: 96 pairs of
-// 16-128 tokens (up to 16 bytes) without a band take 144 us (193 with masks gathered and a ranking kernel).
+// 16-128 tokens (up to 16 bytes) without a band take 147 us (193 with masks gathered and a ranking kernel).
 // The table makes the target token the text; gathered masks let the shorter token be it, so the
 // tables pay only where draft tokens are long: a pair uses them when a quarter of its draft
 // tokens have more than kEqLong bytes.  Tokens of 1-16 bytes, evenly: 0.84 of the time without tables; drafts so and

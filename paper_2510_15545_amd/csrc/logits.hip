@@ -446,8 +446,9 @@ __device__ __forceinline__ uint64_t lse_residual(const LseScan &rec) {
 // row per stream).  Rows go in rounds: round r screens a window of positions of the streams
 // that every earlier window accepted whole, each window three times as long as the one before, so a
 // few launches cover any number of positions and little is read that no test needs.  The same
-// batch takes 88 us (rounds of 18, 23 and 12 us, the walk 22); 64 streams 48 against 195, 32
-// streams of 32,000 25 against 59, 512 of 32,000 96 against 113.
+// batch takes 84 us (rounds of 18, 22 and 11 us, 5 between, the walk 22).  Where half of the tests accept, 4 to 16
+// positions a stream, against one workgroup per stream: 64 streams 44 against 118, 8 streams 22 against 51; of 32,000
+// logits 64 streams 26 against 59, 512 70 against 89; of 4,000 logits 256 streams 24 against 47.
 //
 // The margin: P = E / S and its estimate e / s differ (relative, |mu| < 512, q < 2^60) by
 //   3.2e-5  exponents of the exact weights held at 31 (mu rounded by at most 2^-16, 31 - mu by
@@ -949,8 +950,8 @@ Route route(const LogitsArgs &a, int nc) {
     // Speed against the one kernel where half of the tests accept.  One test a stream: two kernels more cost what
     // the second row's walk takes, so only few streams of long rows gain (64 streams of 32,000 logits 1.17 times; of
     // 4,000 below 0.95, 200 of 32,000 0.73).  Two tests: not while rows of middling length fill the chip (200 streams of
-    // 32,000 to 64,000 logits 0.84 to 0.95; of 4,000 1.09, of 151,936 1.05).  From three on 1.0 to 4 times; one
-    // stream alone gains or loses by its own luck.  A batch that rejects every first proposal loses with any
+    // 32,000 to 64,000 logits 0.84 to 0.95; of 4,000 1.09, of 151,936 1.05).  From three on 1.0 to 4 times, but
+    // few streams gain or lose by their luck (one stream 0.64 to 3.6).  A batch that rejects every first proposal loses with any
     // number (0.4 to 0.75 times; 8 streams of 151,936 logits 1.0): a caller that knows gives no workspace.
     const bool screened = a.n_streams <= kScreenStreams &&
                           (a.max_m >= 3 || (a.max_m == 2 && (a.n_streams <= 128 || nc <= 8 || nc >= 128)) ||

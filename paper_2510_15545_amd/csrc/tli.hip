@@ -17,7 +17,7 @@
 // the XCD's L2.  A row's slices run together on one XCD (3 to 4 rows of 512 KB in flight there);
 // with one workgroup per row 32 rows (16 MB) were, and nearly every gather went to the Infinity
 // Cache.  1,024 rows of 128,256 -> 151,936 ids with 60% shared: 1,215 us with one workgroup per
-// row, 530 so (tli_fill about 200 G gathers/s).  Short rows keep the one kernel
+// row, 511 so (tli_fill about 200 G gathers/s).  Short rows keep the one kernel
 // (tli_rows).  The maps are shared by every row and stay in cache.
 #include "verify_core.h"
 

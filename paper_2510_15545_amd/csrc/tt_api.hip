@@ -180,12 +180,11 @@ int tt_verify_tli(int32_t n_streams, int32_t v_d, int32_t v_t, const int32_t *d2
                             target_probs, target_ld, u_accept, u_sample, max_m, n_accepted, out_token, nullptr, 0, stream);
 }
 
-
 int tt_verify_tli_ws(int32_t n_streams, int32_t v_d, int32_t v_t, const int32_t *d2t, const int32_t *t2d,
-                  const int32_t *target_ids, const int32_t *target_off, const float *draft_probs, int64_t draft_ld,
-                  const float *draft_mass, const float *target_probs, int64_t target_ld, const float *u_accept,
-                  const float *u_sample, int32_t max_m, int32_t *n_accepted, int32_t *out_token, void *workspace,
-                     size_t workspace_bytes, void *stream) {
+                     const int32_t *target_ids, const int32_t *target_off, const float *draft_probs,
+                     int64_t draft_ld, const float *draft_mass, const float *target_probs, int64_t target_ld,
+                     const float *u_accept, const float *u_sample, int32_t max_m, int32_t *n_accepted,
+                     int32_t *out_token, void *workspace, size_t workspace_bytes, void *stream) {
     if (n_streams < 0 || v_d < 1 || v_t < 1 || draft_ld < v_d || target_ld < v_t || max_m < 0 ||
         max_m > kMaxVerifyLen)
         return TT_EINVAL;
