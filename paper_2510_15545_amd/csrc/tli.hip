@@ -45,11 +45,15 @@ constexpr int kCus = 256;
 // 35.3; 256 of 12,000 -> 50,000: 18.8 against 16.0, 23.0 against 20.7).
 constexpr int kFewRows = 64, kFewRowsVocab = 65536;
 constexpr int kManyRowsDraft = 16384, kManyRowsTarget = 32768;
-// Once rows take half of the compute units and more only from longer draft rows on, up to one row each longer still:
-// 256 rows of 17,000 -> 33,000 ids 15.8 us against 13.7 with few shared tokens, 24.0 against 22.5 with most; of 28,000 ->
-// 33,000 18.9 against 16.0 and 31.2 against 33.8; 1,024 of 17,000 -> 33,000 50.2 against 45.3 and 71.1 against 71.3, of
-// 24,000 -> 40,000 57.9 against 59.8 and 95.5 against 106; but 128 of 17,000 -> 33,000 12.3 against 12.5 and 14.7 against 17.4.
-constexpr int kHalfFull = 128, kFullDraft = 28672, kSeveralDraft = 20480;
+// Rows that take between half and all of the compute units are in flight all at once, one on each, so one kernel has no
+// last wave of rows to wait for: there two kernels only from longer draft rows on, or with target rows long enough that
+// the spread writes pay.  Three sets of buffers in turn, two kernels against one, few shared tokens and most: 256 rows of
+// 17,000 -> 33,000 ids 16.4 us against 13.8 and 22.5 against 21.9, of 28,000 -> 33,000 18.7 against 16.3 and 31.3 against
+// 34.3, of 17,000 -> 75,296 24.5 against 20.9 and 30.4 against 29.8, of 24,000 -> 88,001 30.0 against 27.4 and 37.2
+// against 47.3; but 130 of 17,000 -> 60,000 15.3 against 16.0 and 18.4 against 22.4, 257 of 17,000 -> 33,000 20.2 against
+// 21.0 and 25.8 against 31.0, 1,024 52.2 against 56.0 and 73.0 against 80.4 (475, the worst seen, 26.8 against 25.2 and
+// 37.2 against 37.1).
+constexpr int kHalfFull = 128, kFullDraft = 28672, kFullTarget = 81920;
 constexpr int64_t kCacheBytes = int64_t(256) << 20;  // the Infinity Cache
 constexpr int64_t kMaxItems = int64_t(1) << 21;      // workgroups of one grid
 // Verification with the proposal formed on the fly: a row is spread over workgroups from this many
@@ -704,9 +708,9 @@ inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 int launch_tli_proposal(const TliArgs &a, hipStream_t stream) {
     if (a.n_rows == 0) return TT_OK;
+    const bool full = a.n_rows > kHalfFull && a.n_rows <= kCus;  // one kernel: every row at once, on most of the chip
     const bool two = a.n_rows <= kFewRows ? (int64_t)a.v_d + a.v_t >= kFewRowsVocab
-                                          : a.v_t > kManyRowsTarget && a.v_d > (a.n_rows <= kHalfFull ? kManyRowsDraft
-                                                                                : a.n_rows <= kCus ? kFullDraft : kSeveralDraft);
+                                          : a.v_t > kManyRowsTarget && a.v_d > (full && a.v_t <= kFullTarget ? kFullDraft : kManyRowsDraft);
     if (!two) {
         hipLaunchKernelGGL(tli_rows, dim3(a.n_rows), dim3(kThreads), 0, stream, a);
         return hipGetLastError() == hipSuccess ? TT_OK : TT_ELAUNCH;

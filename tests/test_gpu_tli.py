@@ -136,8 +136,8 @@ def test_proposal_at_the_benchmark_vocabulary_sizes():
 
 @pytest.mark.parametrize("v_d,v_t,n", [(65531, 5, 3), (65531, 4, 3), (65500, 63, 3), (65500, 64, 4), (63600, 2047, 9),
                                        (63600, 2049, 64), (63600, 2049, 65), (33000, 36863, 130), (16385, 32769, 70),
-                                       (16384, 32769, 70), (65537, 6145, 1), (100, 65436, 2), (28672, 32769, 129), (28673, 32769, 129), (20480, 32769, 257), (20481, 32769, 257),
-                                       (16385, 32769, 128)])
+                                       (16384, 32769, 70), (65537, 6145, 1), (100, 65436, 2), (28672, 32769, 129), (28673, 32769, 129),
+                                       (16385, 81920, 129), (16385, 81921, 256), (16385, 32769, 257), (16385, 32769, 128)])
 def test_proposal_rows_in_two_kernels(v_d, v_t, n):
     """Around the rule's line, slices with and without a remainder, a row's mass in 1 to 16 parts."""
     rng = np.random.default_rng(v_d + v_t + n)
