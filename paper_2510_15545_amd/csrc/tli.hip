@@ -17,7 +17,7 @@
 // the XCD's L2.  A row's slices run together on one XCD (3 to 4 rows of 512 KB in flight there);
 // with one workgroup per row 32 rows (16 MB) were, and nearly every gather went to the Infinity
 // Cache.  1,024 rows of 128,256 -> 151,936 ids with 60% shared: 1,215 us with one workgroup per
-// row, 511 so (tli_fill about 200 G gathers/s).  Short rows keep the one kernel
+// row, 499 so (tli_fill about 200 G gathers/s).  Short rows keep the one kernel
 // (tli_rows).  The maps are shared by every row and stay in cache.
 #include "verify_core.h"
 
@@ -40,9 +40,11 @@ constexpr int kCus = 256;
 // (16 rows of 78,456 -> 14,532 ids 9.9 us against 15.7 in one kernel, of 128,256 -> 151,936 17.4
 // against 87; of 30,000 -> 4,000 10.6 against 7.9).  Many rows: when the draft rows in flight in one
 // kernel (one per CU, 32 per XCD) overflow the XCD's 4 MB L2 and there are target ids enough to
-// gather for, whatever their share (300 rows of 32,000 -> 50,257: 34.5 us against 36.3 with few shared
+// gather for (300 rows of 32,000 -> 50,257: 34.5 us against 36.3 with few shared
 // tokens, 49.6 against 65.8 with 70%; 256 rows of 40,000 -> 22,000: 23.7 against 17.2, 32.8 against
-// 35.3; 256 of 12,000 -> 50,000: 18.8 against 16.0, 23.0 against 20.7).
+// 35.3; 256 of 12,000 -> 50,000: 18.8 against 16.0, 23.0 against 20.7).  The share is not known here: with 5% of
+// the tokens shared and v_t about v_d or less two kernels take up to 1.15 times as long (600 rows of 60,000 -> 40,000 85 us
+// against 80), with 60% 0.7 of the time (120 against 180).
 constexpr int kFewRows = 64, kFewRowsVocab = 65536;
 constexpr int kManyRowsDraft = 16384, kManyRowsTarget = 32768;
 // Rows that take between half and all of the compute units are in flight all at once, one on each, so one kernel has no
@@ -54,7 +56,14 @@ constexpr int kManyRowsDraft = 16384, kManyRowsTarget = 32768;
 // 21.0 and 25.8 against 31.0, 1,024 52.2 against 56.0 and 73.0 against 80.4 (475, the worst seen, 26.8 against 25.2 and
 // 37.2 against 37.1).
 constexpr int kHalfFull = 128, kFullDraft = 28672, kFullTarget = 81920;
-constexpr int64_t kCacheBytes = int64_t(256) << 20;  // the Infinity Cache
+// Draft bytes, and draft and target bytes, of a part of the rows.  tli_fill gathers from the draft rows that tli_mass has
+// read: they stay in the 256 MB Infinity Cache only if the part's own writes, which go through it as well, leave room;
+// up to kPartSmall of draft bytes a part is not worth dividing.  Three sets of buffers in turn, against parts of 256 MB of
+// draft bytes alone, 5% of the tokens shared and 60%: 1,024 rows of 40,000 -> 50,257 ids 113 us against 134 and 163 against
+// 186 (one kernel 106 and 210), of 40,000 -> 151,936 180 against 243 and 267 against 302 (180 and 326), of 128,256 ->
+// 151,936 330 against 350 and 492 against 507 (370 and 1,180); 2,048 of 24,000 -> 75,296 206 against 273 (197).  By all
+// bytes alone 768 rows of 17,000 -> 151,936 took 98 us, 89 so; with 112 MB of draft bytes 400 rows of 60,000 -> 40,000 went in two parts, 55, 48 so.
+constexpr int64_t kPartDraft = int64_t(128) << 20, kPartBytes = int64_t(340) << 20, kPartSmall = int64_t(80) << 20;
 constexpr int64_t kMaxItems = int64_t(1) << 21;      // workgroups of one grid
 // Verification with the proposal formed on the fly: a row is spread over workgroups from this many
 // chunks on and up to this many streams, more for long rows.  128,256 -> 151,936 ids with the
@@ -716,12 +725,15 @@ int launch_tli_proposal(const TliArgs &a, hipStream_t stream) {
         return hipGetLastError() == hipSuccess ? TT_OK : TT_ELAUNCH;
     }
     const int slices = a.v_t >= kSlice ? a.v_t / kSlice : 1;
-    // rows whose draft bytes fit the Infinity Cache go through both kernels together, in multiples
-    // of the compute units (a mass workgroup takes one), few enough for one grid
-    int64_t chunk = kCacheBytes / (4 * (int64_t)a.v_d);
+    // the rows go through both kernels in equal parts, multiples of the compute units (a mass workgroup takes one),
+    // a short rest with the part before it, each part few enough for one grid
+    const int64_t draft_row = 4 * (int64_t)a.v_d, row = draft_row + 4 * (int64_t)a.v_t;
+    int64_t chunk = kPartDraft / draft_row < kPartBytes / row ? kPartDraft / draft_row : kPartBytes / row;
+    if (chunk < kPartSmall / draft_row) chunk = kPartSmall / draft_row;
     chunk = chunk < kCus ? kCus : chunk / kCus * kCus;
+    const int64_t parts = (a.n_rows + chunk - 1) / chunk;
+    chunk = a.n_rows <= chunk + kCus / 4 ? a.n_rows : ((a.n_rows + parts - 1) / parts + kCus - 1) / kCus * kCus;
     if (chunk > kMaxItems / slices) chunk = kMaxItems / slices;
-    if (chunk > a.n_rows || (4 * (int64_t)a.v_d * a.n_rows <= kCacheBytes && a.n_rows <= kMaxItems / slices)) chunk = a.n_rows;
     int splits = (int)(kCus / chunk);
     if (splits > kMaxSplits) splits = kMaxSplits;
     while (splits > 1 && (splits * 4 > a.v_t || a.v_d / splits < 4096)) --splits;

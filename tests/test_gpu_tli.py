@@ -166,6 +166,20 @@ def test_proposal_rows_past_the_cache():
         assert torch.equal(whole[a:b], tt.tli_proposal(d2t, t2d, q[a:b]))
 
 
+@pytest.mark.parametrize("v_d,v_t,n", [(131072, 33000, 320), (131072, 33000, 321), (17000, 151936, 577), (66000, 33000, 1025)])
+def test_proposal_rows_in_parts(v_d, v_t, n):
+    """Rows on both sides of the parts' ends, by their draft bytes and by all bytes: the same alone."""
+    import torch
+
+    import paper_2510_15545_amd as tt
+
+    d2t, t2d = (to_dev(x) for x in random_maps(np.random.default_rng(n), v_d, v_t, 0.6))
+    q = torch.rand((n, v_d), generator=torch.Generator(device="cuda").manual_seed(n), device="cuda") / v_d
+    whole = tt.tli_proposal(d2t, t2d, q)
+    for a in range(0, n, 64):
+        assert torch.equal(whole[a:a + 64], tt.tli_proposal(d2t, t2d, q[a:a + 64]))
+
+
 def test_standard_sd_on_the_tli_proposal():
     """Alg. 3 then Alg. 4 on the GPU: q' from tt_tli_proposal, drafts drawn from q', then
     tt_verify_dense; accept counts and tokens equal the oracle's on the oracle's q'."""
