@@ -397,7 +397,8 @@ __device__ __forceinline__ void load_px_strided(const TliVerifyArgs &a, const fl
 // rounded quotient (Markstein 1990), so q' is the IEEE quotient in 5 instructions instead of the 10 of
 // a division.  The first step takes g * r (within two units) to within one.  Exact while nothing
 // underflows: S in [2^-30, 2^10] and g = 0 or g >= 2^-60; else the division.  256 streams of
-// 151,936 ids: 61.6 us, 63.6 with divisions.
+// 151,936 ids: 61.6 us, 63.6 with divisions.  S = 0, as for a bonus row, needs none (every quotient is
+// defined as 0): 64 streams of 16,384 ids that accept every proposal 9.1 us, 9.4 with divisions.
 struct RowMass {
     float S, r;
     bool fast;
@@ -406,8 +407,8 @@ struct RowMass {
 __device__ __forceinline__ RowMass row_reciprocal(float S) {
     RowMass m;
     m.S = S;
-    m.r = 1.0f / S;
-    m.fast = S >= 0x1p-30f && S <= 0x1p10f;
+    m.r = S == 0.0f ? 0.0f : 1.0f / S;
+    m.fast = S == 0.0f || (S >= 0x1p-30f && S <= 0x1p10f);
     return m;
 }
 
