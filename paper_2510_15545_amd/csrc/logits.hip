@@ -936,17 +936,22 @@ constexpr int kCus = 256;
 constexpr int kSumGrid = 1024;     // workgroups of logits_sums to aim for
 constexpr int kScreenGrid = 2048;  // workgroups of a screening round
 // With normalisers, the row split over workgroups and sampled by a second kernel: for rows long enough
-// to pay for that launch and streams too few to fill the chip.  32 streams of 151,936: 10.9 us against
-// 17.9 in one kernel, 128: 18.1 against 19.9, 200: 22.9 against 20.9; 32 of 32,000: 8.8 against 10.1,
-// 32 of 16,000: 10.2 against 9.6, 128 of 20,000 11.0 against 10.2.
+// to pay for that launch, longer the more streams there are to fill the chip without it.  Three sets of buffers in
+// turn: 32 streams of 151,936 logits 11.5 us against 18.1 in one kernel, of 32,768 8.9 against 9.4; 64 of 28,672 9.4
+// against 9.4, of 64,000 10.3 against 12.3; 100 of 57,344 11.5 against 11.2, of 64,000 11.9 against 12.4; 128 of 40,960
+// 11.5 against 10.3, of 81,920 13.6 against 13.4, of 100,000 15.1 against 15.1, of 151,936 17.8 against 19.0; 200 of
+// 151,936 22.9 against 20.9.  32 of 16,000 10.2 against 9.6.
 constexpr int kLseSplitStreams = 128;
 constexpr int kLseSplitChunks = 28;
+constexpr int kLseSplitPerStream = 36;  // chunks and this at least the number of streams
 
 // Which kernels a call takes (with a workspace).
 enum Route { kRowRoute, kLseSplit, kScreenRow, kScreenSplit };
 
 Route route(const LogitsArgs &a, int nc) {
-    if (a.lse != nullptr) return a.n_streams <= kLseSplitStreams && nc >= kLseSplitChunks ? kLseSplit : kRowRoute;
+    if (a.lse != nullptr)
+        return a.n_streams <= kLseSplitStreams && nc >= kLseSplitChunks && nc + kLseSplitPerStream >= a.n_streams ? kLseSplit
+                                                                                                                  : kRowRoute;
     // Speed against the one kernel where half of the tests accept.  One test a stream: two kernels more cost what
     // the second row's walk takes, so only few streams of long rows gain (64 streams of 32,000 logits 1.17 times; of
     // 4,000 below 0.95, 200 of 32,000 0.73).  Two tests: not while rows of middling length fill the chip (200 streams of

@@ -242,7 +242,7 @@ def test_logits_screened_rows(n, V, max_m):
 
 
 @pytest.mark.parametrize("n,V", [(1, 15361), (3, 16384), (128, 15400), (129, 15400), (2, 40001), (1, 27648), (1, 27649),
-                                 (128, 27700), (129, 27700)])
+                                 (128, 27700), (129, 27700), (64, 27649), (65, 28672), (65, 28673)])
 def test_logits_lse_split_rows(n, V):
     """With normalisers, around the line to the split kernels; ragged rows, sentinels among the streams."""
     ids, off, q, bits, it, ua, us, Ms = logits_case(n, V, seed=6, max_m=5)
